@@ -136,6 +136,13 @@ struct DevBuf {
         if (e == hipSuccess) bytes = want;
         return e;
     }
+    // The same where another path is left: false, with no error pending, when
+    // the device has no room.
+    bool try_ensure(size_t n) {
+        if (ensure(n) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
+    }
     template <typename T>
     T *as() const { return static_cast<T *>(p); }
 };
@@ -171,6 +178,7 @@ struct DevCtx {
     DevBuf setup, adj, adjbits, nbr, ipos, deg, rowcnt, rowbase, edges_tmp, edges, min_accept, rdepth, pool, ctl;
     DevBuf pstat, ecnt;  // per-problem counters of multi-dataset searches
     DevBuf pair_part;    // partial Gram tiles of depth 0 through the pair contraction
+    DevBuf planes;       // bit planes of the columns
     DevBuf tri_node, tri_rowoff, tri_eidx, tri_part;  // depth 1 through the masked contractions
     DevBuf pairs_setup, pairs_out;  // bns_ci_pairs: tile plan and results
     DevBuf err_val, err_tag, err_cnt;  // verification log
@@ -637,12 +645,14 @@ extern "C" bns_status bns_ci_batch_noalloc(const bns_dataset *ds, const bns_ci_t
     return BNS_OK;
 }
 
-// Depth 0 through the pair contraction: one-hot column maps, tiles and
-// sample chunks of every problem.
+// Depth 0 through the pair contraction: rows of the Gram matrix (bit planes,
+// or one-hot columns in the byte form), tiles and sample chunks of every
+// problem.
 struct PairPlan {
     bool on = false;
-    int T = 64;
+    bool planes = false;
     int64_t chunk = 0, items = 0, tiles = 0, part_bytes = 0, gram_bytes = 0;
+    int64_t plane_bytes = 0, plane_items = 0;
     std::vector<GramProb> gps;
     std::vector<int32_t> oh_var, var_oh;
     std::vector<uint16_t> oh_cat;
@@ -655,47 +665,74 @@ static const int64_t kPairPartMax = 1ll << 30;
 // MI355X, 8.9e7 (60 variables, 50,000 samples) is faster in the test kernel,
 // 2.4e9 (220 variables, 100,000 samples) and more through the contraction.
 static const double kPairsAutoWork = 5e8;
+// Bit planes kept between calls; a larger buffer goes at the end of its call.
+static const size_t kPlanesKeep = 512ull << 20;
 // Depth 1 through the masked contractions: work items held at most (64 KiB
 // each; beyond, the depth runs in the test kernel).
 static const int64_t kTriItemsMax = 16384;
 
-static bns_status plan_pairs(const DevCtx &dc, const bns_dataset *const *ds, int32_t P, PairPlan &pp) {
+// planes: bit planes wanted; they are used when they take no more memory than
+// the columns (a mean cardinality of at most 9) or than 64 MiB.
+static bns_status plan_pairs(const DevCtx &dc, const bns_dataset *const *ds, int32_t P, bool planes, PairPlan &pp) {
     pp = PairPlan();
-    int64_t m_max = 1;
-    for (int32_t k = 0; k < P; ++k) m_max = std::max(m_max, ds[k]->m);
-    // 64 x 64 tiles: a workgroup's LDS (two steps of 2 x 64 one-hot columns)
-    // leaves room for more workgroups per CU than 128 x 128 tiles do, which
-    // the expansion and LDS traffic need more than the larger tiles' reuse
-    // (1,000 variables: 3.91 -> 3.46 ms; 64 datasets: 3.01 -> 2.58 ms)
-    pp.T = 64;
-    const int64_t T = pp.T;
+    const int64_t T = kGramT;
+    int64_t m_max = 1, plane_bytes = 0;
+    double col_bytes = 0.0, tile_samples = 0.0;
+    for (int32_t k = 0; k < P; ++k) {
+        m_max = std::max(m_max, ds[k]->m);
+        const int64_t blocks = (ds[k]->m + kPlaneBlock - 1) / kPlaneBlock;
+        for (uint8_t c : ds[k]->cards) plane_bytes += (c - 1) * blocks * (kPlaneBlock / 8);
+        col_bytes += (double)ds[k]->n * (double)ds[k]->m;
+    }
+    pp.planes = planes && (double)plane_bytes <= std::max(col_bytes, 64.0 * 1048576.0);
+    // 64 x 64 tiles.  Bytes: a workgroup's LDS (two steps of 2 x 64 one-hot
+    // columns) leaves room for more workgroups per CU than 128 x 128 tiles
+    // do, which the expansion and LDS traffic need more than the larger
+    // tiles' reuse (1,000 variables: 3.91 -> 3.46 ms; 64 datasets: 3.01 ->
+    // 2.58 ms).
     int64_t tiles = 0;
     std::vector<int64_t> tiles_k((size_t)P);
     for (int32_t k = 0; k < P; ++k) {
         int64_t R = 0;
-        for (uint8_t c : ds[k]->cards) R += c;
+        for (uint8_t c : ds[k]->cards) R += c - (pp.planes ? 1 : 0);
         const int64_t nb = (R + T - 1) / T;
         tiles_k[k] = nb * (nb + 1) / 2;
         tiles += tiles_k[k];
+        tile_samples += (double)tiles_k[k] * (double)ds[k]->m;
     }
     // about two work items per workgroup slot of the device: split the
     // samples into chunks when the tiles alone are fewer
-    const int64_t want = 2ll * dc.num_cu * gram_max_wg_per_cu(pp.T);
-    int64_t chunk = (m_max + 63) / 64 * 64;
-    if (tiles < want) chunk = std::max<int64_t>(2048, ((m_max * tiles + want - 1) / want + 63) / 64 * 64);
-    pp.chunk = std::min(chunk, (m_max + 63) / 64 * 64);
+    const int64_t unit = pp.planes ? kPlaneBlock : 64;
+    const int64_t least = pp.planes ? 4096 : 2048;
+    const int64_t want = 2ll * dc.num_cu * gram_max_wg_per_cu(pp.planes);
+    const int64_t whole = (m_max + unit - 1) / unit * unit;
+    int64_t chunk = whole;
+    if (pp.planes) {
+        // (by the mean work per tile: datasets of different lengths)
+        chunk = std::max<int64_t>(least, (int64_t)(tile_samples / (double)want) / unit * unit);
+    } else if (tiles < want) chunk = std::max<int64_t>(least, ((m_max * tiles + want - 1) / want + unit - 1) / unit * unit);
+    pp.chunk = std::min(chunk, whole);
     pp.gps.resize((size_t)P);
-    pp.var_oh.clear();
+    int32_t var_off = 0;
+    int64_t plane_words = 0;
     for (int32_t k = 0; k < P; ++k) {
         const bns_dataset *d = ds[k];
         GramProb &g = pp.gps[k];
+        std::memset(&g, 0, sizeof(g));
         g.data = d->d_data;
         g.ld = d->ld;
         g.m = d->m;
+        g.n = d->n;
+        g.var_off = var_off;
+        var_off += d->n;
         g.oh_base = (int32_t)pp.oh_var.size();
         int32_t R = 0;
         for (int32_t v = 0; v < d->n; ++v) {
             pp.var_oh.push_back(R);
+            if (pp.planes) {
+                R += d->cards[v] - 1;
+                continue;
+            }
             const uint16_t wide = d->cards[v] > 8 ? 0x100 : 0;
             for (int x = 0; x < d->cards[v]; ++x) {
                 pp.oh_var.push_back(v);
@@ -704,18 +741,28 @@ static bns_status plan_pairs(const DevCtx &dc, const bns_dataset *const *ds, int
             R += d->cards[v];
         }
         const int64_t Rp = (R + T - 1) / T * T;
-        for (int64_t c = R; c < Rp; ++c) {
-            pp.oh_var.push_back(-1);
-            pp.oh_cat.push_back(0);
-        }
-        g.R = (int32_t)Rp;
+        if (!pp.planes)
+            for (int64_t c = R; c < Rp; ++c) {
+                pp.oh_var.push_back(-1);
+                pp.oh_cat.push_back(0);
+            }
+        g.R = pp.planes ? R : (int32_t)Rp;
         g.nb = (int32_t)(Rp / T);
         g.nchunks = (int32_t)((d->m + pp.chunk - 1) / pp.chunk);
         g.item_base = pp.items;
         g.tile_base = pp.tiles;
         pp.items += tiles_k[k] * g.nchunks;
         pp.tiles += tiles_k[k];
+        if (pp.planes) {
+            const int64_t blocks = (d->m + kPlaneBlock - 1) / kPlaneBlock;
+            g.plane_off = plane_words;
+            g.plane_stride = blocks * (kPlaneBlock / 32);
+            g.plane_item = pp.plane_items;
+            plane_words += (int64_t)R * g.plane_stride;
+            pp.plane_items += (int64_t)d->n * ((g.plane_stride + 64 * kPlaneItem - 1) / (64 * kPlaneItem));
+        }
     }
+    pp.plane_bytes = plane_words * 4;
     pp.part_bytes = pp.items * T * T * 4;
     pp.gram_bytes = pp.items > pp.tiles ? pp.tiles * T * T * 4 : 0;  // summed tiles (when chunks were split)
     if (pp.part_bytes + pp.gram_bytes > kPairPartMax || (int64_t)pp.oh_var.size() > INT32_MAX) {
@@ -727,6 +774,39 @@ static bns_status plan_pairs(const DevCtx &dc, const bns_dataset *const *ds, int
     pp.on = true;
     return BNS_OK;
 }
+
+// The device arrays of a pair plan: the setup sections at sb (offsets o_*),
+// partial tiles and planes.
+static PairArgs pair_args(const DevCtx &dc, const PairPlan &pp, char *sb, size_t o_gp, size_t o_ohvar, size_t o_ohcat,
+                          size_t o_varoh) {
+    PairArgs pa;
+    std::memset(&pa, 0, sizeof(pa));
+    pa.gp = (const GramProb *)(sb + o_gp);
+    pa.planes = pp.planes ? dc.planes.as<uint32_t>() : nullptr;
+    pa.oh_var = (const int32_t *)(sb + o_ohvar);
+    pa.oh_cat = (const uint16_t *)(sb + o_ohcat);
+    pa.var_oh = (const int32_t *)(sb + o_varoh);
+    pa.part = dc.pair_part.as<int32_t>();
+    pa.gram = pp.gram_bytes ? pa.part + pp.part_bytes / 4 : pa.part;
+    pa.items = pp.items;
+    pa.tiles = pp.tiles;
+    pa.chunk = pp.chunk;
+    pa.plane_items = pp.plane_items;
+    pa.T = kGramT;
+    pa.n_gp = (int32_t)pp.gps.size();
+    const int64_t slots = (int64_t)dc.num_cu * gram_max_wg_per_cu(pp.planes);
+    pa.gram_grid = (int)std::max<int64_t>(1, std::min<int64_t>(pp.items, slots));
+    pa.plane_grid = (int)std::max<int64_t>(1, std::min<int64_t>((pp.plane_items + kWaves - 1) / kWaves, 8ll * dc.num_cu));
+    return pa;
+}
+
+// Releases a bit-plane buffer too large to keep, at the end of a call.
+struct PlanesKeep {
+    DevCtx &dc;
+    ~PlanesKeep() {
+        if (dc.planes.bytes > kPlanesKeep) dc.planes.release();
+    }
+};
 
 // ---------------------------------------------------------------------------
 // bns_ci_pairs: every pairwise marginal test of a dataset through the pair
@@ -746,17 +826,25 @@ extern "C" bns_status bns_ci_pairs(const bns_dataset *ds, double alpha, const bn
     if (!dg.ok) return fail(BNS_E_DEVICE, "cannot select device %d", ds->device);
     std::lock_guard<std::mutex> lk(dc->mu);
     hipStream_t s = o.stream ? (hipStream_t)o.stream : dc->stream;
-    PairPlan pp;
-    st = plan_pairs(*dc, &ds, 1, pp);
-    if (st != BNS_OK) return st;
+    PlanesKeep keep{*dc};
     const int64_t n = ds->n, npairs = n * (n - 1) / 2;
-    auto al8 = [](size_t x) { return (x + 7) & ~(size_t)7; };
-    const size_t o_ohvar = al8(sizeof(GramProb));
-    const size_t o_ohcat = al8(o_ohvar + sizeof(int32_t) * pp.oh_var.size());
-    const size_t o_varoh = al8(o_ohcat + sizeof(uint16_t) * pp.oh_cat.size());
-    const size_t setup_bytes = al8(o_varoh + sizeof(int32_t) * pp.var_oh.size());
     const size_t out_bytes = (size_t)npairs * (8 + 8 + 8 + 4) + 32;
-    st = check_workspace(o, (double)(setup_bytes + out_bytes + pp.part_bytes + pp.gram_bytes), "bns_ci_pairs");
+    auto al8 = [](size_t x) { return (x + 7) & ~(size_t)7; };
+    PairPlan pp;
+    size_t o_ohvar = 0, o_ohcat = 0, o_varoh = 0, setup_bytes = 0;
+    // bit planes, or the byte form when they do not fit the caller's limit or the device
+    for (bool planes : {true, false}) {
+        st = plan_pairs(*dc, &ds, 1, planes, pp);
+        if (st != BNS_OK) return st;
+        o_ohvar = al8(sizeof(GramProb));
+        o_ohcat = al8(o_ohvar + sizeof(int32_t) * pp.oh_var.size());
+        o_varoh = al8(o_ohcat + sizeof(uint16_t) * pp.oh_cat.size());
+        setup_bytes = al8(o_varoh + sizeof(int32_t) * pp.var_oh.size());
+        st = check_workspace(o, (double)(setup_bytes + out_bytes + pp.part_bytes + pp.gram_bytes + pp.plane_bytes),
+                             "bns_ci_pairs");
+        if (st == BNS_OK && pp.planes && !dc->planes.try_ensure((size_t)pp.plane_bytes)) st = BNS_E_NOMEM;
+        if (st == BNS_OK || !pp.planes) break;
+    }
     if (st != BNS_OK) return st;
     std::vector<char> h(setup_bytes, 0);
     std::memcpy(h.data(), pp.gps.data(), sizeof(GramProb));
@@ -767,21 +855,7 @@ extern "C" bns_status bns_ci_pairs(const bns_dataset *ds, double alpha, const bn
     HIP_TRY(dc->pair_part.ensure((size_t)(pp.part_bytes + pp.gram_bytes)));
     HIP_TRY(dc->pairs_out.ensure(out_bytes));
     HIP_TRY(hipMemcpyAsync(dc->pairs_setup.p, h.data(), setup_bytes, hipMemcpyHostToDevice, s));
-    char *sb = dc->pairs_setup.as<char>();
-    PairArgs pa;
-    std::memset(&pa, 0, sizeof(pa));
-    pa.gp = (const GramProb *)sb;
-    pa.oh_var = (const int32_t *)(sb + o_ohvar);
-    pa.oh_cat = (const uint16_t *)(sb + o_ohcat);
-    pa.var_oh = (const int32_t *)(sb + o_varoh);
-    pa.part = dc->pair_part.as<int32_t>();
-    pa.gram = pp.gram_bytes ? pa.part + pp.part_bytes / 4 : pa.part;
-    pa.items = pp.items;
-    pa.tiles = pp.tiles;
-    pa.chunk = pp.chunk;
-    pa.T = pp.T;
-    pa.n_gp = 1;
-    pa.gram_grid = (int)std::min<int64_t>(pp.items, (int64_t)dc->num_cu * gram_max_wg_per_cu(pp.T));
+    const PairArgs pa = pair_args(*dc, pp, dc->pairs_setup.as<char>(), 0, o_ohvar, o_ohcat, o_varoh);
     char *ob = dc->pairs_out.as<char>();
     double *d_stat = (double *)ob;
     double *d_p = d_stat + npairs;
@@ -1057,16 +1131,13 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     const bool verify = o.report_errors != 0 && o.precision == BNS_PREC_FP32_RECHECK;
     // Depth 0 through the pair contraction (verification mode keeps the test
     // kernel, whose FP32 statistic it compares with FP64).
-    PairPlan pp;
-    if (!verify && o.depth0 == BNS_DEPTH0_PAIRS) {
-        st = plan_pairs(dc, ds, P, pp);
-        if (st != BNS_OK) return st;
-    } else if (!verify && o.depth0 == BNS_DEPTH0_AUTO) {
-        // the contraction's fixed cost (three launches, latency-bound
-        // steps) pays once the depth's counting work is large
+    bool want_pairs = !verify && o.depth0 == BNS_DEPTH0_PAIRS;
+    if (!verify && o.depth0 == BNS_DEPTH0_AUTO) {
+        // the contraction's fixed cost (its launches, latency-bound steps)
+        // pays once the depth's counting work is large
         double work = 0.0;
         for (int32_t k = 0; k < P; ++k) work += 0.5 * (double)ds[k]->n * (ds[k]->n - 1) * (double)ds[k]->m;
-        if (work >= kPairsAutoWork && plan_pairs(dc, ds, P, pp) != BNS_OK) pp = PairPlan();
+        want_pairs = work >= kPairsAutoWork;
     }
     // Depth 1 through the masked Gram contractions (batched form; verification
     // mode keeps the test kernel, as at depth 0).
@@ -1106,13 +1177,21 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
                                           (double)tri_cap * kTriCats * 64 * 64 * 4
                                     : 0.0;
     const size_t o_gp = al8(o_cards + (size_t)G);
-    const size_t o_ohvar = al8(o_gp + sizeof(GramProb) * pp.gps.size());
-    const size_t o_ohcat = al8(o_ohvar + sizeof(int32_t) * pp.oh_var.size());
-    const size_t o_varoh = al8(o_ohcat + sizeof(uint16_t) * pp.oh_cat.size());
-    const size_t setup_bytes = al8(o_varoh + sizeof(int32_t) * pp.var_oh.size());
+    size_t o_ohvar = 0, o_ohcat = 0, o_varoh = 0, setup_bytes = 0;
     const int64_t err_cap = verify ? kErrLogEntries : 0;
     const size_t rbytes = ((size_t)adj_total + 7) & ~(size_t)7;  // removal depths, padded for 8-byte copies
-    {
+    PairPlan pp;
+    PlanesKeep keep{dc};
+    // bit planes, or the byte form when they do not fit the caller's limit or the device
+    for (bool planes : {true, false}) {
+        if (want_pairs) {
+            st = plan_pairs(dc, ds, P, planes, pp);
+            if (st != BNS_OK && o.depth0 == BNS_DEPTH0_PAIRS) return st;
+        }
+        o_ohvar = al8(o_gp + sizeof(GramProb) * pp.gps.size());
+        o_ohcat = al8(o_ohvar + sizeof(int32_t) * pp.oh_var.size());
+        o_varoh = al8(o_ohcat + sizeof(uint16_t) * pp.oh_cat.size());
+        setup_bytes = al8(o_varoh + sizeof(int32_t) * pp.var_oh.size());
         // every workspace buffer of the search (removal records: the first
         // launch's share; later growth is checked when it happens)
         const double bits = 8.0 * (double)std::min<int64_t>(std::max<int64_t>(bit_total, 1), kSmallBitWords);
@@ -1120,10 +1199,12 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
                             16.0 * G + (2.0 * sizeof(EdgeRec) + 8.0) * (double)pairs_total + sizeof(Ctl) +
                             4.0 * (double)kSplitWords + 4.0 * (double)kSplitTickets +
                             4.0 * 1024 + (per_prob ? sizeof(PStatDev) * (double)P * kMaxDepths + 8.0 * pairs_total : 0.0) +
-                            8.0 * (double)err_cap + (double)(pp.part_bytes + pp.gram_bytes) + tri_bytes;
+                            8.0 * (double)err_cap + (double)(pp.part_bytes + pp.gram_bytes + pp.plane_bytes) + tri_bytes;
         st = check_workspace(o, need, "the skeleton search");
-        if (st != BNS_OK) return st;
+        if (st == BNS_OK && pp.planes && !dc.planes.try_ensure((size_t)pp.plane_bytes)) st = BNS_E_NOMEM;
+        if (st == BNS_OK || !pp.planes) break;
     }
+    if (st != BNS_OK) return st;
     HIP_TRY(dc.setup.ensure(setup_bytes));
     HIP_TRY(dc.pinned(setup_bytes));
     {
@@ -1245,19 +1326,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     const bool runs = o.ticket_runs == 2 || (o.ticket_runs == 0 && col_bytes > kGrabRunBytes);
     a.grab_block_log2 = runs ? kGrabRunLog2 : 0;
     if (pp.on) {
-        char *sb = dc.setup.as<char>();
-        a.pairs.gp = (const GramProb *)(sb + o_gp);
-        a.pairs.oh_var = (const int32_t *)(sb + o_ohvar);
-        a.pairs.oh_cat = (const uint16_t *)(sb + o_ohcat);
-        a.pairs.var_oh = (const int32_t *)(sb + o_varoh);
-        a.pairs.part = dc.pair_part.as<int32_t>();
-        a.pairs.gram = pp.gram_bytes ? a.pairs.part + pp.part_bytes / 4 : a.pairs.part;
-        a.pairs.items = pp.items;
-        a.pairs.tiles = pp.tiles;
-        a.pairs.chunk = pp.chunk;
-        a.pairs.T = pp.T;
-        a.pairs.n_gp = P;
-        a.pairs.gram_grid = (int)std::min<int64_t>(pp.items, (int64_t)dc.num_cu * gram_max_wg_per_cu(pp.T));
+        a.pairs = pair_args(dc, pp, dc.setup.as<char>(), o_gp, o_ohvar, o_ohcat, o_varoh);
     }
     if (tri_on) {
         a.tri.node = dc.tri_node.as<TriNode>();

@@ -15,33 +15,50 @@ namespace bns {
 // The Gram matrix of each problem is computed in T x T tiles (upper triangle
 // of tile blocks) over chunks of samples; each (tile, chunk) work item writes
 // its partial tile, and the pair kernel sums a pair's block over the chunks.
+//
+// Two forms of A.  Bit planes (PairArgs.planes): one bit per sample for every
+// category but a variable's last, made from the columns by k_planes before
+// the contraction; the last row and column of a table follow from the
+// category counts (the diagonal) and m.  Bytes: every category, expanded from
+// the columns inside the contraction; for problems whose planes would take
+// more memory than their columns (mean cardinality above 9).
 struct GramProb {
     const uint8_t *data;   // column v at data + v * ld
     int64_t ld;
     int64_t m;
-    int32_t R;             // one-hot columns, padded to a multiple of T
-    int32_t nb;            // tile blocks per side (R / T)
-    int32_t oh_base;       // first entry of the problem in oh_var / oh_cat
+    int32_t R;             // rows of A^T A: planes, or one-hot columns padded to a multiple of T
+    int32_t nb;            // tile blocks per side
+    int32_t oh_base;       // bytes: first entry of the problem in oh_var / oh_cat
     int32_t nchunks;       // sample chunks of the problem
     int64_t item_base;     // first work item of the problem
     int64_t tile_base;     // first tile of the problem in the summed tiles
+    int64_t plane_off;     // planes: word offset of the problem's first plane
+    int64_t plane_stride;  // planes: words per plane (a multiple of 32; bits past m are 0)
+    int64_t plane_item;    // planes: first work item of the problem in k_planes
+    int32_t n;             // variables
+    int32_t var_off;       // first global variable
 };
 
 struct PairArgs {
     const GramProb *gp;    // per problem
+    uint32_t *planes;      // bit planes of every problem (null: the byte form)
     const int32_t *oh_var; // one-hot column -> variable of the problem (-1: padding column)
     const uint16_t *oh_cat; // category of the column (low byte); bit 8: the variable has more than 8 categories
-    const int32_t *var_oh; // global variable -> its first one-hot column within its problem
+    const int32_t *var_oh; // global variable -> its first row of A^T A within its problem
     int32_t *part;         // partial tiles, T * T int32 per work item (null: depth 0 uses the test kernel)
     int32_t *gram;         // tiles summed over the chunks, T * T int32 per tile (= part when no problem has two chunks)
     int64_t items;         // work items over all problems
     int64_t tiles;         // tiles over all problems
-    int64_t chunk;         // samples per chunk (a multiple of 64)
-    int32_t T;             // tile side: 64 or 128
+    int64_t chunk;         // samples per chunk (bytes: a multiple of 64; planes: of kPlaneBlock)
+    int64_t plane_items;   // work items of k_planes
+    int32_t T;             // tile side: kGramT
     int32_t n_gp;
     int32_t gram_grid;     // workgroups of the tile kernel
-    int32_t pad;
+    int32_t plane_grid;    // workgroups of k_planes
 };
+constexpr int kGramT = 64;
+constexpr int kPlaneBlock = 1024;  // samples per block of a plane (128 bytes): planes are padded to whole blocks
+constexpr int kPlaneItem = 2;      // 64-word pieces of one variable's planes per k_planes work item
 
 // Depth 1 as masked Gram contractions.  Every depth-1 test of an edge (x, y)
 // conditions on one z from the frozen neighbours of one endpoint, the owner u
@@ -191,7 +208,7 @@ hipError_t launch_depth0_pairs(const DepthArgs &a, hipStream_t s);
 hipError_t launch_ci_pairs(const PairArgs &p, const uint8_t *cards, int32_t n, double alpha, int stat,
                            int df_rule, double *stat_out, int64_t *df_out, double *p_out, int32_t *flags_out,
                            hipStream_t s);
-int gram_max_wg_per_cu(int T);
+int gram_max_wg_per_cu(bool planes);
 // Depth 1 through the masked contractions: plan, tiles, chunk sums and one
 // decision per test (the depth's test kernel then returns at once).  Runs
 // only when the control block's depth is 1; falls back to the test kernel

@@ -7,12 +7,17 @@
 // each category, which are the marginals N_x+ and N_+y of every pair table.
 // The products of 0/1 bytes summed in int32 are exact (m < 2^31).
 //
-// k_gram: one work item is a T x T tile of the upper triangle of tile blocks
-// of one problem's Gram matrix over one chunk of samples; a workgroup (2 x 2
-// waves, each a (T/2) x (T/2) block of 32 x 32 MFMA tiles) expands the tile's
-// one-hot columns for 64 samples at a time into LDS (double-buffered: the
-// global loads of the next step are in flight during the MFMAs of this one)
-// and writes its partial tile.
+// The contraction's work items are T x T tiles of the upper triangle of tile
+// blocks of one problem's Gram matrix over one chunk of samples; each writes
+// its partial tile.
+// k_planes, k_gram_planes: the columns become bit planes (one bit per sample
+// for each category but the last), and the contraction forms its int8
+// operands from plane words in registers, with no LDS in its loop.
+// k_gram: the byte form, for problems of mostly wide variables; a workgroup
+// (2 x 2 waves, each a (T/2) x (T/2) block of 32 x 32 MFMA tiles) expands the
+// tile's one-hot columns for 64 samples at a time into LDS (double-buffered:
+// the global loads of the next step are in flight during the MFMAs of this
+// one).
 // k_gram_reduce: sums each tile's partials over its problem's chunks.
 // k_depth0_pairs: one lane per edge of the depth reads the pair's block of the
 // summed tiles, forms the statistic in FP64, its own chi-square tail and the
@@ -29,8 +34,234 @@ constexpr int kGramKS = 64;             // samples per pipeline step
 constexpr int kGramRow = kGramKS + 16;  // LDS bytes per one-hot column and step
 constexpr int kGramQS = kGramKS / 16;   // 16-sample groups per column and step
 
-// c: the search's control block (its done flag, the depth's start stamp), or
-// null for the all-pairs entry point.
+// Start of the depth-0 span and its launch shape (c: the search's control
+// block, or null for the all-pairs entry point); true when the search is done.
+BNS_INLINE bool gram_enter(const PairArgs &P, Ctl *c, int *quit) {
+    if (threadIdx.x == 0) {
+        *quit = c ? c->done : 0;
+        if (c && blockIdx.x == 0) {
+            // (with planes the span starts in k_planes)
+            if (!P.planes) c->stats[0].t_start = wall_clock64();
+            c->stats[0].mode = 2;  // depth 0 as the pair contraction
+            c->stats[0].chunks = 0;
+            c->stats[0].chunk_len = P.chunk;
+        }
+    }
+    __syncthreads();
+    return *quit != 0;
+}
+
+// Work item -> problem, tile (tr <= tc), chunk of samples.
+struct GramItem {
+    GramProb gp;
+    int tr, tc;
+    int64_t s0, s1;
+};
+BNS_INLINE GramItem gram_item(const PairArgs &P, int64_t item) {
+    int lo = 0, hi = P.n_gp - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (P.gp[mid].item_base <= item) lo = mid;
+        else hi = mid - 1;
+    }
+    GramItem it;
+    it.gp = P.gp[lo];
+    const int64_t rel = item - it.gp.item_base;
+    const int64_t t = rel / it.gp.nchunks;
+    const int kc = (int)(rel - t * it.gp.nchunks);
+    it.tr = 0;
+    int64_t rem = t;
+    while (rem >= it.gp.nb - it.tr) {
+        rem -= it.gp.nb - it.tr;
+        ++it.tr;
+    }
+    it.tc = it.tr + (int)rem;
+    it.s0 = (int64_t)kc * P.chunk;
+    it.s1 = min(it.gp.m, it.s0 + P.chunk);
+    return it;
+}
+
+// ---------------------------------------------------------------------------
+// Bit planes.  A lane takes 32 samples of one variable (two 16-byte loads)
+// and forms their word of each plane: first one word per bit of the value,
+// bit k of dword j's four bytes going to bits j, 8 + j, 16 + j, 24 + j (one
+// shift and one and-or per dword and bit), then category c's word as the
+// conjunction of the value bits of c or their complements.  The samples are
+// permuted within a word, the same way in every plane, which no count can
+// see.  0.5 vector operations per sample and value bit (comparing bytes
+// across the wave took 3 per sample and category), so reading the columns
+// bounds it: 1,000 variables x 200,000 samples in 42 us, 250 MB at 5.9 TB/s
+// (89 us with the wave compares).  Bits of samples past m are 0.
+// ---------------------------------------------------------------------------
+template <int NB>
+BNS_INLINE void plane_words(const u32x4 (&x)[2], uint32_t valid, int r, uint32_t *out, int64_t stride) {
+    uint32_t bit[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        uint32_t wd = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t d = x[j >> 2][j & 3];
+            wd |= (j >= k ? d << (j - k) : d >> (k - j)) & (0x01010101u << j);
+        }
+        bit[k] = wd;
+    }
+    for (int cat = 0; cat < r - 1; ++cat) {
+        uint32_t wd = valid;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) wd &= ((cat >> k) & 1) ? bit[k] : ~bit[k];
+        out[(int64_t)cat * stride] = wd;
+    }
+}
+
+__global__ __launch_bounds__(kWG) void k_planes(PairArgs P, const uint8_t *cards, Ctl *c) {
+    if (c && blockIdx.x == 0 && threadIdx.x == 0) c->stats[0].t_start = wall_clock64();
+    const int lane = threadIdx.x & 63;
+    const int w = uni((int)(threadIdx.x >> 6));
+    for (int64_t item = (int64_t)blockIdx.x * kWaves + w; item < P.plane_items; item += (int64_t)gridDim.x * kWaves) {
+        int lo = 0, hi = P.n_gp - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (P.gp[mid].plane_item <= item) lo = mid;
+            else hi = mid - 1;
+        }
+        const GramProb &gp = P.gp[lo];
+        const int64_t m = uni(gp.m), stride = uni(gp.plane_stride);
+        const int64_t nq = (stride + kPlaneItem * 64 - 1) / (kPlaneItem * 64);
+        const int64_t rel = item - uni(gp.plane_item);
+        const int v = (int)(rel / nq);
+        const int64_t w0 = (rel - (int64_t)v * nq) * (kPlaneItem * 64) + lane;  // this lane's first word
+        const int g = uni(gp.var_off) + v;
+        const int r = uni((int)cards[g]);
+        if (r < 2) continue;
+        const uint8_t *col = gp.data + (int64_t)v * uni(gp.ld);
+        u32x4 x[kPlaneItem][2];
+#pragma unroll
+        for (int u = 0; u < kPlaneItem; ++u) {
+            const int64_t s = 32 * (w0 + 64 * u);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                x[u][q] = u32x4{0u, 0u, 0u, 0u};
+                if (s + 16 * q < m) x[u][q] = *(const gvec4 *)(col + s + 16 * q);
+            }
+        }
+        uint32_t *out = P.planes + uni(gp.plane_off) + (int64_t)uni(P.var_oh[g]) * stride;
+#pragma unroll
+        for (int u = 0; u < kPlaneItem; ++u) {
+            const int64_t wi = w0 + 64 * u;
+            if (wi >= stride) continue;
+            uint32_t valid = ~0u;
+            const int64_t left = m - 32 * wi;
+            if (left < 32) {  // sample i of the word is bit 8 (i mod 4) + i / 4
+                valid = 0u;
+                for (int i = 0; i < (int)left; ++i) valid |= 1u << (8 * (i & 3) + (i >> 2));
+            }
+            if (r <= 2) plane_words<1>(x[u], valid, r, out + wi, stride);
+            else if (r <= 4) plane_words<2>(x[u], valid, r, out + wi, stride);
+            else if (r <= 8) plane_words<3>(x[u], valid, r, out + wi, stride);
+            else plane_words<8>(x[u], valid, r, out + wi, stride);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Gram tiles from bit planes.  The four waves of a workgroup compute the same
+// 64 x 64 tile over interleaved 256-sample steps of the chunk (the waves'
+// 32-byte pieces of a plane share its 128-byte lines) and add their tiles in
+// LDS.  A lane of an operand holds one plane's 32-bit word: bytes k, k + 8,
+// k + 16, k + 24 of the samples come from one shift and one mask, (w >> k) &
+// 0x01010101, so 32 samples cost 15 vector operations and feed two MFMA steps
+// (the sample order inside a step does not matter as long as both operands
+// use the same).  Per step and wave 240 vector operations meet 32 MFMAs of 32
+// cycles: about balanced, against forming one-hot bytes from the columns in
+// LDS (k_gram), which is bound by that forming and reads 8 times the bytes.
+// 1,000 variables x 200,000 samples (2,000 planes): 305 us, 2.6e15 int8
+// operations/s over the upper triangle; k_gram's 3,000 one-hot columns took
+// 2,050 us, the planes included 347.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kGramWG) void k_gram_planes(PairArgs P, Ctl *c) {
+    constexpr int T = kGramT;
+    __shared__ int32_t red[T * T];
+    __shared__ int quit;
+    if (gram_enter(P, c, &quit)) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = uni(tid >> 6);
+    const int h = lane >> 5;
+    for (int64_t item = blockIdx.x; item < P.items; item += gridDim.x) {
+        const GramItem it = gram_item(P, item);
+        const GramProb &gp = it.gp;
+        const uint32_t *base = P.planes + gp.plane_off;
+        // rows past the last plane read the last one; their entries are not used
+        const uint32_t *row[4];
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            const int rr = min((f < 2 ? it.tr : it.tc) * T + 32 * (f & 1) + (lane & 31), gp.R - 1);
+            row[f] = base + (int64_t)rr * gp.plane_stride + 4 * h;
+        }
+        for (int i = tid; i < T * T; i += kGramWG) red[i] = 0;
+        v16i acc[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+        // 256-sample steps of the chunk (whole blocks: the planes are padded)
+        const int64_t st0 = it.s0 >> 8;
+        const int64_t st1 = (it.s1 + kPlaneBlock - 1) / kPlaneBlock * (kPlaneBlock >> 8);
+        u32x4 nx[4];
+        int64_t st = st0 + w;
+        if (st < st1) {
+#pragma unroll
+            for (int f = 0; f < 4; ++f) nx[f] = *(const gvec4 *)(row[f] + 8 * st);
+        }
+        while (st < st1) {
+            u32x4 x[4];
+#pragma unroll
+            for (int f = 0; f < 4; ++f) x[f] = nx[f];
+            const int64_t sn = st + kWaves;
+            if (sn < st1) {
+#pragma unroll
+                for (int f = 0; f < 4; ++f) nx[f] = *(const gvec4 *)(row[f] + 8 * sn);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) {
+                    v4i o[4];
+#pragma unroll
+                    for (int f = 0; f < 4; ++f)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[f][e] = (int)((x[f][q] >> (4 * kk + e)) & 0x01010101u);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(o[i], o[2 + j], acc[i][j], 0, 0, 0);
+                }
+            }
+            st = sn;
+        }
+        __syncthreads();  // red is clear
+        // register r of lane l holds row (r % 4) + 4 (l / 32) + 8 (r / 4),
+        // column l % 32 of a 32 x 32 tile
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int rr = 32 * i + (r & 3) + 4 * h + 8 * (r >> 2);
+                    const int cc = 32 * j + (lane & 31);
+                    atomicAdd(&red[rr * T + cc], acc[i][j][r]);
+                }
+        __syncthreads();
+        int4 *out = (int4 *)(P.part + item * (int64_t)(T * T));
+        for (int i = tid; i < T * T / 4; i += kGramWG) out[i] = ((const int4 *)red)[i];
+        __syncthreads();  // red is cleared for the next item
+    }
+}
+
 template <int T>
 __global__ __launch_bounds__(kGramWG) void k_gram(PairArgs P, Ctl *c) {
     constexpr int WT = T / 2;              // rows (and columns) of a wave's block
@@ -40,42 +271,16 @@ __global__ __launch_bounds__(kGramWG) void k_gram(PairArgs P, Ctl *c) {
     static_assert(kPer * kGramWG == kTasks, "tasks split evenly");
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][2 * T * kGramRow];  // [buffer][operand][column][sample]
     __shared__ int quit;
-    if (threadIdx.x == 0) {
-        quit = c ? c->done : 0;
-        if (c && blockIdx.x == 0) {
-            c->stats[0].t_start = wall_clock64();
-            c->stats[0].mode = 2;  // depth 0 as the pair contraction
-            c->stats[0].chunks = 0;
-            c->stats[0].chunk_len = P.chunk;
-        }
-    }
-    __syncthreads();
-    if (quit) return;
+    if (gram_enter(P, c, &quit)) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = w >> 1, wc = w & 1;
     for (int64_t item = blockIdx.x; item < P.items; item += gridDim.x) {
-        // work item -> problem, tile (tr <= tc), chunk of samples
-        int lo = 0, hi = P.n_gp - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (P.gp[mid].item_base <= item) lo = mid;
-            else hi = mid - 1;
-        }
-        const GramProb gp = P.gp[lo];
-        const int64_t rel = item - gp.item_base;
-        const int64_t t = rel / gp.nchunks;
-        const int kc = (int)(rel - t * gp.nchunks);
-        int tr = 0;
-        int64_t rem = t;
-        while (rem >= gp.nb - tr) {
-            rem -= gp.nb - tr;
-            ++tr;
-        }
-        const int tc = tr + (int)rem;
+        const GramItem it = gram_item(P, item);
+        const GramProb &gp = it.gp;
+        const int tr = it.tr, tc = it.tc;
+        const int64_t s0 = it.s0, s1 = it.s1;
         const bool diag = tr == tc;  // the second operand is the first
-        const int64_t s0 = (int64_t)kc * P.chunk;
-        const int64_t s1 = min(gp.m, s0 + P.chunk);
         const int nsteps = (int)((s1 - s0 + kGramKS - 1) / kGramKS);
         // this thread's expansion tasks for every step of the item
         const uint8_t *colp[kPer];
@@ -208,27 +413,129 @@ BNS_INLINE uint32_t gram_entry(const PairArgs &P, const GramProb &gp, int a, int
     return (uint32_t)P.gram[(gp.tile_base + ti) * (int64_t)T * T + (int64_t)(a - ta * T) * T + (b - tb * T)];
 }
 
-// Statistic (G^2 or X^2, FP64) and df of the pair of variables whose one-hot
-// columns start at oi and oj (oi < oj) with ri and rj categories, over m
-// samples: the table is the pair's block of the Gram matrix, the marginals
-// N_x+ and N_+y its diagonal entries (the category counts), N_++ = m.
-BNS_INLINE void pair_stat(const PairArgs &P, const GramProb &gp, int oi, int oj, int ri, int rj, int64_t m,
-                          int stat_kind, bool adj, double &stat, int64_t &df) {
+// Statistic (G^2 or X^2, FP64) and df of a pair with ri and rj categories
+// over m samples from its cells and category counts (the marginals N_x+ and
+// N_+y; N_++ = m).
+template <typename CellF, typename RowF, typename ColF>
+BNS_INLINE void pair_terms(int ri, int rj, int64_t m, int stat_kind, bool adj, double &stat, int64_t &df, CellF cell,
+                           RowF cnt_i, ColF cnt_j) {
     int na = 0, nb = 0;
     stat = 0.0;
-    for (int y = 0; y < rj; ++y) nb += gram_entry(P, gp, oj + y, oj + y) > 0u ? 1 : 0;
+    for (int y = 0; y < rj; ++y) nb += cnt_j(y) > 0u ? 1 : 0;
     for (int x = 0; x < ri; ++x) {
-        const uint32_t nx = gram_entry(P, gp, oi + x, oi + x);  // N_x+
+        const uint32_t nx = cnt_i(x);  // N_x+
         na += nx > 0u ? 1 : 0;
         for (int y = 0; y < rj; ++y) {
-            const uint32_t ny = gram_entry(P, gp, oj + y, oj + y);  // N_+y
-            const uint32_t N = gram_entry(P, gp, oi + x, oj + y);
+            const uint32_t ny = cnt_j(y);  // N_+y
+            const uint32_t N = cell(x, y);
             if (stat_kind) stat += x2_term<double>(N, nx, ny, (uint32_t)m);
             else stat += g2_half_term<double>(N, nx, ny, (uint32_t)m);
         }
     }
     if (!stat_kind) stat *= 2.0;
     df = adj ? (int64_t)(na - 1) * (int64_t)(nb - 1) : (int64_t)(ri - 1) * (int64_t)(rj - 1);
+}
+
+// The same for the pair of variables whose rows of the Gram matrix start at
+// oi and oj (oi < oj).  The diagonal entries are the category counts.  With
+// planes only the cells of neither variable's last category are entries; the
+// last column is what the other columns leave of N_x+, the last row what the
+// other rows leave of N_+y.  Up to kRegCats categories (the usual networks)
+// the table is completed in registers.
+constexpr int kRegCats = 5;
+
+BNS_INLINE void pair_stat(const PairArgs &P, const GramProb &gp, int oi, int oj, int ri, int rj, int64_t m,
+                          int stat_kind, bool adj, double &stat, int64_t &df) {
+    if (!P.planes) {
+        pair_terms(ri, rj, m, stat_kind, adj, stat, df, [&](int x, int y) { return gram_entry(P, gp, oi + x, oj + y); },
+                   [&](int x) { return gram_entry(P, gp, oi + x, oi + x); },
+                   [&](int y) { return gram_entry(P, gp, oj + y, oj + y); });
+        return;
+    }
+    const int pi = ri - 1, pj = rj - 1;
+    if (ri <= kRegCats && rj <= kRegCats) {
+        // every entry loaded once, all loads in flight together
+        uint32_t N[kRegCats][kRegCats], ni[kRegCats], nj[kRegCats];
+#pragma unroll
+        for (int x = 0; x < kRegCats; ++x)
+#pragma unroll
+            for (int y = 0; y < kRegCats; ++y)
+                N[x][y] = (x < pi && y < pj) ? gram_entry(P, gp, oi + x, oj + y) : 0u;
+#pragma unroll
+        for (int x = 0; x < kRegCats; ++x) ni[x] = x < pi ? gram_entry(P, gp, oi + x, oi + x) : 0u;
+#pragma unroll
+        for (int y = 0; y < kRegCats; ++y) nj[y] = y < pj ? gram_entry(P, gp, oj + y, oj + y) : 0u;
+        // counts of the last categories, then the last column and row
+        uint32_t li = (uint32_t)m, lj = (uint32_t)m;
+#pragma unroll
+        for (int x = 0; x < kRegCats; ++x) li -= ni[x];
+#pragma unroll
+        for (int y = 0; y < kRegCats; ++y) lj -= nj[y];
+#pragma unroll
+        for (int x = 0; x < kRegCats; ++x)
+            if (x == pi) ni[x] = li;
+#pragma unroll
+        for (int y = 0; y < kRegCats; ++y)
+            if (y == pj) nj[y] = lj;
+#pragma unroll
+        for (int x = 0; x < kRegCats; ++x) {
+            uint32_t rest = ni[x];
+#pragma unroll
+            for (int y = 0; y < kRegCats; ++y) rest -= N[x][y];
+#pragma unroll
+            for (int y = 0; y < kRegCats; ++y)
+                if (y == pj && x < pi) N[x][y] = rest;
+        }
+#pragma unroll
+        for (int y = 0; y < kRegCats; ++y) {
+            uint32_t rest = nj[y];
+#pragma unroll
+            for (int x = 0; x < kRegCats; ++x) rest -= x < pi ? N[x][y] : 0u;
+#pragma unroll
+            for (int x = 0; x < kRegCats; ++x)
+                if (x == pi && y <= pj) N[x][y] = rest;
+        }
+        int na = 0, nb = 0;
+        stat = 0.0;
+#pragma unroll
+        for (int y = 0; y < kRegCats; ++y) nb += y <= pj && nj[y] > 0u ? 1 : 0;
+#pragma unroll
+        for (int x = 0; x < kRegCats; ++x) {
+            if (x > pi) continue;
+            na += ni[x] > 0u ? 1 : 0;
+#pragma unroll
+            for (int y = 0; y < kRegCats; ++y) {
+                if (y > pj) continue;
+                if (stat_kind) stat += x2_term<double>(N[x][y], ni[x], nj[y], (uint32_t)m);
+                else stat += g2_half_term<double>(N[x][y], ni[x], nj[y], (uint32_t)m);
+            }
+        }
+        if (!stat_kind) stat *= 2.0;
+        df = adj ? (int64_t)(na - 1) * (int64_t)(nb - 1) : (int64_t)pi * (int64_t)pj;
+        return;
+    }
+    uint32_t li = (uint32_t)m, lj = (uint32_t)m;
+    for (int x = 0; x < pi; ++x) li -= gram_entry(P, gp, oi + x, oi + x);
+    for (int y = 0; y < pj; ++y) lj -= gram_entry(P, gp, oj + y, oj + y);
+    auto cnt_i = [&](int x) { return x < pi ? gram_entry(P, gp, oi + x, oi + x) : li; };
+    auto cnt_j = [&](int y) { return y < pj ? gram_entry(P, gp, oj + y, oj + y) : lj; };
+    uint32_t left_row = 0;  // what is left of row x
+    pair_terms(ri, rj, m, stat_kind, adj, stat, df,
+               [&](int x, int y) {
+                   if (y == 0) left_row = cnt_i(x);
+                   uint32_t N;
+                   if (y == pj) {
+                       N = left_row;  // (the last row's too: its other cells have been taken off)
+                   } else if (x < pi) {
+                       N = gram_entry(P, gp, oi + x, oj + y);
+                   } else {
+                       N = cnt_j(y);
+                       for (int a = 0; a < pi; ++a) N -= gram_entry(P, gp, oi + a, oj + y);
+                   }
+                   left_row -= N;
+                   return N;
+               },
+               cnt_i, cnt_j);
 }
 
 // The depth-0 tests of a skeleton search: one lane per edge of the depth.
@@ -295,20 +602,23 @@ __global__ __launch_bounds__(kWG) void k_ci_pairs(PairArgs P, const uint8_t *car
     }
 }
 
-static int gram_occupancy(int T) {
+int gram_max_wg_per_cu(bool planes) {
     int nb = 0;
-    const hipError_t e = T == 128 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_gram<128>, kGramWG, 0)
-                                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_gram<64>, kGramWG, 0);
+    const hipError_t e = planes ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_gram_planes, kGramWG, 0)
+                                : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_gram<kGramT>, kGramWG, 0);
     return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 
-int gram_max_wg_per_cu(int T) { return gram_occupancy(T); }
-
-// The Gram tiles of every problem (and their sum over chunks).
-static void launch_gram(const PairArgs &p, Ctl *c, hipStream_t s) {
+// The Gram tiles of every problem (and their sum over chunks); cards: per
+// global variable.
+static void launch_gram(const PairArgs &p, const uint8_t *cards, Ctl *c, hipStream_t s) {
     const dim3 grid(p.gram_grid);
-    if (p.T == 128) hipLaunchKernelGGL(k_gram<128>, grid, dim3(kGramWG), 0, s, p, c);
-    else hipLaunchKernelGGL(k_gram<64>, grid, dim3(kGramWG), 0, s, p, c);
+    if (p.planes) {
+        hipLaunchKernelGGL(k_planes, dim3(p.plane_grid), dim3(kWG), 0, s, p, cards, c);
+        hipLaunchKernelGGL(k_gram_planes, grid, dim3(kGramWG), 0, s, p, c);
+    } else {
+        hipLaunchKernelGGL(k_gram<kGramT>, grid, dim3(kGramWG), 0, s, p, c);
+    }
     if (p.gram != p.part) {
         const int64_t words = p.tiles * p.T * p.T / 4;
         const int rg = (int)std::max<int64_t>(1, std::min<int64_t>(4096, (words + kWG - 1) / kWG));
@@ -317,7 +627,7 @@ static void launch_gram(const PairArgs &p, Ctl *c, hipStream_t s) {
 }
 
 hipError_t launch_depth0_pairs(const DepthArgs &a, hipStream_t s) {
-    launch_gram(a.pairs, a.ctl, s);
+    launch_gram(a.pairs, a.cards, a.ctl, s);
     hipLaunchKernelGGL(k_depth0_pairs, dim3(a.edge_grid), dim3(kWG), 0, s, a);
     return hipGetLastError();
 }
@@ -325,7 +635,7 @@ hipError_t launch_depth0_pairs(const DepthArgs &a, hipStream_t s) {
 hipError_t launch_ci_pairs(const PairArgs &p, const uint8_t *cards, int32_t n, double alpha, int stat,
                            int df_rule, double *stat_out, int64_t *df_out, double *p_out, int32_t *flags_out,
                            hipStream_t s) {
-    launch_gram(p, nullptr, s);
+    launch_gram(p, cards, nullptr, s);
     const int64_t npairs = (int64_t)n * (n - 1) / 2;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(2048, (npairs + kWG - 1) / kWG));
     hipLaunchKernelGGL(k_ci_pairs, dim3(grid), dim3(kWG), 0, s, p, cards, n, alpha, stat, df_rule, stat_out,
