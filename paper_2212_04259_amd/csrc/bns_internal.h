@@ -108,8 +108,8 @@ struct Ctl {
     // pairs, the longest chunk count of a node and the samples per chunk.
     int32_t gram_depth;
     int32_t tri_nch_max;
-    int32_t xy;                        // test kernel units: 0 tests, 1 (edge, level) groups
-    int32_t pad1;
+    int32_t xy;                        // work units: 0 tests, 1 (edge, level) groups, 2 (edge, segment of its ranks)
+    int32_t unit_segs;                 // units per edge (xy 2)
     unsigned long long tri_items;
     unsigned long long tri_base;
     unsigned long long tri_tests;

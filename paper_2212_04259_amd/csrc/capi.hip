@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <fstream>
+#include <limits>
 #include <memory>
 #include <mutex>
 #include <sstream>
@@ -167,6 +168,13 @@ struct GraphEntry {
     }
 };
 
+// Statistics that enclose the decisions of one alpha: for df = 1 .. kCritDf - 1
+// a statistic below x has p > alpha + reach, one above y has p < alpha - reach.
+struct CritRow {
+    double alpha, reach;
+    std::vector<double2> v;
+};
+
 // Per-device state: properties, a library stream, and grow-only workspaces.
 struct DevCtx {
     int device = -1;
@@ -179,6 +187,8 @@ struct DevCtx {
     DevBuf pstat, ecnt;  // per-problem counters of multi-dataset searches
     DevBuf pair_part;    // partial Gram tiles of depth 0 through the pair contraction
     DevBuf planes;       // bit planes of the columns
+    DevBuf tables;       // every pairwise table, for depth 1 from bit planes
+    std::vector<CritRow> crit;  // critical values by alpha and band
     DevBuf tri_node, tri_rowoff, tri_eidx, tri_part;  // depth 1 through the masked contractions
     DevBuf pairs_setup, pairs_out;  // bns_ci_pairs: tile plan and results
     DevBuf err_val, err_tag, err_cnt;  // verification log
@@ -213,6 +223,7 @@ struct DevCtx {
     }
     std::vector<std::unique_ptr<GraphEntry>> graphs;  // captured depth launches
     int search_lds = 0;  // default dynamic LDS of the skeleton test kernel (bytes)
+    bool last_bits = false;  // the last search ran depths 0 and 1 from bit planes
     int last_sequences = 0;  // depth sequences the last finished search needed
     void *hres = nullptr;    // pinned staging for result downloads
     size_t hres_bytes = 0;
@@ -665,8 +676,14 @@ static const int64_t kPairPartMax = 1ll << 30;
 // MI355X, 8.9e7 (60 variables, 50,000 samples) is faster in the test kernel,
 // 2.4e9 (220 variables, 100,000 samples) and more through the contraction.
 static const double kPairsAutoWork = 5e8;
+// The same when depth 1 runs from bit planes too (which needs the planes and
+// pairwise tables): 9.5e5 (20 variables, 5,000 samples) is 5% slower, 8.9e7
+// (60 variables, 50,000 samples) 9% faster than in the test kernel.
+static const double kBitsAutoWork = 1e7;
 // Bit planes kept between calls; a larger buffer goes at the end of its call.
 static const size_t kPlanesKeep = 512ull << 20;
+// Pairwise tables held at most for depth 1 from bit planes (1 GiB).
+static const int64_t kBitTableWords = 256ll << 20;
 // Depth 1 through the masked contractions: work items held at most (64 KiB
 // each; beyond, the depth runs in the test kernel).
 static const int64_t kTriItemsMax = 16384;
@@ -800,13 +817,74 @@ static PairArgs pair_args(const DevCtx &dc, const PairPlan &pp, char *sb, size_t
     return pa;
 }
 
-// Releases a bit-plane buffer too large to keep, at the end of a call.
+// Releases bit planes and pairwise tables too large to keep, at the end of a call.
 struct PlanesKeep {
     DevCtx &dc;
     ~PlanesKeep() {
         if (dc.planes.bytes > kPlanesKeep) dc.planes.release();
+        if (dc.tables.bytes > kPlanesKeep) dc.tables.release();
     }
 };
+
+// Upper tail of the chi-square distribution with df degrees of freedom at 2 x
+// and the Gamma(df / 2, 1) density there (closed forms for integer df).
+static double chi2_upper(int df, double x, double *dens) {
+    const double pi = 3.141592653589793;
+    const bool odd = (df & 1) != 0;
+    const int n = df >> 1;
+    double term = odd ? 2.0 * std::sqrt(x / pi) : 1.0, sum = 0.0, last = 0.0;
+    for (int k = 0; k < n; ++k) {
+        sum += term;
+        last = term;
+        term *= x / ((double)(k + 1) + (odd ? 0.5 : 0.0));
+    }
+    const double ex = std::exp(-x);
+    *dens = n > 0 ? ex * last : ex / std::sqrt(pi * x);
+    return (odd ? std::erfc(std::sqrt(x)) : 0.0) + ex * sum;
+}
+
+// 2 x with upper tail q in (0, 1), to about 1e-12: Newton's method from the
+// Wilson-Hilferty approximation, kept inside a shrinking bracket.
+static double chi2_quantile(int df, double q) {
+    // normal quantile (Abramowitz and Stegun 26.2.23)
+    const double u = std::sqrt(-2.0 * std::log(q < 0.5 ? q : 1.0 - q));
+    double zn = u - (2.515517 + 0.802853 * u + 0.010328 * u * u) /
+                        (1.0 + 1.432788 * u + 0.189269 * u * u + 0.001308 * u * u * u);
+    if (q >= 0.5) zn = -zn;
+    const double h = 2.0 / (9.0 * df), c = 1.0 - h + zn * std::sqrt(h);
+    double x = std::max(0.5 * df * c * c * c, 1e-8 * df), lo = 0.0, hi = 700.0;
+    for (int it = 0; it < 100; ++it) {
+        double d;
+        const double f = chi2_upper(df, x, &d) - q;
+        if (f > 0) lo = x;
+        else hi = x;
+        double nx = x + f / d;
+        if (!(nx > lo && nx < hi)) nx = 0.5 * (lo + hi);
+        const bool done = std::fabs(nx - x) <= 1e-12 * x;
+        x = nx;
+        if (done) break;
+    }
+    return 2.0 * x;
+}
+
+// The row of (alpha, reach): decisions outside [x, y] are certain without a
+// tail.  reach covers the re-check band and, with 1e-3, four times the
+// propagated FP32 error bound (at most 1e-4 for df < kCritDf).
+static const std::vector<double2> &crit_row(DevCtx &dc, double alpha, double band) {
+    const double reach = std::max(band, 1e-3);
+    for (const CritRow &c : dc.crit)
+        if (c.alpha == alpha && c.reach == reach) return c.v;
+    if (dc.crit.size() >= 64) dc.crit.erase(dc.crit.begin());
+    CritRow r{alpha, reach, std::vector<double2>((size_t)kCritDf, make_double2(0.0, 0.0))};
+    const double inf = std::numeric_limits<double>::infinity();
+    for (int df = 1; df < kCritDf; ++df) {
+        // (a part in 10^6 to spare)
+        r.v[(size_t)df].x = alpha + reach < 1.0 ? chi2_quantile(df, alpha + reach) * (1.0 - 1e-6) : 0.0;
+        r.v[(size_t)df].y = alpha - reach > 1e-12 ? chi2_quantile(df, alpha - reach) * (1.0 + 1e-6) : inf;
+    }
+    dc.crit.push_back(std::move(r));
+    return dc.crit.back().v;
+}
 
 // ---------------------------------------------------------------------------
 // bns_ci_pairs: every pairwise marginal test of a dataset through the pair
@@ -1132,12 +1210,14 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     // Depth 0 through the pair contraction (verification mode keeps the test
     // kernel, whose FP32 statistic it compares with FP64).
     bool want_pairs = !verify && o.depth0 == BNS_DEPTH0_PAIRS;
+    bool bits_pay = true;
     if (!verify && o.depth0 == BNS_DEPTH0_AUTO) {
         // the contraction's fixed cost (its launches, latency-bound steps)
         // pays once the depth's counting work is large
         double work = 0.0;
         for (int32_t k = 0; k < P; ++k) work += 0.5 * (double)ds[k]->n * (ds[k]->n - 1) * (double)ds[k]->m;
         want_pairs = work >= kPairsAutoWork;
+        bits_pay = work >= kBitsAutoWork;
     }
     // Depth 1 through the masked Gram contractions (batched form; verification
     // mode keeps the test kernel, as at depth 0).
@@ -1180,28 +1260,70 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     size_t o_ohvar = 0, o_ohcat = 0, o_varoh = 0, setup_bytes = 0;
     const int64_t err_cap = verify ? kErrLogEntries : 0;
     const size_t rbytes = ((size_t)adj_total + 7) & ~(size_t)7;  // removal depths, padded for 8-byte copies
+    // Depth 1 from bit planes, after a depth 0 through the contraction: when
+    // every variable has at most kBitCards categories (a test's work grows
+    // with the product of its plane counts, and the kernel holds its counts in
+    // registers) and the caller leaves the paths and shapes of depths 0 and 1
+    // open.
+    bool bits_want = bits_pay && !verify && o.form == BNS_FORM_BATCHED && o.depth0 != BNS_DEPTH0_TESTS &&
+                     o.depth1 == BNS_DEPTH1_AUTO && o.group_tests == BNS_GROUP_AUTO && o.round_tests == 0 &&
+                     o.test_group == 0 && ((o.wave_depths | o.block_depths) & 3u) == 0u && (unbounded || dmax >= 1);
+    int64_t table_words = 0;
+    for (int32_t k = 0; k < P && bits_want; ++k) {
+        int64_t R = 0;
+        for (uint8_t cv : ds[k]->cards) {
+            R += cv;
+            if (cv > kBitCards) bits_want = false;
+        }
+        table_words += R * R;
+        // (the kernel addresses a problem's planes with 32-bit byte offsets)
+        const int64_t plane = (ds[k]->m + kPlaneBlock - 1) / kPlaneBlock * (kPlaneBlock / 8);
+        if (table_words > kBitTableWords || (R - ds[k]->n) * plane >= (1ll << 32) || ds[k]->m >= (1ll << 26))
+            bits_want = false;  // (products of two counts below 2^53)
+    }
+    // critical values per distinct alpha
+    std::vector<double> crit_alpha;
+    std::vector<int32_t> crit_of((size_t)P, 0);
+    for (int32_t k = 0; k < P && bits_want; ++k) {
+        size_t q = 0;
+        while (q < crit_alpha.size() && crit_alpha[q] != alpha[k]) ++q;
+        if (q == crit_alpha.size()) crit_alpha.push_back(alpha[k]);
+        crit_of[(size_t)k] = (int32_t)q;
+    }
     PairPlan pp;
     PlanesKeep keep{dc};
-    // bit planes, or the byte form when they do not fit the caller's limit or the device
-    for (bool planes : {true, false}) {
-        if (want_pairs) {
-            st = plan_pairs(dc, ds, P, planes, pp);
+    bool bits = false;
+    size_t o_vars = 0, o_bits = 0, o_crit = 0;
+    // bit planes for depths 0 and 1, for depth 0, or the byte form, as far as
+    // they fit the caller's limit and the device
+    for (int level = bits_want ? 0 : 1; level < 3; ++level) {
+        bits = level == 0;
+        pp = PairPlan();
+        if (bits || want_pairs) {
+            st = plan_pairs(dc, ds, P, level < 2, pp);
+            if (bits && (st != BNS_OK || !pp.planes)) continue;
             if (st != BNS_OK && o.depth0 == BNS_DEPTH0_PAIRS) return st;
         }
         o_ohvar = al8(o_gp + sizeof(GramProb) * pp.gps.size());
         o_ohcat = al8(o_ohvar + sizeof(int32_t) * pp.oh_var.size());
         o_varoh = al8(o_ohcat + sizeof(uint16_t) * pp.oh_cat.size());
-        setup_bytes = al8(o_varoh + sizeof(int32_t) * pp.var_oh.size());
+        o_vars = (o_varoh + sizeof(int32_t) * pp.var_oh.size() + 15) & ~(size_t)15;
+        o_bits = al8(o_vars + (bits ? sizeof(VarRec) * (size_t)G : 0));
+        o_crit = (o_bits + (bits ? sizeof(BitProb) * (size_t)P : 0) + 15) & ~(size_t)15;
+        setup_bytes = al8(o_crit + (bits ? sizeof(double2) * kCritDf * crit_alpha.size() : 0));
+        const double table_bytes = bits ? 4.0 * (double)table_words : 0.0;
         // every workspace buffer of the search (removal records: the first
         // launch's share; later growth is checked when it happens)
-        const double bits = 8.0 * (double)std::min<int64_t>(std::max<int64_t>(bit_total, 1), kSmallBitWords);
-        const double need = (double)setup_bytes + 9.0 * (double)adj_total + bits + (double)rbytes +
+        const double bitrows = 8.0 * (double)std::min<int64_t>(std::max<int64_t>(bit_total, 1), kSmallBitWords);
+        const double need = (double)setup_bytes + 9.0 * (double)adj_total + bitrows + (double)rbytes +
                             16.0 * G + (2.0 * sizeof(EdgeRec) + 8.0) * (double)pairs_total + sizeof(Ctl) +
                             4.0 * (double)kSplitWords + 4.0 * (double)kSplitTickets +
                             4.0 * 1024 + (per_prob ? sizeof(PStatDev) * (double)P * kMaxDepths + 8.0 * pairs_total : 0.0) +
-                            8.0 * (double)err_cap + (double)(pp.part_bytes + pp.gram_bytes + pp.plane_bytes) + tri_bytes;
+                            8.0 * (double)err_cap + (double)(pp.part_bytes + pp.gram_bytes + pp.plane_bytes) +
+                            table_bytes + tri_bytes;
         st = check_workspace(o, need, "the skeleton search");
         if (st == BNS_OK && pp.planes && !dc.planes.try_ensure((size_t)pp.plane_bytes)) st = BNS_E_NOMEM;
+        if (st == BNS_OK && bits && !dc.tables.try_ensure((size_t)table_bytes)) st = BNS_E_NOMEM;
         if (st == BNS_OK || !pp.planes) break;
     }
     if (st != BNS_OK) return st;
@@ -1218,6 +1340,25 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
             std::memcpy(h + o_ohvar, pp.oh_var.data(), sizeof(int32_t) * pp.oh_var.size());
             std::memcpy(h + o_ohcat, pp.oh_cat.data(), sizeof(uint16_t) * pp.oh_cat.size());
             std::memcpy(h + o_varoh, pp.var_oh.data(), sizeof(int32_t) * pp.var_oh.size());
+        }
+        if (bits) {
+            VarRec *vr = (VarRec *)(h + o_vars);
+            BitProb *bp = (BitProb *)(h + o_bits);
+            int64_t tab = 0;
+            for (int32_t k = 0; k < P; ++k) {
+                int32_t R = 0;
+                for (int32_t v = 0; v < ds[k]->n; ++v) {
+                    const int32_t g = probs[k].var_off + v;
+                    vr[g] = {ds[k]->cards[v], pp.var_oh[(size_t)g], R, 0};
+                    R += ds[k]->cards[v];
+                }
+                bp[k] = {dc.planes.as<uint32_t>() + pp.gps[k].plane_off, (uint32_t)(4 * pp.gps[k].plane_stride),
+                         (uint32_t)((ds[k]->m + 31) / 32), (uint32_t)(4 * pp.gps[k].R * pp.gps[k].plane_stride), R, crit_of[(size_t)k], dc.tables.as<int32_t>() + tab};
+                tab += (int64_t)R * R;
+            }
+            for (size_t q = 0; q < crit_alpha.size(); ++q)
+                std::memcpy(h + o_crit + q * sizeof(double2) * kCritDf,
+                            crit_row(dc, crit_alpha[q], tile.fp64 ? 0.0 : tile.band).data(), sizeof(double2) * kCritDf);
         }
     }
     if (!(dc.setup_last_dev == dc.setup.p && dc.setup_last.size() == setup_bytes &&
@@ -1327,6 +1468,18 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     a.grab_block_log2 = runs ? kGrabRunLog2 : 0;
     if (pp.on) {
         a.pairs = pair_args(dc, pp, dc.setup.as<char>(), o_gp, o_ohvar, o_ohcat, o_varoh);
+    }
+    dc.last_bits = bits;
+    if (bits) {
+        char *sb = dc.setup.as<char>();
+        a.bits.prob = (const BitProb *)(sb + o_bits);
+        a.bits.var = (const VarRec *)(sb + o_vars);
+        a.bits.crit = (const double2 *)(sb + o_crit);
+        a.bits.n_crit = (int32_t)crit_alpha.size();
+        a.bits.grid = std::max(1, dc.num_cu * bits_max_wg_per_cu());
+        a.bits.run_log2 = a.grab_block_log2;
+        a.bits_policy = 1;
+        a.xy_policy = 0;
     }
     if (tri_on) {
         a.tri.node = dc.tri_node.as<TriNode>();
@@ -1802,6 +1955,9 @@ static bool g_tune_loaded = false;
 
 // The tuned options that are kept (stream excluded), in file order.
 static const int kTuneFields = 12;
+// Part of the key: choices measured before a change of the paths that the
+// open options take (1: depths 0 and 1 from bit planes) are not used after it.
+static const int64_t kTunePaths = 1;
 static int32_t *tune_field(bns_options &o, int i) {
     int32_t *f[] = {&o.test_group, &o.max_replicas, &o.lds_bytes, &o.tickets_per_grab, &o.split_min_samples,
                     &o.units_per_group, &o.depth0, &o.round_tests, (int32_t *)&o.wave_depths,
@@ -1901,6 +2057,7 @@ extern "C" bns_status bns_autotune(const bns_dataset *const *ds, int32_t n_probl
     for (int i = 0; i < kTuneFields; ++i) key.push_back(*tune_field(o, i));
     key.push_back(o.statistic);
     key.push_back(o.df_rule);
+    key.push_back(kTunePaths);
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         if (!g_tune_loaded) tune_load_file();
@@ -1931,6 +2088,14 @@ extern "C" bns_status bns_autotune(const bns_dataset *const *ds, int32_t n_probl
     double cur_t = 0.0;
     st = timed(cur, &cur_t);
     if (st != BNS_OK) return st;
+    bool planes = false;  // depths 0 and 1 ran from bit planes
+    {
+        DevCtx *dc = nullptr;
+        st = get_ctx(ds[0]->device, &dc);
+        if (st != BNS_OK) return st;
+        std::lock_guard<std::mutex> lk(dc->mu);
+        planes = dc->last_bits;
+    }
     // Per depth: one wave or one workgroup per test, whichever ran that
     // depth's test kernel in less time (device-clock spans).  The skeleton,
     // and so each depth's edges and tests, is the same either way.
@@ -1968,7 +2133,8 @@ extern "C" bns_status bns_autotune(const bns_dataset *const *ds, int32_t n_probl
         if (s2 != BNS_OK) return s2;
         cm.test_group = 0;
         cm.wave_depths = cm.block_depths = 0u;
-        for (size_t d = 0; d < std::min(sw.size(), sb.size()) && d < 32; ++d)
+        // (depths that the open options run from bit planes have no such choice)
+        for (size_t d = planes ? 2 : 0; d < std::min(sw.size(), sb.size()) && d < 32; ++d)
             (sw[d] < sb[d] ? cm.wave_depths : cm.block_depths) |= 1u << d;
         if (std::memcmp(&cm, &cur, sizeof(cm)) == 0) return BNS_OK;
         double t = 0.0;

@@ -96,6 +96,42 @@ struct TriArgs {
     int32_t grid;         // workgroups of the contraction kernel
 };
 
+// Depth 1 from bit planes (bits.hip): the planes of the depth-0 contraction
+// and every pairwise table, which depth 0 leaves behind.
+constexpr int kBitCards = 5;   // largest cardinality: at most 4 planes per variable (a test's cost
+                               // grows with the product of its plane counts; see k_depth1_bits)
+constexpr int kBitUnit = 8;    // tests per pass at most
+constexpr int kBitSegs = 8;    // segments of an edge's ranks at most
+constexpr int kBitSegRanks = 16;  // ranks per segment aimed for
+constexpr int kCritDf = 128;   // critical values by df: df <= (kBitCards - 1)^2 kBitCards = 80
+
+struct VarRec {
+    int32_t card;
+    int32_t plane;   // first plane within the problem
+    int32_t cat;     // first category within the problem (row of the pairwise tables)
+    int32_t pad;
+};
+
+struct BitProb {
+    const uint32_t *planes;  // the problem's first plane
+    uint32_t plane_bytes;    // bytes per plane
+    uint32_t words;          // words of a plane that hold samples
+    uint32_t bytes;          // bytes of the problem's planes (below 4 GiB)
+    int32_t R;               // categories of all variables
+    int32_t crit_row;        // row of the critical values
+    int32_t *gram;           // pairwise tables: gram[(cat of x) R + cat of y] = N_xy; diagonal: category counts
+};
+
+struct BitArgs {
+    const BitProb *prob;   // per problem (null: depth 1 uses the test kernel)
+    const VarRec *var;     // per global variable
+    const double2 *crit;   // [row][df]: a statistic below .x accepts, above .y does not (between: by its p)
+    int32_t n_crit;        // rows: distinct alphas
+    int32_t grid;          // workgroups of the kernel
+    int32_t run_log2;      // units dealt to a grab counter in runs of 2^this
+    int32_t pad;
+};
+
 // Arguments of the per-depth pipeline of a skeleton search (all device pointers).
 struct DepthArgs {
     const ProbDev *probs;
@@ -158,7 +194,7 @@ struct DepthArgs {
     int32_t edge_form;        // 1: one group per edge runs its tests in order to the first accept
     int32_t xy_policy;        // depth 1: a work unit is one edge's ranks of a level, counted in one pass
                               // sharing the X and Y columns (0 never, 1 always)
-    int32_t pad2;
+    int32_t bits_policy;      // depth 1 from bit planes: a unit is a segment of an edge's ranks
     // Results of a launch, written into pinned host memory by its last kernel.
     Ctl *h_ctl;               // copy of the control block
     char *h_res;              // null, or removal depths (res_rbytes) then the first removal records
@@ -171,6 +207,7 @@ struct DepthArgs {
     unsigned long long *h_flag;   // pinned host
     PairArgs pairs;               // depth 0 as one contraction (pairs.part non-null)
     TriArgs tri;                  // depth 1 as masked contractions (tri.node non-null)
+    BitArgs bits;                 // depth 1 from bit planes (bits.prob non-null)
 };
 
 // Small searches keep the adjacency as bit rows in LDS and prepare each depth
@@ -184,17 +221,22 @@ hipError_t launch_depth_prepare(const DepthArgs &a, hipStream_t s);   // snapsho
 // units: the instance for the depth's work units: 0 one test, 1 (edge, level)
 // groups (depth 1 with a.xy_policy), 2 one test of at most kNarrowDepth + 2
 // columns (the instance without the wider counting loops, whose registers
-// otherwise spill); the host's choice for a depth must match depth_units().
+// otherwise spill), 3 units of the bit-plane kernel (launch_depth1_bits); the
+// host's choice for a depth must match depth_units().
 hipError_t launch_depth_tests(const DepthArgs &a, int grid, hipStream_t s,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr, int units = 0);
 constexpr int kNarrowDepth = 2;
 // Work units of depth d (the rule the depth preparation applies).
 inline int depth_units(const DepthArgs &a, int d) {
     if (a.edge_form || a.err_val) return 0;
+    if (a.bits_policy && d == 1) return 3;
     if (a.xy_policy == 1 && d == 1 && a.round_width == 0) return 1;
     if (d <= kNarrowDepth && a.tile.stat == 0 && a.tile.df_rule == 0) return 2;
     return 0;
 }
+// Depth 1 from bit planes, in place of the depth's test kernel (units 3).
+hipError_t launch_depth1_bits(const DepthArgs &a, hipStream_t s, hipEvent_t start, hipEvent_t stop);
+int bits_max_wg_per_cu();
 hipError_t launch_depth_apply(const DepthArgs &a, hipStream_t s);     // removals + finalize
 // LDS increment throughput: grid workgroups of kWG lanes, 16 * steps
 // increments per lane; sink receives the increments' total.

@@ -369,10 +369,21 @@ BNS_INLINE void levels_wave(const DepthArgs &A, Ctl *c, const unsigned int *hist
     if (g > 0) width = lane < 63 ? (unsigned long long)g
                                  : (maxn > 63ull * g ? maxn - 63ull * g : (unsigned long long)g);
     if (xy) width = 1ull;
+    // Depth 1 from bit planes: each edge is cut into segments of its ranks,
+    // at most kBitSegRanks long (a chain of passes ends the depth late) and
+    // enough of them to leave the grid's waves two units each
+    const bool bits = A.bits_policy && d == 1;
+    const unsigned long long n0 = bits ? __shfl(cnt, 0, 64) : 0ull;  // edges with a test
+    unsigned long long segs = 1ull;
+    if (bits)
+        segs = min((unsigned long long)kBitSegs,
+                   max(max(1ull, 2ull * kWaves * (unsigned)max(A.bits.grid, 1) / max(n0, 1ull)),
+                       (2ull * (unsigned)maxdeg + kBitSegRanks - 1) / kBitSegRanks));
+    if (bits) width = lane == 0 ? segs : 0ull;
     int bad = 0;
     unsigned long long tk = 0;
     if (cnt) {
-        if ((g <= 0 && lane >= 60) || cnt > (1ull << 61) / width) bad = 1;
+        if ((g <= 0 && lane >= 60) || cnt > (1ull << 61) / max(width, 1ull)) bad = 1;
         else tk = cnt * width;
     }
     unsigned long long pre = tk;  // inclusive prefix over lanes <= lane
@@ -402,6 +413,7 @@ BNS_INLINE void levels_wave(const DepthArgs &A, Ctl *c, const unsigned int *hist
         const uint32_t dbit = d < 32 ? 1u << d : 0u;
         const int mode = (A.block_depths & dbit) ? 1
                        : (A.wave_depths & dbit)  ? 0
+                       : bits                    ? 0
                        : xy                      ? 1  // (edge, level) units: a wave's LDS share holds few tables
                        : (A.mode_policy == 2)    ? 1
                        : (A.mode_policy == 1)    ? 0
@@ -415,7 +427,7 @@ BNS_INLINE void levels_wave(const DepthArgs &A, Ctl *c, const unsigned int *hist
         // With more tickets the merges cost more than the idle groups.
         unsigned long long C = 1, cap = 0;
         long long Lc = A.m_max;
-        if (!xy && A.split_min > 0 && total > 0 && total <= (unsigned long long)A.split_tickets) {
+        if (!xy && !bits && A.split_min > 0 && total > 0 && total <= (unsigned long long)A.split_tickets) {
             const unsigned long long want =
                 (unsigned long long)max(A.units_per_group, 1) * groups / total;
             const unsigned long long by_len = (unsigned long long)(A.m_max / A.split_min);
@@ -434,7 +446,8 @@ BNS_INLINE void levels_wave(const DepthArgs &A, Ctl *c, const unsigned int *hist
             cap = 0;
         }
         c->mode = mode;
-        c->xy = xy ? 1 : 0;
+        c->xy = bits ? 2 : xy ? 1 : 0;
+        c->unit_segs = (int32_t)segs;
         c->chunks = (int)C;
         c->chunk_len = Lc;
         c->split_cap = cap;
@@ -2112,6 +2125,7 @@ static auto depth_tests_kernel(const DepthArgs &a, int units) -> decltype(&k_dep
 
 hipError_t launch_depth_tests(const DepthArgs &a, int grid, hipStream_t s, hipEvent_t start,
                               hipEvent_t stop, int units) {
+    if (units == 3) return launch_depth1_bits(a, s, start, stop);
     auto kern = depth_tests_kernel(a, units);
     if (a.edge_form) kern = (a.tile.stat != 0 || a.tile.df_rule != 0) ? &k_depth_edges<true> : &k_depth_edges<false>;
     if (start && stop)

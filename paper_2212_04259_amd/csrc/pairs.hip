@@ -444,8 +444,13 @@ BNS_INLINE void pair_terms(int ri, int rj, int64_t m, int stat_kind, bool adj, d
 // the table is completed in registers.
 constexpr int kRegCats = 5;
 
+// keep (may be null): a problem's pairwise tables over all categories (R
+// columns), where the pair's table and its transpose are left at rows ci and
+// cj; cnt: the variables whose category counts it leaves on the diagonal
+// (1: i, 2: j).
 BNS_INLINE void pair_stat(const PairArgs &P, const GramProb &gp, int oi, int oj, int ri, int rj, int64_t m,
-                          int stat_kind, bool adj, double &stat, int64_t &df) {
+                          int stat_kind, bool adj, double &stat, int64_t &df, int32_t *keep = nullptr, int ci = 0,
+                          int cj = 0, int R = 0, int cnt = 0) {
     if (!P.planes) {
         pair_terms(ri, rj, m, stat_kind, adj, stat, df, [&](int x, int y) { return gram_entry(P, gp, oi + x, oj + y); },
                    [&](int x) { return gram_entry(P, gp, oi + x, oi + x); },
@@ -494,6 +499,21 @@ BNS_INLINE void pair_stat(const PairArgs &P, const GramProb &gp, int oi, int oj,
 #pragma unroll
             for (int x = 0; x < kRegCats; ++x)
                 if (x == pi && y <= pj) N[x][y] = rest;
+        }
+        if (keep) {
+#pragma unroll
+            for (int x = 0; x < kRegCats; ++x)
+#pragma unroll
+                for (int y = 0; y < kRegCats; ++y)
+                    if (x <= pi && y <= pj) {
+                        keep[(uint32_t)(ci + x) * (uint32_t)R + (uint32_t)(cj + y)] = (int32_t)N[x][y];
+                        keep[(uint32_t)(cj + y) * (uint32_t)R + (uint32_t)(ci + x)] = (int32_t)N[x][y];
+                    }
+#pragma unroll
+            for (int x = 0; x < kRegCats; ++x) {
+                if ((cnt & 1) && x <= pi) keep[(uint32_t)(ci + x) * (uint32_t)(R + 1)] = (int32_t)ni[x];
+                if ((cnt & 2) && x <= pj) keep[(uint32_t)(cj + x) * (uint32_t)(R + 1)] = (int32_t)nj[x];
+            }
         }
         int na = 0, nb = 0;
         stat = 0.0;
@@ -558,8 +578,18 @@ __global__ __launch_bounds__(kWG) void k_depth0_pairs(DepthArgs A) {
         const int gi = pd.var_off + rec.i, gj = pd.var_off + rec.j;
         double stat;
         int64_t df;
+        int32_t *keep = nullptr;
+        int R = 0, ci = 0, cj = 0;
+        if (A.bits.prob) {
+            keep = A.bits.prob[rec.prob].gram;
+            R = A.bits.prob[rec.prob].R;
+            ci = A.bits.var[gi].cat;
+            cj = A.bits.var[gj].cat;
+        }
+        // (pair (i, i + 1) leaves the counts of i, the last pair those of the last variable)
         pair_stat(P, gp, P.var_oh[gi], P.var_oh[gj], A.cards[gi], A.cards[gj], pd.m, A.tile.stat,
-                  A.tile.df_rule != 0, stat, df);
+                  A.tile.df_rule != 0, stat, df, keep, ci, cj, R,
+                  rec.j == rec.i + 1 ? (rec.j == pd.n - 1 ? 3 : 1) : 0);
         if (chi2_tail_lane(df, stat) > pd.alpha) A.min_accept[e] = 0ull;  // the depth's only test accepted
         ++ex;
         ob += 2.0 * (double)pd.m;
