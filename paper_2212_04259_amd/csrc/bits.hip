@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "device_ci.h"
+#include "gram.h"
 #include "kernels.h"
 
 namespace bns {
@@ -595,6 +596,285 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
         if (tal_bytes > 0.0) atomicAdd(&c->stats[1].operand_bytes, tal_bytes);
         atomicMax(&c->stats[1].t_end, (unsigned long long)wall_clock64());
     }
+}
+
+// A pair's decision in FP64 by a whole wave: lane c < ri rj holds cell c of
+// its table (out of line: rare).  n: the table [x][y], then N_x+ and N_+y.
+static __device__ __noinline__ bool pair_near(const uint32_t *n, int ri, int rj, uint32_t m, int df, double alpha,
+                                              int stat) {
+    const int lane = threadIdx.x & 63;
+    const int x = lane / rj, y = lane - x * rj;
+    double s = 0.0;
+    if (lane < ri * rj) {
+        const uint32_t N = n[x * kBitCards + y], nx = n[kBitCards * kBitCards + x];
+        const uint32_t ny = n[kBitCards * (kBitCards + 1) + y];
+        s = stat ? x2_term<double>(N, nx, ny, m) : g2_half_term<double>(N, nx, ny, m);
+    }
+    s = wave_sum(s);
+    return chi2_tail_wave(df, stat ? s : 2.0 * s).p > alpha;
+}
+
+// ---------------------------------------------------------------------------
+// Depth 0 of a search that runs depth 1 from bit planes: one workgroup per
+// block of 16 x 16 pairs, one lane per pair.  The lane sums its cells over
+// the chunks of the Gram tiles, completes the table, leaves it and its
+// transpose in the pairwise tables, and decides the pair by its FP32
+// statistic against the critical values (in FP64 within their reach); the
+// block writes the adjacency, the removal depths and, for small searches, its
+// 16-bit pieces of the adjacency bit rows.  Every pair is tested once, so the
+// depth needs no edge list (records, level order and removals of half a
+// million edges).  What bounds it: a few dependent loads per lane, and the
+// FP32 terms at many pairs.  With the chunk sum and the FP64 pair kernel in
+// its place, depth 0 and its preparation took 220 us more at 1,000 variables,
+// 190 us at 220 (one workgroup's edge list) and 30 us at 20; this kernel takes
+// 74, 22 and 12 us there.
+// ---------------------------------------------------------------------------
+constexpr int kPairSide = 16;
+constexpr int kBitPlanes = kBitCards - 1;
+
+__global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
+    __shared__ uint32_t cnt[2][kPairSide][kBitCards];  // category counts of the block's rows and columns
+    __shared__ uint8_t keep_sh[kPairSide][kPairSide + 4];
+    __shared__ uint32_t near_sh[kWaves][kBitCards * (kBitCards + 2)];
+    __shared__ unsigned int removed_sh;
+    const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
+    const PairArgs &PA = A.pairs;
+    int lo = 0, hi = A.n_probs - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (A.bits.prob[mid].block_base <= (int)blockIdx.x) lo = mid;
+        else hi = mid - 1;
+    }
+    const BitProb B = A.bits.prob[lo];
+    const ProbDev P = A.probs[lo];
+    const GramProb gp = PA.gp[lo];
+    int ib = 0, rem = (int)blockIdx.x - B.block_base;
+    while (rem >= B.nb16 - ib) {
+        rem -= B.nb16 - ib;
+        ++ib;
+    }
+    const int jb = ib + rem;
+    const VarRec *vars = A.bits.var + P.var_off;
+    const uint32_t m = (uint32_t)P.m;
+    const uint32_t R = (uint32_t)B.R;
+    // entry (a, b) of the Gram matrix summed over the chunks
+    const int nch = gp.nchunks;
+    const int64_t tile_words = (int64_t)kGramT * kGramT;
+    auto entry = [&](int a, int b) {
+        int off;
+        const int64_t t = gram_tile(gp, kGramT, a, b, &off);
+        return PA.part + (gp.item_base + t * nch) * tile_words + off;
+    };
+    if (tid == 0) removed_sh = 0u;
+    // category counts: two lanes' worth of variables, one plane per lane
+    if (tid < 2 * kPairSide * kBitPlanes) {
+        const int side = tid / (kPairSide * kBitPlanes), q = tid - side * kPairSide * kBitPlanes;
+        const int k = q / kBitPlanes, x = q - k * kBitPlanes;
+        const int v = kPairSide * (side ? jb : ib) + k;
+        uint32_t s = 0;
+        if (v < P.n && x < vars[v].card - 1) {
+            const int32_t *e = entry(vars[v].plane + x, vars[v].plane + x);
+            for (int c = 0; c < nch; c += 8) {
+                uint32_t u[8];
+#pragma unroll
+                for (int k8 = 0; k8 < 8; ++k8) u[k8] = (uint32_t)e[(c + k8 < nch ? c + k8 : 0) * tile_words];
+#pragma unroll
+                for (int k8 = 0; k8 < 8; ++k8) s += c + k8 < nch ? u[k8] : 0u;
+            }
+        }
+        cnt[side][k][x] = s;
+    }
+    __syncthreads();
+    if (tid < 2 * kPairSide) {
+        const int side = tid / kPairSide, k = tid - side * kPairSide;
+        const int v = kPairSide * (side ? jb : ib) + k;
+        if (v < P.n) {
+            const int r = vars[v].card;
+            uint32_t s = m;
+            for (int x = 0; x < r - 1; ++x) s -= cnt[side][k][x];
+            cnt[side][k][r - 1] = s;
+            // (the diagonal blocks leave the category counts in the tables)
+            if (ib == jb && side == 0)
+                for (int x = 0; x < r; ++x) {
+                    const uint32_t d = (uint32_t)(vars[v].cat + x);
+                    B.gram[d * (R + 1u)] = (int32_t)cnt[0][k][x];
+                }
+        }
+    }
+    __syncthreads();
+    const int i = kPairSide * ib + ti, j = kPairSide * jb + tj;
+    bool kept = false, near = false;
+    int df = 0, ri = 1, rj = 1;
+    uint32_t *mine = near_sh[tid >> 6];
+    uint32_t N[kBitCards][kBitCards];
+    if (i < j && j < P.n) {
+        const VarRec vi = vars[i], vj = vars[j];
+        const int pi = vi.card - 1, pj = vj.card - 1;
+        ri = vi.card;
+        rj = vj.card;
+#pragma unroll
+        for (int x = 0; x < kBitCards; ++x)
+#pragma unroll
+            for (int y = 0; y < kBitCards; ++y) N[x][y] = 0u;
+        {
+            const int32_t *e[kBitPlanes][kBitPlanes];
+#pragma unroll
+            for (int x = 0; x < kBitPlanes; ++x)
+#pragma unroll
+                for (int y = 0; y < kBitPlanes; ++y)
+                    e[x][y] = entry(vi.plane + (x < pi ? x : 0), vj.plane + (y < pj ? y : 0));
+            if (pi > 0 && pj > 0)
+                for (int c = 0; c < nch; c += 4) {
+                    // four chunks' entries in flight (past the end: the first
+                    // chunk's, not added)
+                    uint32_t v[4][kBitPlanes][kBitPlanes];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int x = 0; x < kBitPlanes; ++x)
+#pragma unroll
+                            for (int y = 0; y < kBitPlanes; ++y)
+                                if (x < pi && y < pj)
+                                    v[u][x][y] = (uint32_t)e[x][y][(c + u < nch ? c + u : 0) * tile_words];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int x = 0; x < kBitPlanes; ++x)
+#pragma unroll
+                            for (int y = 0; y < kBitPlanes; ++y)
+                                if (x < pi && y < pj && c + u < nch) N[x][y] += v[u][x][y];
+                }
+        }
+        // last column, then last row
+#pragma unroll
+        for (int x = 0; x < kBitCards; ++x) {
+            uint32_t rest = cnt[0][ti][x <= pi ? x : 0];
+#pragma unroll
+            for (int y = 0; y < kBitPlanes; ++y) rest -= N[x][y];
+#pragma unroll
+            for (int y = 0; y < kBitCards; ++y)
+                if (y == pj && x < pi) N[x][y] = rest;
+        }
+#pragma unroll
+        for (int y = 0; y < kBitCards; ++y) {
+            uint32_t rest = cnt[1][tj][y <= pj ? y : 0];
+#pragma unroll
+            for (int x = 0; x < kBitPlanes; ++x) rest -= N[x][y];
+#pragma unroll
+            for (int x = 0; x < kBitCards; ++x)
+                if (x == pi && y <= pj) N[x][y] = rest;
+        }
+        const uint32_t ci = (uint32_t)vi.cat, cj = (uint32_t)vj.cat;
+        const bool x2 = A.tile.stat != 0;
+        float st = 0.0f;
+        int na = 0, nb = 0;
+#pragma unroll
+        for (int y = 0; y < kBitCards; ++y) nb += y <= pj && cnt[1][tj][y] > 0u ? 1 : 0;
+#pragma unroll
+        for (int x = 0; x < kBitCards; ++x) {
+            if (x > pi) continue;
+            const uint32_t nx = cnt[0][ti][x];
+            na += nx > 0u ? 1 : 0;
+#pragma unroll
+            for (int y = 0; y < kBitCards; ++y) {
+                if (y > pj) continue;
+                B.gram[(ci + x) * R + cj + y] = (int32_t)N[x][y];
+                B.gram[(cj + y) * R + ci + x] = (int32_t)N[x][y];
+                const uint32_t ny = cnt[1][tj][y];
+                st += x2 ? x2_term<float>(N[x][y], nx, ny, m) : bit_g2_term(N[x][y], nx, ny, m);
+            }
+        }
+        const double stat = x2 ? (double)st : 2.0 * (double)st;
+        df = A.tile.df_rule ? (na - 1) * (nb - 1) : pi * pj;
+        const double2 cr = A.bits.crit[(int64_t)B.crit_row * kCritDf + df];
+        kept = df > 0 && stat > cr.y;
+        near = df > 0 && !(stat < cr.x) && !kept;
+    }
+    for (uint64_t todo = __ballot(near); todo; todo &= todo - 1ull) {
+        // the wave decides its near pairs one after the other
+        const int L = __ffsll((long long)todo) - 1;
+        if ((tid & 63) == L) {
+#pragma unroll
+            for (int x = 0; x < kBitCards; ++x) {
+#pragma unroll
+                for (int y = 0; y < kBitCards; ++y) mine[x * kBitCards + y] = N[x][y];
+                mine[kBitCards * kBitCards + x] = cnt[0][ti][x < ri ? x : 0];
+                mine[kBitCards * (kBitCards + 1) + x] = cnt[1][tj][x < rj ? x : 0];
+            }
+        }
+        Grp::wave().sync();
+        const bool indep = pair_near(mine, __shfl(ri, L, 64), __shfl(rj, L, 64), m, __shfl(df, L, 64), P.alpha,
+                                     A.tile.stat);
+        if ((tid & 63) == L) kept = !indep;
+        Grp::wave().sync();
+    }
+    keep_sh[ti][tj] = kept ? 1 : 0;
+    __syncthreads();
+    // both orders of every pair of the block; (row, column) of the block's own
+    // and of its transpose
+    unsigned int gone = i < j && j < P.n && !kept ? 1u : 0u;
+    const int8_t dep = 0;
+    if (ib != jb) {
+        if (i < P.n && j < P.n) {
+            A.adj[P.adj_off + (int64_t)i * P.n + j] = kept ? 1 : 0;
+            A.rdepth[P.adj_off + (int64_t)i * P.n + j] = kept ? (int8_t)-1 : dep;
+        }
+        const int i2 = kPairSide * jb + ti, j2 = kPairSide * ib + tj;  // transposed
+        if (i2 < P.n && j2 < P.n) {
+            const bool k2 = keep_sh[tj][ti] != 0;
+            A.adj[P.adj_off + (int64_t)i2 * P.n + j2] = k2 ? 1 : 0;
+            A.rdepth[P.adj_off + (int64_t)i2 * P.n + j2] = k2 ? (int8_t)-1 : dep;
+        }
+    } else if (i < P.n && j < P.n) {
+        const bool k2 = (i < j ? keep_sh[ti][tj] : keep_sh[tj][ti]) != 0;
+        A.adj[P.adj_off + (int64_t)i * P.n + j] = k2 && i != j ? 1 : 0;
+        A.rdepth[P.adj_off + (int64_t)i * P.n + j] = k2 || i == j ? (int8_t)-1 : dep;
+    }
+    if (small && tid < 2 * kPairSide) {
+        // 16-bit pieces of the bit rows (rows beyond n have none; a piece
+        // beyond n is 0)
+        const int side = tid / kPairSide, k = tid - side * kPairSide;
+        const int v = kPairSide * (side ? jb : ib) + k, piece = side ? ib : jb;
+        if (v < P.n && !(side && ib == jb)) {
+            uint32_t bits = 0;
+            for (int q = 0; q < kPairSide; ++q) {
+                const bool on = ib == jb ? (k < q ? keep_sh[k][q] : keep_sh[q][k]) != 0 && k != q
+                                         : (side ? keep_sh[q][k] : keep_sh[k][q]) != 0;
+                bits |= on ? 1u << q : 0u;
+            }
+            const int W = (P.n + 63) >> 6;
+            ((uint16_t *)(A.adjbits + P.bit_off + (int64_t)v * W))[piece] = (uint16_t)bits;
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) gone += __shfl_xor(gone, off, 64);
+    if ((tid & 63) == 0 && gone) atomicAdd(&removed_sh, gone);
+    __syncthreads();
+    if (tid == 0) {
+        Ctl *c = A.ctl;
+        const unsigned long long np = (unsigned long long)P.n * (unsigned long long)(P.n - 1) / 2ull;
+        if (removed_sh) atomicAdd(&c->stats[0].removed, (unsigned long long)removed_sh);
+        if (A.per_prob) {
+            PStatDev &ps = A.pstat[(int64_t)lo * kMaxDepths];
+            if (removed_sh) atomicAdd(&ps.removed, (unsigned long long)removed_sh);
+            if ((int)blockIdx.x == B.block_base) ps.edges = ps.tickets = ps.required = ps.executed = np;
+        }
+        if ((int)blockIdx.x == B.block_base) atomicAdd(&c->stats[0].operand_bytes, 2.0 * (double)np * (double)P.m);
+        if (blockIdx.x == 0) {
+            const unsigned long long all = (unsigned long long)A.n_pairs;
+            c->stats[0].edges = c->stats[0].tickets = c->stats[0].required = c->stats[0].executed = all;
+            c->depth = 1;
+        }
+        atomicMax(&c->stats[0].t_end, (unsigned long long)wall_clock64());
+    }
+}
+
+hipError_t launch_depth0_bits(const DepthArgs &a, hipStream_t s) {
+    const bool small = small_search(a);
+    hipError_t e = launch_gram_tiles(a, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_depth0_bits, dim3(a.bits.blocks), dim3(kWG), 0, s, a, small ? 1 : 0);
+    e = hipGetLastError();
+    return e == hipSuccess && small ? launch_prepare_small(a, s) : e;
 }
 
 hipError_t launch_depth1_bits(const DepthArgs &a, hipStream_t s, hipEvent_t start, hipEvent_t stop) {

@@ -676,10 +676,6 @@ static const int64_t kPairPartMax = 1ll << 30;
 // MI355X, 8.9e7 (60 variables, 50,000 samples) is faster in the test kernel,
 // 2.4e9 (220 variables, 100,000 samples) and more through the contraction.
 static const double kPairsAutoWork = 5e8;
-// The same when depth 1 runs from bit planes too (which needs the planes and
-// pairwise tables): 9.5e5 (20 variables, 5,000 samples) is 5% slower, 8.9e7
-// (60 variables, 50,000 samples) 9% faster than in the test kernel.
-static const double kBitsAutoWork = 1e7;
 // Bit planes kept between calls; a larger buffer goes at the end of its call.
 static const size_t kPlanesKeep = 512ull << 20;
 // Pairwise tables held at most for depth 1 from bit planes (1 GiB).
@@ -720,13 +716,20 @@ static bns_status plan_pairs(const DevCtx &dc, const bns_dataset *const *ds, int
     // about two work items per workgroup slot of the device: split the
     // samples into chunks when the tiles alone are fewer
     const int64_t unit = pp.planes ? kPlaneBlock : 64;
-    const int64_t least = pp.planes ? 4096 : 2048;
+    const int64_t least = pp.planes ? 8192 : 2048;
     const int64_t want = 2ll * dc.num_cu * gram_max_wg_per_cu(pp.planes);
     const int64_t whole = (m_max + unit - 1) / unit * unit;
     int64_t chunk = whole;
     if (pp.planes) {
-        // (by the mean work per tile: datasets of different lengths)
-        chunk = std::max<int64_t>(least, (int64_t)(tile_samples / (double)want) / unit * unit);
+        // (by the mean work per tile: datasets of different lengths.  An item
+        // of fewer than 16,384 samples spends more on its tile's way through
+        // LDS and memory than on the product, so shorter chunks are only for
+        // plans with less than one item per compute unit.)
+        auto cut = [&](int64_t items, int64_t floor) {
+            return std::max<int64_t>(floor, (int64_t)(tile_samples / (double)items) / unit * unit);
+        };
+        chunk = cut(want, 16384);
+        if (tile_samples / (double)chunk < (double)dc.num_cu) chunk = cut(dc.num_cu, least);
     } else if (tiles < want) chunk = std::max<int64_t>(least, ((m_max * tiles + want - 1) / want + unit - 1) / unit * unit);
     pp.chunk = std::min(chunk, whole);
     pp.gps.resize((size_t)P);
@@ -1114,8 +1117,9 @@ static bns_status depth_graph(DevCtx &dc, const DepthArgs &a, int grid, int K, b
     g->tri_seq = tri_seq;
     g->seq_units = seq_units;
     HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    hipError_t e = init ? launch_init_search(a, s) : hipSuccess;
-    for (int i = 0; i < K && e == hipSuccess; ++i) {
+    const bool bits0 = init && a.bits_policy;  // depth 0 without edge records
+    hipError_t e = bits0 ? launch_depth0_bits(a, s) : init ? launch_init_search(a, s) : hipSuccess;
+    for (int i = bits0 ? 1 : 0; i < K && e == hipSuccess; ++i) {
         e = launch_depth_prepare(a, s);
         if (e == hipSuccess && i == tri_seq) e = launch_depth1_gram(a, s);
         if (e == hipSuccess)
@@ -1210,14 +1214,12 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     // Depth 0 through the pair contraction (verification mode keeps the test
     // kernel, whose FP32 statistic it compares with FP64).
     bool want_pairs = !verify && o.depth0 == BNS_DEPTH0_PAIRS;
-    bool bits_pay = true;
     if (!verify && o.depth0 == BNS_DEPTH0_AUTO) {
         // the contraction's fixed cost (its launches, latency-bound steps)
         // pays once the depth's counting work is large
         double work = 0.0;
         for (int32_t k = 0; k < P; ++k) work += 0.5 * (double)ds[k]->n * (ds[k]->n - 1) * (double)ds[k]->m;
         want_pairs = work >= kPairsAutoWork;
-        bits_pay = work >= kBitsAutoWork;
     }
     // Depth 1 through the masked Gram contractions (batched form; verification
     // mode keeps the test kernel, as at depth 0).
@@ -1265,7 +1267,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     // with the product of its plane counts, and the kernel holds its counts in
     // registers) and the caller leaves the paths and shapes of depths 0 and 1
     // open.
-    bool bits_want = bits_pay && !verify && o.form == BNS_FORM_BATCHED && o.depth0 != BNS_DEPTH0_TESTS &&
+    bool bits_want = !verify && o.form == BNS_FORM_BATCHED && o.depth0 != BNS_DEPTH0_TESTS &&
                      o.depth1 == BNS_DEPTH1_AUTO && o.group_tests == BNS_GROUP_AUTO && o.round_tests == 0 &&
                      o.test_group == 0 && ((o.wave_depths | o.block_depths) & 3u) == 0u && (unbounded || dmax >= 1);
     int64_t table_words = 0;
@@ -1329,6 +1331,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     if (st != BNS_OK) return st;
     HIP_TRY(dc.setup.ensure(setup_bytes));
     HIP_TRY(dc.pinned(setup_bytes));
+    int32_t blocks16 = 0;  // blocks of 16 x 16 pairs
     {
         char *h = (char *)dc.hpin;
         std::memcpy(h + o_probs, probs.data(), sizeof(ProbDev) * (size_t)P);
@@ -1345,6 +1348,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
             VarRec *vr = (VarRec *)(h + o_vars);
             BitProb *bp = (BitProb *)(h + o_bits);
             int64_t tab = 0;
+            blocks16 = 0;
             for (int32_t k = 0; k < P; ++k) {
                 int32_t R = 0;
                 for (int32_t v = 0; v < ds[k]->n; ++v) {
@@ -1352,8 +1356,12 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
                     vr[g] = {ds[k]->cards[v], pp.var_oh[(size_t)g], R, 0};
                     R += ds[k]->cards[v];
                 }
+                // (whole words of the bit rows: four pieces of 16)
+                const int32_t nb16 = (ds[k]->n + 63) / 64 * 4;
                 bp[k] = {dc.planes.as<uint32_t>() + pp.gps[k].plane_off, (uint32_t)(4 * pp.gps[k].plane_stride),
-                         (uint32_t)((ds[k]->m + 31) / 32), (uint32_t)(4 * pp.gps[k].R * pp.gps[k].plane_stride), R, crit_of[(size_t)k], dc.tables.as<int32_t>() + tab};
+                         (uint32_t)((ds[k]->m + 31) / 32), (uint32_t)(4 * pp.gps[k].R * pp.gps[k].plane_stride), R, crit_of[(size_t)k], blocks16, nb16,
+                         dc.tables.as<int32_t>() + tab};
+                blocks16 += nb16 * (nb16 + 1) / 2;
                 tab += (int64_t)R * R;
             }
             for (size_t q = 0; q < crit_alpha.size(); ++q)
@@ -1478,6 +1486,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
         a.bits.n_crit = (int32_t)crit_alpha.size();
         a.bits.grid = std::max(1, dc.num_cu * bits_max_wg_per_cu());
         a.bits.run_log2 = a.grab_block_log2;
+        a.bits.blocks = blocks16;
         a.bits_policy = 1;
         a.xy_policy = 0;
     }
@@ -1581,8 +1590,15 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
             HIP_TRY(hipGraphLaunch(ge->exec, s));
             HIP_TRY(hipEventRecord(ge->done, s));
         } else {
-            if (d == 0) HIP_TRY(launch_init_search(a, s));
-            for (int i = 0; i < K; ++i) {
+            const bool bits0 = d == 0 && a.bits_policy;  // depth 0 without edge records
+            if (bits0) {
+                if (o.timing) HIP_TRY(hipEventRecord(evg.v[0], s));
+                HIP_TRY(launch_depth0_bits(a, s));
+                if (o.timing) HIP_TRY(hipEventRecord(evg.v[1], s));
+            } else if (d == 0) {
+                HIP_TRY(launch_init_search(a, s));
+            }
+            for (int i = bits0 ? 1 : 0; i < K; ++i) {
                 HIP_TRY(launch_depth_prepare(a, s));
                 if (d == 0 && i == 0 && a.pairs.part) {
                     if (o.timing) HIP_TRY(hipEventRecord(evg.v[0], s));

@@ -119,6 +119,8 @@ struct BitProb {
     uint32_t bytes;          // bytes of the problem's planes (below 4 GiB)
     int32_t R;               // categories of all variables
     int32_t crit_row;        // row of the critical values
+    int32_t block_base;      // first block of 16 x 16 pairs of the problem
+    int32_t nb16;            // such blocks per side
     int32_t *gram;           // pairwise tables: gram[(cat of x) R + cat of y] = N_xy; diagonal: category counts
 };
 
@@ -129,7 +131,7 @@ struct BitArgs {
     int32_t n_crit;        // rows: distinct alphas
     int32_t grid;          // workgroups of the kernel
     int32_t run_log2;      // units dealt to a grab counter in runs of 2^this
-    int32_t pad;
+    int32_t blocks;        // workgroups of the depth-0 kernel (blocks of 16 x 16 pairs)
 };
 
 // Arguments of the per-depth pipeline of a skeleton search (all device pointers).
@@ -210,6 +212,18 @@ struct DepthArgs {
     BitArgs bits;                 // depth 1 from bit planes (bits.prob non-null)
 };
 
+// A search's counters before its first depth.
+__device__ inline void reset_search(Ctl *c) {
+    c->depth = 0;
+    c->done = 0;
+    c->error = 0;
+    c->n_edges = 0;
+    c->total_tickets = 0;
+    c->pool_used = 0;
+    c->apply_done = 0;
+    c->gram_depth = -1;
+}
+
 // Small searches keep the adjacency as bit rows in LDS and prepare each depth
 // inside the removal kernel of the depth before.
 constexpr int kSmallBitWords = 4096;
@@ -234,6 +248,12 @@ inline int depth_units(const DepthArgs &a, int d) {
     if (d <= kNarrowDepth && a.tile.stat == 0 && a.tile.df_rule == 0) return 2;
     return 0;
 }
+// Depth 0 of a search that runs depth 1 from bit planes, its first kernels:
+// planes, Gram tiles, decisions, removals and pairwise tables, with no edge
+// records; the control block is then at depth 1, prepared for small searches.
+hipError_t launch_depth0_bits(const DepthArgs &a, hipStream_t s);
+hipError_t launch_gram_tiles(const DepthArgs &a, hipStream_t s);
+hipError_t launch_prepare_small(const DepthArgs &a, hipStream_t s);
 // Depth 1 from bit planes, in place of the depth's test kernel (units 3).
 hipError_t launch_depth1_bits(const DepthArgs &a, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 int bits_max_wg_per_cu();

@@ -122,14 +122,7 @@ __global__ void k_init_search(DepthArgs A) {
         Ctl *c = A.ctl;
         if (threadIdx.x == 0) {
             if (A.err_cnt) *A.err_cnt = 0ull;
-            c->depth = 0;
-            c->done = 0;
-            c->error = 0;
-            c->n_edges = 0;
-            c->total_tickets = 0;
-            c->pool_used = 0;
-            c->apply_done = 0;
-            c->gram_depth = -1;
+            reset_search(c);
         }
         for (int i = threadIdx.x; i < kMaxDepths; i += blockDim.x) {
             DepthStatDev z = {};
@@ -2085,6 +2078,11 @@ static int grid_rows(int n_globals) { return (n_globals + kWaves - 1) / kWaves; 
 hipError_t launch_init_search(const DepthArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(k_init_search, dim3(64, a.n_probs), dim3(kWG), 0, s, a);
     if (small_search(a)) hipLaunchKernelGGL(k_prepare_small, dim3(1), dim3(kSmallThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_prepare_small(const DepthArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL(k_prepare_small, dim3(1), dim3(kSmallThreads), 0, s, a);
     return hipGetLastError();
 }
 

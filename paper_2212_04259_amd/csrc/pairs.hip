@@ -114,8 +114,21 @@ BNS_INLINE void plane_words(const u32x4 (&x)[2], uint32_t valid, int r, uint32_t
     }
 }
 
-__global__ __launch_bounds__(kWG) void k_planes(PairArgs P, const uint8_t *cards, Ctl *c) {
-    if (c && blockIdx.x == 0 && threadIdx.x == 0) c->stats[0].t_start = wall_clock64();
+// reset: the kernel is the first of a search (depths 0 and 1 from bit planes)
+// and clears the control block and the per-problem counters.
+__global__ __launch_bounds__(kWG) void k_planes(PairArgs P, const uint8_t *cards, Ctl *c, PStatDev *pstat, int reset) {
+    if (c && blockIdx.x == 0) {
+        if (reset) {
+            if (threadIdx.x == 0) reset_search(c);
+            for (int i = threadIdx.x; i < kMaxDepths; i += kWG) c->stats[i] = DepthStatDev{};
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) c->stats[0].t_start = wall_clock64();
+    }
+    if (reset && pstat)
+        for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < (int64_t)P.n_gp * kMaxDepths;
+             i += (int64_t)gridDim.x * kWG)
+            pstat[i] = PStatDev{};
     const int lane = threadIdx.x & 63;
     const int w = uni((int)(threadIdx.x >> 6));
     for (int64_t item = (int64_t)blockIdx.x * kWaves + w; item < P.plane_items; item += (int64_t)gridDim.x * kWaves) {
@@ -405,14 +418,6 @@ __global__ __launch_bounds__(kWG) void k_gram_reduce(PairArgs P) {
     }
 }
 
-// Entry (a, b), a <= b, of a problem's Gram matrix.
-BNS_INLINE uint32_t gram_entry(const PairArgs &P, const GramProb &gp, int a, int b) {
-    const int T = P.T;
-    const int ta = a / T, tb = b / T;
-    const int64_t ti = (int64_t)ta * gp.nb - (int64_t)ta * (ta - 1) / 2 + (tb - ta);
-    return (uint32_t)P.gram[(gp.tile_base + ti) * (int64_t)T * T + (int64_t)(a - ta * T) * T + (b - tb * T)];
-}
-
 // Statistic (G^2 or X^2, FP64) and df of a pair with ri and rj categories
 // over m samples from its cells and category counts (the marginals N_x+ and
 // N_+y; N_++ = m).
@@ -444,13 +449,8 @@ BNS_INLINE void pair_terms(int ri, int rj, int64_t m, int stat_kind, bool adj, d
 // the table is completed in registers.
 constexpr int kRegCats = 5;
 
-// keep (may be null): a problem's pairwise tables over all categories (R
-// columns), where the pair's table and its transpose are left at rows ci and
-// cj; cnt: the variables whose category counts it leaves on the diagonal
-// (1: i, 2: j).
 BNS_INLINE void pair_stat(const PairArgs &P, const GramProb &gp, int oi, int oj, int ri, int rj, int64_t m,
-                          int stat_kind, bool adj, double &stat, int64_t &df, int32_t *keep = nullptr, int ci = 0,
-                          int cj = 0, int R = 0, int cnt = 0) {
+                          int stat_kind, bool adj, double &stat, int64_t &df) {
     if (!P.planes) {
         pair_terms(ri, rj, m, stat_kind, adj, stat, df, [&](int x, int y) { return gram_entry(P, gp, oi + x, oj + y); },
                    [&](int x) { return gram_entry(P, gp, oi + x, oi + x); },
@@ -499,21 +499,6 @@ BNS_INLINE void pair_stat(const PairArgs &P, const GramProb &gp, int oi, int oj,
 #pragma unroll
             for (int x = 0; x < kRegCats; ++x)
                 if (x == pi && y <= pj) N[x][y] = rest;
-        }
-        if (keep) {
-#pragma unroll
-            for (int x = 0; x < kRegCats; ++x)
-#pragma unroll
-                for (int y = 0; y < kRegCats; ++y)
-                    if (x <= pi && y <= pj) {
-                        keep[(uint32_t)(ci + x) * (uint32_t)R + (uint32_t)(cj + y)] = (int32_t)N[x][y];
-                        keep[(uint32_t)(cj + y) * (uint32_t)R + (uint32_t)(ci + x)] = (int32_t)N[x][y];
-                    }
-#pragma unroll
-            for (int x = 0; x < kRegCats; ++x) {
-                if ((cnt & 1) && x <= pi) keep[(uint32_t)(ci + x) * (uint32_t)(R + 1)] = (int32_t)ni[x];
-                if ((cnt & 2) && x <= pj) keep[(uint32_t)(cj + x) * (uint32_t)(R + 1)] = (int32_t)nj[x];
-            }
         }
         int na = 0, nb = 0;
         stat = 0.0;
@@ -578,18 +563,8 @@ __global__ __launch_bounds__(kWG) void k_depth0_pairs(DepthArgs A) {
         const int gi = pd.var_off + rec.i, gj = pd.var_off + rec.j;
         double stat;
         int64_t df;
-        int32_t *keep = nullptr;
-        int R = 0, ci = 0, cj = 0;
-        if (A.bits.prob) {
-            keep = A.bits.prob[rec.prob].gram;
-            R = A.bits.prob[rec.prob].R;
-            ci = A.bits.var[gi].cat;
-            cj = A.bits.var[gj].cat;
-        }
-        // (pair (i, i + 1) leaves the counts of i, the last pair those of the last variable)
         pair_stat(P, gp, P.var_oh[gi], P.var_oh[gj], A.cards[gi], A.cards[gj], pd.m, A.tile.stat,
-                  A.tile.df_rule != 0, stat, df, keep, ci, cj, R,
-                  rec.j == rec.i + 1 ? (rec.j == pd.n - 1 ? 3 : 1) : 0);
+                  A.tile.df_rule != 0, stat, df);
         if (chi2_tail_lane(df, stat) > pd.alpha) A.min_accept[e] = 0ull;  // the depth's only test accepted
         ++ex;
         ob += 2.0 * (double)pd.m;
@@ -639,21 +614,31 @@ int gram_max_wg_per_cu(bool planes) {
     return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 
-// The Gram tiles of every problem (and their sum over chunks); cards: per
-// global variable.
-static void launch_gram(const PairArgs &p, const uint8_t *cards, Ctl *c, hipStream_t s) {
+// The Gram tiles of every problem; cards: per global variable, first: see
+// k_planes.
+static void launch_tiles(const PairArgs &p, const uint8_t *cards, Ctl *c, PStatDev *pstat, int first, hipStream_t s) {
     const dim3 grid(p.gram_grid);
     if (p.planes) {
-        hipLaunchKernelGGL(k_planes, dim3(p.plane_grid), dim3(kWG), 0, s, p, cards, c);
+        hipLaunchKernelGGL(k_planes, dim3(p.plane_grid), dim3(kWG), 0, s, p, cards, c, pstat, first);
         hipLaunchKernelGGL(k_gram_planes, grid, dim3(kGramWG), 0, s, p, c);
     } else {
         hipLaunchKernelGGL(k_gram<kGramT>, grid, dim3(kGramWG), 0, s, p, c);
     }
+}
+
+// The Gram tiles and their sum over chunks.
+static void launch_gram(const PairArgs &p, const uint8_t *cards, Ctl *c, hipStream_t s) {
+    launch_tiles(p, cards, c, nullptr, 0, s);
     if (p.gram != p.part) {
         const int64_t words = p.tiles * p.T * p.T / 4;
         const int rg = (int)std::max<int64_t>(1, std::min<int64_t>(4096, (words + kWG - 1) / kWG));
         hipLaunchKernelGGL(k_gram_reduce, dim3(rg), dim3(kWG), 0, s, p);
     }
+}
+
+hipError_t launch_gram_tiles(const DepthArgs &a, hipStream_t s) {
+    launch_tiles(a.pairs, a.cards, a.ctl, a.per_prob ? a.pstat : nullptr, 1, s);
+    return hipGetLastError();
 }
 
 hipError_t launch_depth0_pairs(const DepthArgs &a, hipStream_t s) {

@@ -38,8 +38,12 @@ def _chain(cards, m, seed, keep=0.75):
     return np.array(cols, dtype=np.uint8), np.array(cards, dtype=np.uint8)
 
 
+PAIRS = 2  # options.depth0: small searches take the path too
+
+
 def _compare(bns, orc, data, cards, alpha, max_depth, label, statistic=0, df_rule=0, **opt):
     print(label, flush=True)
+    opt = dict(dict(depth0=PAIRS), **opt)
     ref = orc.pc_skeleton(data, cards, alpha, max_depth, statistic=statistic, df_rule=df_rule)
     o = bns.bns_options_default(statistic=statistic, df_rule=df_rule, **opt)
     got = bns.bns_pc_skeleton(data, cards, alpha, max_depth, o)
@@ -59,6 +63,15 @@ def test_plane_counts(bns, orc, rx, rz):
     # every (r_X, r_Y) with Z of two or five categories
     data, cards = _chain([rx, 2, rz, 3, rz, 4, rz, 5, rz, rx], 4_000, seed=10 * rx + rz)
     _compare(bns, orc, data, cards, 0.01, 1, f"bits rx={rx} rz={rz}")
+
+
+@pytest.mark.parametrize("n", [2, 15, 16, 17, 63, 64, 65, 129])
+def test_pair_blocks(bns, orc, n):
+    # depth 0 in blocks of 16 x 16 pairs, 64-bit adjacency rows
+    rng = np.random.default_rng(n)
+    data, cards = _chain(rng.integers(1, 6, n).tolist(), 700, seed=n, keep=0.5)
+    for max_depth in (0, 2):
+        _compare(bns, orc, data, cards, 0.05, max_depth, f"bits n={n} depth<={max_depth}")
 
 
 @pytest.mark.parametrize("n,r", [(30, 5), (40, 2), (70, 3)])
@@ -85,7 +98,7 @@ def test_batch_with_several_alphas(bns, orc):
     alphas = [0.05, 0.01, 0.2, 1e-4, 0.9995]
     hs = [bns.bns_dataset_create(d.data, d.cards) for d in dss]
     print("bits batch of alphas", flush=True)
-    outs = bns.bns_pc_skeleton_batch(hs, alphas, [-1, 1, 2, -1, -1], bns.bns_options_default())
+    outs = bns.bns_pc_skeleton_batch(hs, alphas, [-1, 1, 2, -1, -1], bns.bns_options_default(depth0=PAIRS))
     for d, a, md, got in zip(dss, alphas, [-1, 1, 2, -1, -1], outs):
         compare_with_oracle(got, orc.pc_skeleton(d.data, d.cards, a, md), f"alpha={a}")
 
