@@ -175,6 +175,20 @@ struct CritRow {
     std::vector<double2> v;
 };
 
+// Pinned staging of a CI batch of at most kCiStageBytes: the kernel itself
+// brings the results to host memory and raises a completion flag, which the
+// host polls: no copies out, no stream synchronisation.  Allocated with the
+// device's state.
+static const size_t kCiStageBytes = 1 << 20;
+static const size_t kCiDirect = 256;  // tests up to which the kernel works on the host memory itself (777: 72 against 66 us a call)
+struct CiStage {
+    char *h = nullptr;                   // kCiStageBytes, pinned
+    char *d = nullptr;                   // the same on the device
+    unsigned long long *flag = nullptr;  // pinned
+    unsigned int *cnt = nullptr;         // device: workgroups done
+    unsigned long long seq = 0;          // launches so far
+};
+
 // Per-device state: properties, a library stream, and grow-only workspaces.
 struct DevCtx {
     int device = -1;
@@ -239,6 +253,10 @@ struct DevCtx {
     }
     int lds_per_cu = 0;
     int wall_khz = 0;  // device wall-clock rate
+    // staging of bns_ci_batch (under mu) and of bns_ci_batch_noalloc (under
+    // its own lock: the two may run at the same time)
+    CiStage ci_stage, ci_stage_noalloc;
+    int ci_wg = 0;  // workgroups of the CI kernel per compute unit at the default LDS
 };
 
 static std::mutex g_ctx_mu;
@@ -269,6 +287,13 @@ static bns_status get_ctx(int device, DevCtx **out) {
     *c->h_flag = 0;
     HIP_TRY(hipMalloc(&c->pub, 64));
     HIP_TRY(hipMemset(c->pub, 0, 64));
+    for (CiStage *st : {&c->ci_stage, &c->ci_stage_noalloc}) {
+        HIP_TRY(hipHostMalloc((void **)&st->h, kCiStageBytes, hipHostMallocDefault));
+        HIP_TRY(hipHostMalloc((void **)&st->flag, 64, hipHostMallocDefault));
+        HIP_TRY(hipMalloc((void **)&st->d, kCiStageBytes));
+        *st->flag = 0;
+        st->cnt = (unsigned int *)((char *)c->pub + (st == &c->ci_stage ? 16 : 32));
+    }
     *out = c.get();
     g_ctx.push_back(std::move(c));
     return BNS_OK;
@@ -337,6 +362,13 @@ extern "C" bns_status bns_dataset_create(const uint8_t *data, int64_t m, int32_t
     }
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
+    {
+        // the device's state, with its staging: calls that may not allocate
+        // find it in place
+        DevCtx *dc = nullptr;
+        st = get_ctx(dev, &dc);
+        if (st != BNS_OK) return st;
+    }
     std::unique_ptr<bns_dataset> ds(new bns_dataset());
     ds->device = dev;
     ds->m = m;
@@ -478,6 +510,61 @@ static bns_status check_ci_tests(const bns_dataset *ds, const bns_ci_test *tests
 // ---------------------------------------------------------------------------
 // bns_ci_batch
 // ---------------------------------------------------------------------------
+static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
+static hipError_t wait_published(hipStream_t s, const volatile unsigned long long *flag, unsigned long long want);
+
+// Workgroups of the CI kernel per compute unit (kept for the default LDS).
+static int ci_wg_per_cu(DevCtx &dc, const Tile &tile) {
+    if (tile.lds_words * 4 != kDefaultLdsBytes) return std::max(1, depth_tests_max_wg_per_cu(tile.lds_words * 4));
+    if (!dc.ci_wg) dc.ci_wg = std::max(1, depth_tests_max_wg_per_cu(kDefaultLdsBytes));
+    return dc.ci_wg;
+}
+
+// Runs a checked batch through pinned staging (it must fit): results in the
+// caller's arrays.  *done is false, with nothing run, when it does not fit.
+static bns_status ci_staged(CiStage &sg, const bns_dataset *ds, const bns_ci_test *tests, int64_t n_tests,
+                            const int32_t *z_pool, int64_t z_pool_len, double alpha, const Tile &tile, int max_grid,
+                            hipStream_t s, double *g2, int64_t *df, double *p, int32_t *flags, bool *done) {
+    static_assert(sizeof(bns_ci_test) == sizeof(CiTestDev), "test records are copied as they are");
+    *done = false;
+    const size_t nt = (size_t)n_tests;
+    if (nt > kCiStageBytes || (size_t)z_pool_len > kCiStageBytes) return BNS_OK;
+    // tests | conditioning pool | g2 | p | df | flags
+    const size_t o_z = al256(sizeof(CiTestDev) * nt), o_g2 = o_z + al256(sizeof(int32_t) * (size_t)z_pool_len);
+    const size_t o_p = o_g2 + al256(sizeof(double) * nt), o_df = o_p + al256(sizeof(double) * nt);
+    const size_t o_fl = o_df + al256(sizeof(int64_t) * nt);
+    if (o_fl + al256(sizeof(int32_t) * nt) > kCiStageBytes) return BNS_OK;
+    *done = true;
+    const size_t end = o_fl + al256(sizeof(int32_t) * nt);
+    std::memcpy(sg.h, tests, sizeof(CiTestDev) * nt);
+    if (z_pool_len > 0) std::memcpy(sg.h + o_z, z_pool, sizeof(int32_t) * (size_t)z_pool_len);
+    // few tests: the kernel reads and writes the host memory itself; many:
+    // one copy in and a copying kernel out
+    const bool direct = nt <= kCiDirect;
+    char *db = direct ? sg.h : sg.d;
+    auto at = [&](char *b) {
+        return CiOutSoa{(double *)(b + o_g2), (double *)(b + o_p), (int64_t *)(b + o_df), (int32_t *)(b + o_fl)};
+    };
+    const CiDone done_arg{sg.cnt, sg.flag, ++sg.seq};
+    if (!direct) HIP_TRY(hipMemcpyAsync(sg.d, sg.h, o_g2, hipMemcpyHostToDevice, s));
+    hipError_t e = launch_ci_batch(ds->d_data, ds->ld, ds->m, ds->d_cards, (const CiTestDev *)db,
+                                   (const int32_t *)(db + o_z), n_tests, alpha, tile, nullptr, nullptr, nullptr, max_grid,
+                                   s, at(db),
+                                   direct ? done_arg : CiDone{});
+    if (e == hipSuccess && !direct) e = launch_ci_out(sg.d + o_g2, sg.h + o_g2, (int64_t)(end - o_g2), done_arg, s);
+    if (e == hipSuccess) e = wait_published(s, sg.flag, sg.seq);
+    HIP_TRY(e);
+    const CiOutSoa soa = at(sg.h);
+    for (size_t t = 0; t < nt; ++t)
+        if (soa.flags[t] >> 8) return fail(BNS_E_TABLE_TOO_LARGE, "test %lld exceeded device limits", (long long)t);
+    if (g2) std::memcpy(g2, soa.g2, sizeof(double) * nt);
+    if (p) std::memcpy(p, soa.p, sizeof(double) * nt);
+    if (df) std::memcpy(df, soa.df, sizeof(int64_t) * nt);
+    if (flags)
+        for (size_t t = 0; t < nt; ++t) flags[t] = soa.flags[t] & 3;
+    return BNS_OK;
+}
+
 extern "C" bns_status bns_ci_batch(const bns_dataset *ds, const bns_ci_test *tests, int64_t n_tests,
                                    const int32_t *z_pool, int64_t z_pool_len, double alpha,
                                    const bns_options *opt, double *g2, int64_t *df, double *p,
@@ -520,6 +607,13 @@ extern "C" bns_status bns_ci_batch(const bns_dataset *ds, const bns_ci_test *tes
     if (!dg.ok) return fail(BNS_E_DEVICE, "cannot select device %d", ds->device);
     std::lock_guard<std::mutex> lk(dc->mu);
     hipStream_t s = o.stream ? (hipStream_t)o.stream : dc->stream;
+    const int wg = ci_wg_per_cu(*dc, tile);
+    if (!tables_out) {
+        bool done = false;
+        st = ci_staged(dc->ci_stage, ds, tests, n_tests, z_pool, z_pool_len, alpha, tile, dc->num_cu * wg, s, g2, df, p,
+                       flags, &done);
+        if (done) return st;
+    }
     HIP_TRY(dc->ci_tests.ensure(sizeof(CiTestDev) * (size_t)n_tests));
     HIP_TRY(dc->ci_z.ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(z_pool_len, 1)));
     HIP_TRY(dc->ci_out.ensure(sizeof(CiOutDev) * (size_t)n_tests));
@@ -549,11 +643,9 @@ extern "C" bns_status bns_ci_batch(const bns_dataset *ds, const bns_ci_test *tes
         d_tab = dc->ci_tab.as<uint32_t>();
         d_taboff = dc->ci_taboff.as<int64_t>();
     }
-    const int wg = std::max(1, depth_tests_max_wg_per_cu(tile.lds_words * 4));
-    const int grid = (int)std::min<int64_t>((n_tests + kWaves - 1) / kWaves, (int64_t)dc->num_cu * wg);
     HIP_TRY(launch_ci_batch(ds->d_data, ds->ld, ds->m, ds->d_cards, dc->ci_tests.as<CiTestDev>(),
                             dc->ci_z.as<int32_t>(), n_tests, alpha, tile, dc->ci_out.as<CiOutDev>(),
-                            d_tab, d_taboff, grid, s));
+                            d_tab, d_taboff, dc->num_cu * wg, s));
     std::vector<CiOutDev> ho((size_t)n_tests);
     HIP_TRY(hipMemcpyAsync(ho.data(), dc->ci_out.p, sizeof(CiOutDev) * (size_t)n_tests,
                            hipMemcpyDeviceToHost, s));
@@ -584,15 +676,12 @@ static __device__ __align__(256) unsigned char scratch[BNS_NOALLOC_SCRATCH_BYTES
 static const int kNoallocDevices = 64;
 static std::mutex g_noalloc_mu[kNoallocDevices];   // serialises calls per device
 static void *g_scratch_dev[kNoallocDevices];       // device address of scratch, per device
-static int g_noalloc_cu[kNoallocDevices], g_noalloc_lds[kNoallocDevices];
-
-static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
+static int g_noalloc_cu[kNoallocDevices], g_noalloc_lds[kNoallocDevices], g_noalloc_wg[kNoallocDevices];
 
 extern "C" bns_status bns_ci_batch_noalloc(const bns_dataset *ds, const bns_ci_test *tests, int64_t n_tests,
                                            const int32_t *z_pool, int64_t z_pool_len, double alpha,
                                            const bns_options *opt, double *g2, int64_t *df, double *p,
                                            int32_t *flags) {
-    static_assert(sizeof(bns_ci_test) == sizeof(CiTestDev), "test records are copied as they are");
     if (!ds) return fail(BNS_E_INVALID_ARG, "dataset is NULL");
     if (n_tests < 0) return fail(BNS_E_INVALID_ARG, "n_tests < 0");
     if (n_tests > 0 && !tests) return fail(BNS_E_INVALID_ARG, "tests is NULL");
@@ -633,16 +722,27 @@ extern "C" bns_status bns_ci_batch_noalloc(const bns_dataset *ds, const bns_ci_t
     if (st != BNS_OK) return st;
     char *base = (char *)g_scratch_dev[dev];
     hipStream_t s = (hipStream_t)o.stream;
+    int wg = g_noalloc_wg[dev];
+    if (!wg || tile.lds_words * 4 != kDefaultLdsBytes) wg = std::max(1, depth_tests_max_wg_per_cu(tile.lds_words * 4));
+    if (tile.lds_words * 4 == kDefaultLdsBytes) g_noalloc_wg[dev] = wg;
+    {
+        // (the dataset's creation made the device's state)
+        DevCtx *dc = nullptr;
+        st = get_ctx(dev, &dc);
+        if (st != BNS_OK) return st;
+        bool done = false;
+        st = ci_staged(dc->ci_stage_noalloc, ds, tests, n_tests, z_pool, z_pool_len, alpha, tile,
+                       g_noalloc_cu[dev] * wg, s, g2, df, p, flags, &done);
+        if (done) return st;
+    }
     HIP_TRY(hipMemcpyAsync(base, tests, sizeof(CiTestDev) * (size_t)n_tests, hipMemcpyHostToDevice, s));
     if (z_pool_len > 0)
         HIP_TRY(hipMemcpyAsync(base + o_z, z_pool, sizeof(int32_t) * (size_t)z_pool_len, hipMemcpyHostToDevice, s));
     CiOutSoa soa{(double *)(base + o_g2), (double *)(base + o_p), (int64_t *)(base + o_df),
                  (int32_t *)(base + o_fl)};
-    const int wg = std::max(1, depth_tests_max_wg_per_cu(tile.lds_words * 4));
-    const int grid = (int)std::min<int64_t>((n_tests + kWaves - 1) / kWaves, (int64_t)g_noalloc_cu[dev] * wg);
     HIP_TRY(launch_ci_batch(ds->d_data, ds->ld, ds->m, ds->d_cards, (const CiTestDev *)base,
                             (const int32_t *)(base + o_z), n_tests, alpha, tile, nullptr, nullptr, nullptr,
-                            grid, s, soa));
+                            g_noalloc_cu[dev] * wg, s, soa));
     if (g2) HIP_TRY(hipMemcpyAsync(g2, soa.g2, sizeof(double) * (size_t)n_tests, hipMemcpyDeviceToHost, s));
     if (p) HIP_TRY(hipMemcpyAsync(p, soa.p, sizeof(double) * (size_t)n_tests, hipMemcpyDeviceToHost, s));
     if (df) HIP_TRY(hipMemcpyAsync(df, soa.df, sizeof(int64_t) * (size_t)n_tests, hipMemcpyDeviceToHost, s));

@@ -289,11 +289,22 @@ struct CiOutSoa {
     int64_t *df;
     int32_t *flags;
 };
+// Completion of a launch that leaves its results in pinned host memory: its
+// last workgroup (cnt counts them, 0 between launches) writes seq into *flag,
+// which the host polls.  flag null: no such launch.
+struct CiDone {
+    unsigned int *cnt;
+    unsigned long long *flag;
+    unsigned long long seq;
+};
+// Copies bytes (a multiple of 16) of results to pinned host memory.
+hipError_t launch_ci_out(const void *src, void *dst, int64_t bytes, CiDone done, hipStream_t s);
 hipError_t launch_ci_batch(const uint8_t *data, int64_t ld, int64_t m, const uint8_t *cards,
                            const CiTestDev *tests, const int32_t *zpool, int64_t n_tests,
                            double alpha, Tile tile, CiOutDev *out, uint32_t *tables,
-                           const int64_t *table_off, int grid, hipStream_t s,
-                           CiOutSoa soa = CiOutSoa{nullptr, nullptr, nullptr, nullptr});
+                           const int64_t *table_off, int max_wg, hipStream_t s,
+                           CiOutSoa soa = CiOutSoa{nullptr, nullptr, nullptr, nullptr},
+                           CiDone done = CiDone{});
 
 // Plain per-test form: sample-parallel count of one test into per-block
 // partial tables, then a single-workgroup finish (fixed-order sum, FP64 G^2).

@@ -66,7 +66,7 @@ __device__ inline void unrank_serial(const Binom &B, int64_t p, int d, uint64_t 
 __global__ void k_ci_batch(const uint8_t *data, int64_t ld, int64_t m, const uint8_t *cards,
                            const CiTestDev *tests, const int32_t *zpool, int64_t n_tests,
                            double alpha, Tile tile, CiOutDev *out, CiOutSoa soa, uint32_t *tables,
-                           const int64_t *table_off);
+                           const int64_t *table_off, CiDone done);
 __global__ void k_plain_count(const uint8_t *data, int64_t ld, int64_t m, const uint8_t *cards,
                               const PlainTest pt, int64_t spb, uint32_t *partials, int64_t T,
                               int lds_words);
@@ -2189,14 +2189,26 @@ int depth_tests_fit_lds(int lds_per_cu) {
 // Batched CI tests (bns_ci_batch): one test per wave, same device path as the
 // skeleton search.
 // ---------------------------------------------------------------------------
+// Raises the completion flag when the grid's last workgroup is done (every
+// wave's results visible to the host before its workgroup counts itself).
+BNS_INLINE void signal_done(const CiDone &done) {
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0 && atomicAdd(done.cnt, 1u) + 1u == gridDim.x) {
+        __threadfence_system();
+        *done.cnt = 0u;
+        __hip_atomic_store(done.flag, done.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 // Results go to out (one record per test) or, with out null, to the
-// separate arrays of soa (any may be null).
+// separate arrays of soa (any may be null; host memory with done.flag).
 __global__ __launch_bounds__(kWG) void k_ci_batch(const uint8_t *data, int64_t ld, int64_t m,
                                                   const uint8_t *cards, const CiTestDev *tests,
                                                   const int32_t *zpool, int64_t n_tests,
                                                   double alpha, Tile tile, CiOutDev *out,
                                                   CiOutSoa soa, uint32_t *tables,
-                                                  const int64_t *table_off) {
+                                                  const int64_t *table_off, CiDone done) {
     extern __shared__ uint32_t lds[];
     __shared__ TestSh tsh[kWaves];
     const int w = threadIdx.x >> 6;
@@ -2245,14 +2257,33 @@ __global__ __launch_bounds__(kWG) void k_ci_batch(const uint8_t *data, int64_t l
         }
         gw.sync();
     }
+    if (done.flag) signal_done(done);
+}
+
+// Results of many tests to the host.  A launch of its own: a workgroup that
+// makes its results visible to the others (so that the last one could copy
+// them) writes its XCD's L2 back, which cost 4,096 tests 25 us; the kernel
+// boundary orders them for less, and 8-byte stores to the host one test at a
+// time took 60 us.
+__global__ __launch_bounds__(kWG) void k_ci_out(const uint4 *src, uint4 *dst, int64_t n, CiDone done) {
+    for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < n; i += (int64_t)gridDim.x * kWG) dst[i] = src[i];
+    signal_done(done);
+}
+
+hipError_t launch_ci_out(const void *src, void *dst, int64_t bytes, CiDone done, hipStream_t s) {
+    const int64_t n = bytes / 16;
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(16, (n + kWG - 1) / kWG));
+    hipLaunchKernelGGL(k_ci_out, dim3(grid), dim3(kWG), 0, s, (const uint4 *)src, (uint4 *)dst, n, done);
+    return hipGetLastError();
 }
 
 hipError_t launch_ci_batch(const uint8_t *data, int64_t ld, int64_t m, const uint8_t *cards,
                            const CiTestDev *tests, const int32_t *zpool, int64_t n_tests,
                            double alpha, Tile tile, CiOutDev *out, uint32_t *tables,
-                           const int64_t *table_off, int grid, hipStream_t s, CiOutSoa soa) {
+                           const int64_t *table_off, int max_wg, hipStream_t s, CiOutSoa soa, CiDone done) {
+    const int grid = (int)std::min<int64_t>((n_tests + kWaves - 1) / kWaves, max_wg);
     hipLaunchKernelGGL(k_ci_batch, dim3(grid), dim3(kWG), (size_t)tile.lds_words * 4u, s, data, ld,
-                       m, cards, tests, zpool, n_tests, alpha, tile, out, soa, tables, table_off);
+                       m, cards, tests, zpool, n_tests, alpha, tile, out, soa, tables, table_off, done);
     return hipGetLastError();
 }
 
