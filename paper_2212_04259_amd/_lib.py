@@ -307,11 +307,10 @@ def _collect(h, orient: bool = False) -> Skeleton:
         _check(L.bns_skeleton_removals(h, _ptr(depth), _ptr(off), None, 0, ctypes.byref(plen)))
         pool = np.zeros(max(plen.value, 1), dtype=np.int32)
         _check(L.bns_skeleton_removals(h, None, None, _ptr(pool), plen.value, ctypes.byref(plen)))
-        sep = {}
+        # whole lists at a time: element by element from the arrays cost 1.2 us a pair
         ii, jj = np.nonzero(np.triu(depth >= 0, 1))
-        for i, j in zip(ii.tolist(), jj.tolist()):
-            d, o = int(depth[i, j]), int(off[i, j])
-            sep[(i, j)] = tuple(int(v) for v in pool[o:o + d])
+        members, dd, oo = pool.tolist(), depth[ii, jj].tolist(), off[ii, jj].tolist()
+        sep = {(i, j): tuple(members[o:o + d]) for i, j, d, o in zip(ii.tolist(), jj.tolist(), dd, oo)}
         nd = ctypes.c_int32()
         _check(L.bns_skeleton_stats(h, None, 0, ctypes.byref(nd)))
         st = (bns_depth_stats * max(nd.value, 1))()

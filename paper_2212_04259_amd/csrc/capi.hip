@@ -1098,8 +1098,14 @@ extern "C" int32_t bns_skeleton_n_vars(const bns_skeleton *sk) { return sk ? sk-
 
 extern "C" bns_status bns_skeleton_adjacency(const bns_skeleton *sk, uint8_t *adj) {
     if (!sk || !adj) return fail(BNS_E_INVALID_ARG, "NULL argument");
-    sk->expand();
-    std::memcpy(adj, sk->adj.data(), sk->adj.size());
+    const size_t n = (size_t)sk->n, nn = n * n;
+    if (sk->full) {
+        std::memcpy(adj, sk->adj.data(), nn);
+        return BNS_OK;
+    }
+    const int8_t *r = sk->rdep.data();
+    for (size_t e = 0; e < nn; ++e) adj[e] = (uint8_t)r[e] >> 7;  // -1: kept
+    for (size_t i = 0; i < n; ++i) adj[i * n + i] = 0;
     return BNS_OK;
 }
 
@@ -1109,17 +1115,20 @@ extern "C" bns_status bns_skeleton_sepset(const bns_skeleton *sk, int32_t i, int
     if (!sk || !len) return fail(BNS_E_INVALID_ARG, "NULL argument");
     if (i < 0 || j < 0 || i >= sk->n || j >= sk->n || i == j) return fail(BNS_E_INVALID_ARG, "bad pair");
     if (cap < 0 || (cap > 0 && !members)) return fail(BNS_E_INVALID_ARG, "bad members buffer");
-    sk->expand();
-    const int64_t ij = (int64_t)i * sk->n + j;
-    const int32_t d = sk->depth[ij];
+    const int32_t d = sk->depth_at((int64_t)i * sk->n + j);
     if (removal_depth) *removal_depth = d;
     if (d < 0) {
         *len = -1;
         return BNS_OK;
     }
     *len = d;
-    const int64_t off = sk->sepoff[ij];
-    for (int32_t k = 0; k < d && k < cap; ++k) members[k] = sk->pool[off + k];
+    if (d == 0) return BNS_OK;
+    try {
+        const int64_t off = sk->sepset_at(i, j);
+        for (int32_t k = 0; k < d && k < cap; ++k) members[k] = sk->pool[(size_t)(off + k)];
+    } catch (const std::bad_alloc &) {
+        return fail(BNS_E_NOMEM, "no memory for the sepset index");
+    }
     return BNS_OK;
 }
 
@@ -1127,9 +1136,23 @@ extern "C" bns_status bns_skeleton_removals(const bns_skeleton *sk, int32_t *dep
                                             int32_t *pool, int64_t pool_cap, int64_t *pool_len) {
     if (!sk) return fail(BNS_E_INVALID_ARG, "NULL skeleton");
     if (pool_cap < 0 || (pool_cap > 0 && !pool)) return fail(BNS_E_INVALID_ARG, "bad pool buffer");
-    sk->expand();
-    if (depth) std::memcpy(depth, sk->depth.data(), sk->depth.size() * sizeof(int32_t));
-    if (sep_off) std::memcpy(sep_off, sk->sepoff.data(), sk->sepoff.size() * sizeof(int64_t));
+    const int64_t n = sk->n;
+    const size_t nn = (size_t)n * (size_t)n;
+    if (sk->full) {
+        if (depth) std::memcpy(depth, sk->depth.data(), nn * sizeof(int32_t));
+        if (sep_off) std::memcpy(sep_off, sk->sepoff.data(), nn * sizeof(int64_t));
+    } else {
+        const int8_t *r = sk->rdep.data();
+        if (depth)
+            for (size_t e = 0; e < nn; ++e) depth[e] = r[e];
+        if (sep_off) {
+            for (size_t e = 0; e < nn; ++e) sep_off[e] = r[e] == 0 ? 0 : -1;  // (0: the empty set)
+            for (size_t q = 0; q < sk->rec_pair.size(); ++q) {
+                const int64_t i = sk->rec_pair[q] / n, j = sk->rec_pair[q] % n;
+                sep_off[i * n + j] = sep_off[j * n + i] = sk->rec_off[q];
+            }
+        }
+    }
     if (pool) std::memcpy(pool, sk->pool.data(), sizeof(int32_t) * (size_t)std::min<int64_t>(pool_cap, (int64_t)sk->pool.size()));
     if (pool_len) *pool_len = (int64_t)sk->pool.size();
     return BNS_OK;

@@ -18,71 +18,89 @@
 
 namespace {
 
+// Marks in the caller's n x n matrix.
 struct Marks {
-    int n;
-    std::vector<int8_t> m;  // m[i * n + j]: 0 not adjacent, 1 no arrowhead at j, 2 arrowhead at j
-    int8_t at(int i, int j) const { return m[(size_t)i * n + j]; }
+    int64_t n;
+    int8_t *m;  // m[i * n + j]: 0 not adjacent, 1 no arrowhead at j, 2 arrowhead at j
+    int8_t &at(int i, int j) const { return m[i * n + j]; }
     bool adjacent(int i, int j) const { return at(i, j) != 0; }
     bool directed(int i, int j) const { return at(i, j) == 2 && at(j, i) == 1; }
     bool undirected(int i, int j) const { return at(i, j) == 1 && at(j, i) == 1; }
 };
 
 bool in_sepset(const bns_skeleton &sk, int x, int y, int z) {
-    const int64_t ij = (int64_t)x * sk.n + y;
-    const int32_t d = sk.depth[ij];
+    const int32_t d = sk.depth_at((int64_t)x * sk.n + y);
     if (d <= 0) return false;  // removed with the empty set (depth 0)
-    const int32_t *s = sk.pool.data() + sk.sepoff[ij];
+    const int32_t *s = sk.pool.data() + sk.sepset_at(x, y);
     return std::binary_search(s, s + d, z);  // members are ascending
 }
 
 }  // namespace
 
-extern "C" bns_status bns_skeleton_orient(const bns_skeleton *sk, int8_t *cpdag) {
-    if (!sk || !cpdag) return BNS_E_INVALID_ARG;
-    sk->expand();
+static void orient(const bns_skeleton *sk, int8_t *cpdag) {
     const int n = sk->n;
-    Marks G{n, std::vector<int8_t>((size_t)n * n, 0)};
-    // neighbour lists (ascending) of the skeleton
-    std::vector<std::vector<int>> nb((size_t)n);
-    for (int i = 0; i < n; ++i)
-        for (int j = 0; j < n; ++j)
-            if (i != j && sk->adj[(size_t)i * n + j]) {
-                nb[i].push_back(j);
-                G.m[(size_t)i * n + j] = 1;
+    Marks G{n, cpdag};
+    std::memset(cpdag, 0, (size_t)n * (size_t)n);
+    // neighbour lists (ascending) of the skeleton, and its edges' marks; eight
+    // pairs at a time are passed over when none is kept (the usual case)
+    std::vector<int> nbs;              // all lists, one after the other
+    std::vector<size_t> first((size_t)n + 1, 0);
+    for (int i = 0; i < n; ++i) {
+        const size_t row = (size_t)i * n;
+        for (int j = 0; j < n;) {
+            if (!sk->full && j + 8 <= n) {
+                uint64_t w;
+                std::memcpy(&w, sk->rdep.data() + row + j, 8);
+                if (!(w & 0x8080808080808080ull)) {
+                    j += 8;
+                    continue;
+                }
             }
-    // step 2: unshielded colliders
-    std::vector<uint8_t> head((size_t)n * n, 0);
+            for (const int e = std::min(n, sk->full ? n : j + 8); j < e; ++j)
+                if (sk->kept(i, j)) {
+                    nbs.push_back(j);
+                    cpdag[row + j] = 1;
+                }
+        }
+        first[(size_t)i + 1] = nbs.size();
+    }
+    struct List {
+        const int *b, *e;
+        const int *begin() const { return b; }
+        const int *end() const { return e; }
+    };
+    auto nb = [&](int v) { return List{nbs.data() + first[(size_t)v], nbs.data() + first[(size_t)v + 1]}; };
+    // step 2: unshielded colliders, all judged on the skeleton
+    std::vector<std::pair<int, int>> found;
     for (int z = 0; z < n; ++z) {
-        const std::vector<int> &a = nb[z];
-        for (size_t p = 0; p < a.size(); ++p)
-            for (size_t q = p + 1; q < a.size(); ++q) {
-                const int x = a[p], y = a[q];  // x < y
-                if (sk->adj[(size_t)x * n + y]) continue;
+        const List a = nb(z);
+        for (const int *p = a.b; p < a.e; ++p)
+            for (const int *q = p + 1; q < a.e; ++q) {
+                const int x = *p, y = *q;  // x < y
+                if (G.adjacent(x, y)) continue;
                 if (in_sepset(*sk, x, y, z)) continue;
-                head[(size_t)x * n + z] = head[(size_t)y * n + z] = 1;
+                found.emplace_back(x, z);
+                found.emplace_back(y, z);
             }
     }
-    for (size_t k = 0; k < head.size(); ++k)
-        if (head[k]) G.m[k] = 2;
+    for (const auto &f : found) G.at(f.first, f.second) = 2;
     // step 3: Meek rounds
-    std::vector<std::pair<int, int>> found;
-    std::vector<uint8_t> mark((size_t)n * n, 0);  // orientations found this round
     std::vector<int> cs;
     for (;;) {
         found.clear();
         for (int a = 0; a < n; ++a)
-            for (int b : nb[a]) {
+            for (int b : nb(a)) {
                 if (!G.undirected(a, b)) continue;
                 bool hit = false;
                 // R1: c -> a, c and b not adjacent
-                for (int c : nb[a])
+                for (int c : nb(a))
                     if (c != b && G.directed(c, a) && !G.adjacent(c, b)) {
                         hit = true;
                         break;
                     }
                 // R2: a -> c -> b
                 if (!hit)
-                    for (int c : nb[a])
+                    for (int c : nb(a))
                         if (c != b && G.directed(a, c) && G.directed(c, b)) {
                             hit = true;
                             break;
@@ -90,7 +108,7 @@ extern "C" bns_status bns_skeleton_orient(const bns_skeleton *sk, int8_t *cpdag)
                 // R3: a - c -> b and a - d -> b, c and d not adjacent
                 if (!hit) {
                     cs.clear();
-                    for (int c : nb[a])
+                    for (int c : nb(a))
                         if (c != b && G.undirected(a, c) && G.directed(c, b)) cs.push_back(c);
                     for (size_t p = 0; p < cs.size() && !hit; ++p)
                         for (size_t q = p + 1; q < cs.size(); ++q)
@@ -102,15 +120,19 @@ extern "C" bns_status bns_skeleton_orient(const bns_skeleton *sk, int8_t *cpdag)
                 if (hit) found.emplace_back(a, b);
             }
         if (found.empty()) break;
-        for (const auto &f : found) mark[(size_t)f.first * n + f.second] = 1;
-        for (const auto &f : found) {
-            const int a = f.first, b = f.second;
-            G.m[(size_t)a * n + b] = 2;
-            if (!mark[(size_t)b * n + a]) G.m[(size_t)b * n + a] = 1;
-        }
-        for (const auto &f : found) mark[(size_t)f.first * n + f.second] = 0;
+        // together: an edge this round orients both ways keeps both
+        // arrowheads (each was undirected, 1 / 1, when the round began)
+        for (const auto &f : found) G.at(f.first, f.second) = 2;
     }
-    std::memcpy(cpdag, G.m.data(), G.m.size());
+}
+
+extern "C" bns_status bns_skeleton_orient(const bns_skeleton *sk, int8_t *cpdag) {
+    if (!sk || !cpdag) return BNS_E_INVALID_ARG;
+    try {
+        orient(sk, cpdag);
+    } catch (const std::bad_alloc &) {
+        return BNS_E_NOMEM;
+    }
     return BNS_OK;
 }
 
