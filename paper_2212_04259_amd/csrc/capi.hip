@@ -154,7 +154,7 @@ struct GraphEntry {
     int K = 0;
     bool init = false;  // begins with the search's initialisation
     int tri_seq = -1;   // depth sequence that runs depth 1 through the Gram contraction
-    uint32_t seq_units = 0;  // work units of each depth sequence's test kernel (2 bits each)
+    uint32_t seq_units = 0;  // work units of each depth sequence's test kernel (4 bits each)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipEvent_t done = nullptr;  // recorded after each replay
@@ -785,8 +785,10 @@ static const int64_t kBitTableWords = 256ll << 20;
 static const int64_t kTriItemsMax = 16384;
 
 // planes: bit planes wanted; they are used when they take no more memory than
-// the columns (a mean cardinality of at most 9) or than 64 MiB.
-static bns_status plan_pairs(const DevCtx &dc, const bns_dataset *const *ds, int32_t P, bool planes, PairPlan &pp) {
+// the columns (a mean cardinality of at most 9) or than 64 MiB.  values: planes
+// of values after those of each problem (see value_planes).
+static bns_status plan_pairs(const DevCtx &dc, const bns_dataset *const *ds, int32_t P, bool planes, PairPlan &pp,
+                             bool values = false) {
     pp = PairPlan();
     const int64_t T = kGramT;
     int64_t m_max = 1, plane_bytes = 0;
@@ -878,7 +880,9 @@ static bns_status plan_pairs(const DevCtx &dc, const bns_dataset *const *ds, int
             g.plane_off = plane_words;
             g.plane_stride = blocks * (kPlaneBlock / 32);
             g.plane_item = pp.plane_items;
-            plane_words += (int64_t)R * g.plane_stride;
+            g.rows = R;
+            for (int32_t v = 0; v < d->n && values; ++v) g.rows += value_planes(d->cards[v]);
+            plane_words += g.rows * g.plane_stride;
             pp.plane_items += (int64_t)d->n * ((g.plane_stride + 64 * kPlaneItem - 1) / (64 * kPlaneItem));
         }
     }
@@ -1248,7 +1252,7 @@ static bns_status depth_graph(DevCtx &dc, const DepthArgs &a, int grid, int K, b
         if (e == hipSuccess)
             e = (init && i == 0 && a.pairs.part) ? launch_depth0_pairs(a, s)
                                                   : launch_depth_tests(a, grid, s, nullptr, nullptr,
-                                                                       (int)((seq_units >> (2 * i)) & 3u));
+                                                                       (int)((seq_units >> (4 * i)) & 15u));
         if (e == hipSuccess) e = launch_depth_apply(a, s);
     }
     if (e == hipSuccess) e = launch_publish(a, s);
@@ -1394,16 +1398,19 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
                      o.depth1 == BNS_DEPTH1_AUTO && o.group_tests == BNS_GROUP_AUTO && o.round_tests == 0 &&
                      o.test_group == 0 && ((o.wave_depths | o.block_depths) & 3u) == 0u && (unbounded || dmax >= 1);
     int64_t table_words = 0;
+    // planes of values: for the depths that count from planes (depth_units)
+    const bool values_want = m_max >= kBitSamples && (unbounded || dmax >= 2);
     for (int32_t k = 0; k < P && bits_want; ++k) {
-        int64_t R = 0;
+        int64_t R = 0, values = 0;
         for (uint8_t cv : ds[k]->cards) {
             R += cv;
+            values += values_want ? value_planes(cv) : 0;
             if (cv > kBitCards) bits_want = false;
         }
         table_words += R * R;
         // (the kernel addresses a problem's planes with 32-bit byte offsets)
         const int64_t plane = (ds[k]->m + kPlaneBlock - 1) / kPlaneBlock * (kPlaneBlock / 8);
-        if (table_words > kBitTableWords || (R - ds[k]->n) * plane >= (1ll << 32) || ds[k]->m >= (1ll << 26))
+        if (table_words > kBitTableWords || (R - ds[k]->n + values) * plane >= (1ll << 32) || ds[k]->m >= (1ll << 26))
             bits_want = false;  // (products of two counts below 2^53)
     }
     // critical values per distinct alpha
@@ -1425,7 +1432,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
         bits = level == 0;
         pp = PairPlan();
         if (bits || want_pairs) {
-            st = plan_pairs(dc, ds, P, level < 2, pp);
+            st = plan_pairs(dc, ds, P, level < 2, pp, bits && values_want);
             if (bits && (st != BNS_OK || !pp.planes)) continue;
             if (st != BNS_OK && o.depth0 == BNS_DEPTH0_PAIRS) return st;
         }
@@ -1473,16 +1480,17 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
             int64_t tab = 0;
             blocks16 = 0;
             for (int32_t k = 0; k < P; ++k) {
-                int32_t R = 0;
+                int32_t R = 0, val = pp.gps[k].R;
                 for (int32_t v = 0; v < ds[k]->n; ++v) {
                     const int32_t g = probs[k].var_off + v;
-                    vr[g] = {ds[k]->cards[v], pp.var_oh[(size_t)g], R, 0};
+                    vr[g] = {ds[k]->cards[v], pp.var_oh[(size_t)g], R, val};
                     R += ds[k]->cards[v];
+                    val += value_planes(ds[k]->cards[v]);
                 }
                 // (whole words of the bit rows: four pieces of 16)
                 const int32_t nb16 = (ds[k]->n + 63) / 64 * 4;
                 bp[k] = {dc.planes.as<uint32_t>() + pp.gps[k].plane_off, (uint32_t)(4 * pp.gps[k].plane_stride),
-                         (uint32_t)((ds[k]->m + 31) / 32), (uint32_t)(4 * pp.gps[k].R * pp.gps[k].plane_stride), R, crit_of[(size_t)k], blocks16, nb16,
+                         (uint32_t)((ds[k]->m + 31) / 32), (uint32_t)(4 * pp.gps[k].rows * pp.gps[k].plane_stride), R, crit_of[(size_t)k], blocks16, nb16,
                          dc.tables.as<int32_t>() + tab};
                 blocks16 += nb16 * (nb16 + 1) / 2;
                 tab += (int64_t)R * R;
@@ -1597,6 +1605,10 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     // XCD); else one at a time.
     const bool runs = o.ticket_runs == 2 || (o.ticket_runs == 0 && col_bytes > kGrabRunBytes);
     a.grab_block_log2 = runs ? kGrabRunLog2 : 0;
+    double log_cards = 0.0;
+    for (int32_t g = 0; g < G; ++g) log_cards += std::log((double)std::max<int>(gcards[(size_t)g], 1));
+    a.deep_depth = kNarrowDepth + 1;
+    while (a.deep_depth < kMaxDepths && log_cards / G * (a.deep_depth + 2) < std::log(kDeepCells)) ++a.deep_depth;
     if (pp.on) {
         a.pairs = pair_args(dc, pp, dc.setup.as<char>(), o_gp, o_ohvar, o_ohcat, o_varoh);
     }
@@ -1605,6 +1617,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
         char *sb = dc.setup.as<char>();
         a.bits.prob = (const BitProb *)(sb + o_bits);
         a.bits.var = (const VarRec *)(sb + o_vars);
+        a.pairs.var = values_want ? a.bits.var : nullptr;
         a.bits.crit = (const double2 *)(sb + o_crit);
         a.bits.n_crit = (int32_t)crit_alpha.size();
         a.bits.grid = std::max(1, dc.num_cu * bits_max_wg_per_cu());
@@ -1706,7 +1719,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
         const int tri_seq = (tri_on && d <= 1 && 1 < d + K) ? 1 - d : -1;
         // the test kernel instance of each sequence (its depth's work units)
         uint32_t seq_units = 0;
-        for (int i = 0; i < K; ++i) seq_units |= (uint32_t)depth_units(a, d + i) << (2 * i);
+        for (int i = 0; i < K; ++i) seq_units |= (uint32_t)depth_units(a, d + i) << (4 * i);
         if (use_graph) {
             st = depth_graph(dc, a, grid, K, d == 0, tri_seq, seq_units, s, &ge);
             if (st != BNS_OK) return st;

@@ -29,6 +29,9 @@ struct TestSh {
     uint32_t card[kMaxCols];
     uint32_t mult[kMaxCols];       // cell stride of each column: 1, r_x, r_x r_y, ...
     int32_t ncols;                 // d + 2
+    int32_t bits;                  // > 0: counted from bit planes, the bits of the cell index: col[0 .. bits) are
+                                   // planes, cards and strides powers of two
+    int64_t df;                    // bits > 0: declared degrees of freedom
     int64_t m;                     // samples
     double red_d[kWaves];
     float red_f[kWaves];
@@ -655,6 +658,118 @@ BNS_INLINE void count_range(const TestSh &t, uint32_t *tab, uint32_t cbase, uint
     if ((q1 << 4) < s1) count_tail<kChunk>(t, tab, cbase, Tc, trash, logR, q1 << 4, s1, rank, S);
 }
 
+// ---------------------------------------------------------------------------
+// Counting from bit planes: bit k of every sample's cell index is plane k, 32
+// samples to a word.  A lane takes one word of each plane and transposes them
+// eight planes at a time, in three rounds of exchanges between pairs of words
+// (the 8 x 8 bit transposition within each byte): byte j of word q is then the
+// low eight bits of a cell index (bits past the last plane are 0).  That is
+// 1.5 operations per sample and eight planes, and two more to take a byte out
+// and form its address, against NC + 1 for NC columns of bytes; and a test of
+// four variables of three categories reads one byte per sample instead of
+// four, which is what bounded the byte form (10 TB/s into the compute units).
+// The increments (13.6 per clock and compute unit) bound this one.
+//
+// The order of the samples within a word does not matter; samples past the
+// end have no bit set and count into cell 0, which starts that much below 0.
+// ---------------------------------------------------------------------------
+constexpr int kMinPlaneBits = 4;   // (fewer: nearly every variable constant)
+constexpr int kMaxPlaneBits = 12;  // one pass: 4,096 cells, of which a workgroup's LDS holds one copy and the marginals
+
+template <int J>
+BNS_INLINE void bit_exchange(uint32_t &a, uint32_t &b) {
+    constexpr uint32_t m = J == 4 ? 0x0f0f0f0fu : J == 2 ? 0x33333333u : 0x55555555u;
+    const uint32_t x = (a & m) | ((b << J) & ~m);
+    b = ((a >> J) & m) | (b & ~m);
+    a = x;
+}
+
+// NB planes (at most 8) of 32 samples -> the bytes of their indices.
+template <int NB>
+BNS_INLINE void bit_transpose(const uint32_t *v, uint32_t (&x)[8]) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = k < NB ? v[k] : 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bit_exchange<4>(x[k], x[k + 4]);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        if (!(k & 2)) bit_exchange<2>(x[k], x[k + 2]);
+#pragma unroll
+    for (int k = 0; k < 8; k += 2) bit_exchange<1>(x[k], x[k + 1]);
+}
+
+// Increments for the 32 samples of one word of each plane: sh = logR + 2, at
+// the byte offset of the lane's replica of cell 0.
+template <int NB>
+BNS_INLINE void count_words(const uint32_t (&v)[NB], uint32_t at, int sh) {
+    uint32_t lo[8];
+    bit_transpose<(NB < 8 ? NB : 8)>(v, lo);
+    if constexpr (NB <= 8) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) lds_inc((((lo[k] >> (8 * j)) & 0xffu) << sh) + at);
+    } else {
+        uint32_t hi[8];
+        bit_transpose<NB - 8>(v + 8, hi);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t a = __builtin_amdgcn_perm(hi[k], lo[k], 0x05010400u);  // samples 0 and 1
+            const uint32_t b = __builtin_amdgcn_perm(hi[k], lo[k], 0x07030602u);  // samples 2 and 3
+            lds_inc(((a & 0xffffu) << sh) + at);
+            lds_inc(((a >> 16) << sh) + at);
+            lds_inc(((b & 0xffffu) << sh) + at);
+            lds_inc(((b >> 16) << sh) + at);
+        }
+    }
+}
+
+// Words [w0, w1) of the planes; the next word of every plane is loaded while
+// one is counted (past the last word: that word again).
+template <int NB>
+BNS_INLINE void count_planes(const TestSh &t, uint32_t *tab, int logR, uint32_t w0, uint32_t w1, int rank, int S) {
+    const uint32_t at = lds_offset(tab) + 4u * ((uint32_t)rank & ((1u << logR) - 1u));
+    const int sh = logR + 2;
+    const gword *p[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) p[k] = (const gword *)uniform_col(t.col[k]);
+    const uint32_t last = w1 - 1u;
+    uint32_t i = w0 + (uint32_t)rank;
+    if (i >= w1) return;
+    uint32_t a[NB], b[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) a[k] = p[k][i];
+    for (;;) {
+        const uint32_t ib = i + (uint32_t)S;
+        const uint32_t lb = min(ib, last);
+#pragma unroll
+        for (int k = 0; k < NB; ++k) b[k] = p[k][lb];
+        count_words<NB>(a, at, sh);
+        if (ib >= w1) break;
+        i = ib + (uint32_t)S;
+        const uint32_t la = min(i, last);
+#pragma unroll
+        for (int k = 0; k < NB; ++k) a[k] = p[k][la];
+        count_words<NB>(b, at, sh);
+        if (i >= w1) break;
+    }
+}
+
+BNS_INLINE void count_bits(const TestSh &t, int nb, uint32_t *tab, int logR, int64_t s0, int64_t s1, int rank, int S) {
+    const uint32_t w0 = (uint32_t)(s0 >> 5), w1 = (uint32_t)((s1 + 31) >> 5);
+    switch (nb) {
+        case 4: count_planes<4>(t, tab, logR, w0, w1, rank, S); break;
+        case 5: count_planes<5>(t, tab, logR, w0, w1, rank, S); break;
+        case 6: count_planes<6>(t, tab, logR, w0, w1, rank, S); break;
+        case 7: count_planes<7>(t, tab, logR, w0, w1, rank, S); break;
+        case 8: count_planes<8>(t, tab, logR, w0, w1, rank, S); break;
+        case 9: count_planes<9>(t, tab, logR, w0, w1, rank, S); break;
+        case 10: count_planes<10>(t, tab, logR, w0, w1, rank, S); break;
+        case 11: count_planes<11>(t, tab, logR, w0, w1, rank, S); break;
+        default: count_planes<12>(t, tab, logR, w0, w1, rank, S); break;
+    }
+}
+
 // Sums the 2^logR interleaved replicas of each cell: out[c] = sum_r rep[c * R + r].
 // Lane c starts at replica c mod R, so the lanes of a wave read R (up to 64)
 // different banks at every step.
@@ -757,6 +872,55 @@ BNS_INLINE double adj_df_partial(const Grp &g, const uint32_t *rows, const uint3
     return acc;
 }
 
+// Statistic (FP32) and adjusted df of the strata of one pass of a table of
+// RX x ry cells each, a stratum per lane: its marginals stay in registers.  A
+// pass has hundreds of strata, whose marginal tables took 10 - 23 k cycles and
+// their cells 6 k more.
+template <int RX>
+BNS_INLINE void strata_partial(const Grp &g, const uint32_t *tab, uint32_t ry, uint32_t Zc, int stat, float &acc,
+                               double *df_adj) {
+    for (uint32_t z = g.rank; z < Zc; z += g.size) {
+        const uint32_t *cell = tab + RX * ry * z;
+        uint32_t nx[RX], tot = 0, ny_seen = 0;
+#pragma unroll
+        for (int x = 0; x < RX; ++x) nx[x] = 0;
+        for (uint32_t y = 0; y < ry; ++y) {
+            uint32_t v[RX];
+#pragma unroll
+            for (int x = 0; x < RX; ++x) v[x] = cell[RX * y + x];
+            uint32_t ny = 0;
+#pragma unroll
+            for (int x = 0; x < RX; ++x) {
+                nx[x] += v[x];
+                ny += v[x];
+            }
+            tot += ny;
+            ny_seen += ny > 0u;
+        }
+        if (tot == 0u) continue;
+        for (uint32_t y = 0; y < ry; ++y) {
+            uint32_t v[RX];
+#pragma unroll
+            for (int x = 0; x < RX; ++x) v[x] = cell[RX * y + x];
+            uint32_t ny = 0;
+#pragma unroll
+            for (int x = 0; x < RX; ++x) ny += v[x];
+            if (ny == 0u) continue;  // (its cells add 0)
+#pragma unroll
+            for (int x = 0; x < RX; ++x) {
+                if (nx[x] == 0u) continue;
+                acc += stat ? x2_term<float>(v[x], nx[x], ny, tot) : g2_half_term<float>(v[x], nx[x], ny, tot);
+            }
+        }
+        if (df_adj) {
+            uint32_t nx_seen = 0;
+#pragma unroll
+            for (int x = 0; x < RX; ++x) nx_seen += nx[x] > 0u;
+            *df_adj += (double)(nx_seen - 1u) * (double)(ny_seen - 1u);
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Pass plan of a test: strata per LDS pass and the replication of the table.
 // ---------------------------------------------------------------------------
@@ -835,6 +999,12 @@ struct Src {
     const uint32_t *gsrc;  // non-null: read the table from here (merged chunks of a split test)
     uint32_t *gdst;        // non-null: add the counted table to here, no G^2
     int64_t s0, s1;        // samples counted (s0 a multiple of 16)
+    // A test of several passes shared by groups: this group's passes are c0,
+    // c0 + cstep, ...; part 1: their statistic only, no decision; 2: the
+    // decision from the sums g2 and dfa of every group's.
+    uint32_t c0 = 0, cstep = 1;
+    int32_t part = 0;
+    double g2 = 0.0, dfa = 0.0;
 };
 
 // Counts, marginals and the G^2 sum of one test over all its passes (G^2 in
@@ -846,7 +1016,8 @@ struct Src {
 // is computed.
 // The statistic is G^2 (stat 0) or X^2 (stat 1); with df_adj the adjusted
 // degrees of freedom of the table are summed into *df_adj.
-template <int kNcMax = kMaxCols>
+// kBits: tests may be counted from bit planes (t.bits > 0: they fit one pass).
+template <int kNcMax = kMaxCols, bool kSearch = false, bool kBits = false>
 BNS_INLINE double table_pass(const Grp &g, TestSh &t, const Plan &P, uint32_t *lds, uint32_t *gtab,
                              const Src &src, bool fp64, const uint32_t **tab_out, int stat,
                              double *df_adj) {
@@ -854,7 +1025,7 @@ BNS_INLINE double table_pass(const Grp &g, TestSh &t, const Plan &P, uint32_t *l
     float part32 = 0.0f;
     const uint32_t *tab = lds;
     const bool chunked = P.nchunks > 1;
-    for (uint32_t c = 0; c < P.nchunks; ++c) {
+    for (uint32_t c = src.c0; c < P.nchunks; c += src.cstep) {
         const uint32_t z0 = c * P.zc_per;
         const uint32_t Zc = min(P.zc_per, P.nstrata - z0);
         const uint32_t Tc = P.rxy * Zc;
@@ -886,9 +1057,15 @@ BNS_INLINE double table_pass(const Grp &g, TestSh &t, const Plan &P, uint32_t *l
             }
             g.sync();
         } else {
-            for (uint32_t i = g.rank; i < head; i += g.size) rep_tab[i] = 0u;
+            int nb = 0;
+            if constexpr (kBits) nb = uni(t.bits);
+            // (samples of the planes' last word past s1)
+            const uint32_t past = nb > 0 ? (uint32_t)(-src.s1) & 31u : 0u;
+            for (uint32_t i = g.rank; i < head; i += g.size) rep_tab[i] = i ? 0u : 0u - past;
             g.sync();
-            if (chunked)
+            if (nb > 0)
+                count_bits(t, nb, rep_tab, logR, src.s0, src.s1, g.rank, g.size);
+            else if (chunked)
                 count_range<true, kNcMax>(t, rep_tab, P.rxy * z0, Tc, Tc, 0, src.s0, src.s1, g.rank, g.size);
             else
                 count_range<false, kNcMax>(t, rep_tab, 0, Tc, 0, logR, src.s0, src.s1, g.rank, g.size);
@@ -912,17 +1089,30 @@ BNS_INLINE double table_pass(const Grp &g, TestSh &t, const Plan &P, uint32_t *l
                 if (v) seen |= __hip_atomic_fetch_add(dst + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             if (seen == ~0u) t.bcast_i[1] = 1;
-            if (c + 1 < P.nchunks) g.sync();
+            if (c + src.cstep < P.nchunks) g.sync();
             continue;
         }
         if (gtab)
             for (uint32_t i = g.rank; i < Tc; i += g.size) gtab[P.rxy * z0 + i] = red[i];
+        if constexpr (kSearch) {
+            if (!fp64 && chunked && P.rx >= 2u && P.rx <= 5u) {
+                double *const dp = df_adj ? &dfp : nullptr;
+                switch (P.rx) {
+                    case 2: strata_partial<2>(g, red, P.ry, Zc, stat, part32, dp); break;
+                    case 3: strata_partial<3>(g, red, P.ry, Zc, stat, part32, dp); break;
+                    case 4: strata_partial<4>(g, red, P.ry, Zc, stat, part32, dp); break;
+                    default: strata_partial<5>(g, red, P.ry, Zc, stat, part32, dp); break;
+                }
+                if (c + src.cstep < P.nchunks) g.sync();
+                continue;
+            }
+        }
         marginals(g, red, rows, cols, strata, P.rx, P.ry, Zc);
         if (fp64) part64 += stat_partial<double>(g, red, rows, cols, strata, P.rx, P.ry, Zc, stat);
         else part32 += stat_partial<float>(g, red, rows, cols, strata, P.rx, P.ry, Zc, stat);
         if (df_adj) dfp += adj_df_partial(g, rows, cols, strata, P.rx, P.ry, Zc);
         tab = red;
-        if (c + 1 < P.nchunks) g.sync();
+        if (c + src.cstep < P.nchunks) g.sync();
     }
     *tab_out = tab;
     if (src.gdst) return 0.0;
@@ -978,7 +1168,7 @@ BNS_INLINE Tail group_tail(const Grp &g, int64_t df, double g2, TestSh &t) {
 // the chunk [s0, s1) is counted and added there; no G^2, no decision).
 // kGeneral: the statistic and df rule come from the tile; otherwise the
 // instance is fixed to G^2 with df from the declared cards.
-template <bool kVerify = false, bool kGeneral = true, int kNcMax = kMaxCols>
+template <bool kVerify = false, bool kGeneral = true, int kNcMax = kMaxCols, bool kSearch = false, bool kBits = false>
 BNS_INLINE TestOut run_test(const Grp &g, TestSh &t, uint32_t *lds, uint32_t W, const Tile &tile,
                             double alpha, uint32_t *gtab, const Src &src) {
     TestOut o;
@@ -988,8 +1178,9 @@ BNS_INLINE TestOut run_test(const Grp &g, TestSh &t, uint32_t *lds, uint32_t W, 
     o.flip = 0;
     const uint32_t lo = lds_offset(lds);
     const uint32_t addr_words = lo < 65536u ? (65536u - lo) / 4u : 0u;
-    const Plan P = make_plan(t, W, src.gsrc ? 0 : tile.max_rep_log2, g.size, src.s1 - src.s0,
-                             addr_words);
+    Plan P = make_plan(t, W, src.gsrc ? 0 : tile.max_rep_log2, g.size, src.s1 - src.s0, addr_words);
+    if constexpr (kBits)
+        if (uni(t.bits) > 0) P.df = uni(t.df);
     o.err = P.err;
     o.df = P.df;
     if (P.err != kDevOk) {
@@ -1008,8 +1199,18 @@ BNS_INLINE TestOut run_test(const Grp &g, TestSh &t, uint32_t *lds, uint32_t W, 
     int64_t df = P.df;
     for (int round = 0; round < 2; ++round) {
         double dfa = 0.0;
-        g2 = table_pass<kNcMax>(g, t, P, lds, round == 0 ? gtab : nullptr, src, fp64, &tab, stat,
-                        adj ? &dfa : nullptr);
+        if (kSearch && round == 0 && src.part == 2) {
+            g2 = src.g2;
+            dfa = src.dfa;
+        } else {
+            g2 = table_pass<kNcMax, kSearch, kBits>(g, t, P, lds, round == 0 ? gtab : nullptr, src, fp64, &tab, stat,
+                                           adj ? &dfa : nullptr);
+        }
+        if (kSearch && src.part == 1) {
+            o.g2 = g2;
+            o.p = dfa;
+            return o;
+        }
         if (src.gdst) {  // merge only: no statistic, no decision
             o.g2 = 0.0;
             o.p = 1.0;
@@ -1046,7 +1247,7 @@ BNS_INLINE TestOut run_test(const Grp &g, TestSh &t, uint32_t *lds, uint32_t W, 
         double g64 = g2, p64 = p;
         if (!fp64 && !(o.flags & 2) && df > 0) {
             if (P.nchunks == 1) g64 = stat_fp64_resident(g, t, P, tab, stat);
-            else g64 = table_pass<kNcMax>(g, t, P, lds, nullptr, src, true, &tab, stat, nullptr);
+            else g64 = table_pass<kNcMax, kSearch, kBits>(g, t, P, lds, nullptr, src, true, &tab, stat, nullptr);
             p64 = group_tail(g, df, g64, t).p;
         }
         o.g2_ref = g64;

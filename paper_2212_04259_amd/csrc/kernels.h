@@ -37,11 +37,15 @@ struct GramProb {
     int64_t plane_item;    // planes: first work item of the problem in k_planes
     int32_t n;             // variables
     int32_t var_off;       // first global variable
+    int64_t rows;          // planes: R and the planes of values
 };
+
+struct VarRec;
 
 struct PairArgs {
     const GramProb *gp;    // per problem
     uint32_t *planes;      // bit planes of every problem (null: the byte form)
+    const VarRec *var;     // per global variable, when planes of values are wanted too (else null)
     const int32_t *oh_var; // one-hot column -> variable of the problem (-1: padding column)
     const uint16_t *oh_cat; // category of the column (low byte); bit 8: the variable has more than 8 categories
     const int32_t *var_oh; // global variable -> its first row of A^T A within its problem
@@ -109,8 +113,14 @@ struct VarRec {
     int32_t card;
     int32_t plane;   // first plane within the problem
     int32_t cat;     // first category within the problem (row of the pairwise tables)
-    int32_t pad;
+    int32_t val;     // first plane of its value (value_planes(card) > 0), the value's bits from the lowest
 };
+
+// Bits that tell a variable's categories apart, and the planes of its value:
+// up to three categories the planes of the categories but the last are such
+// bits already (each sample has at most one set).
+__host__ __device__ inline int card_bits(int r) { int b = 0; while ((1 << b) < r) ++b; return b; }
+__host__ __device__ inline int value_planes(int r) { return r <= 3 ? 0 : card_bits(r); }
 
 struct BitProb {
     const uint32_t *planes;  // the problem's first plane
@@ -196,6 +206,7 @@ struct DepthArgs {
     int32_t edge_form;        // 1: one group per edge runs its tests in order to the first accept
     int32_t xy_policy;        // depth 1: a work unit is one edge's ranks of a level, counted in one pass
                               // sharing the X and Y columns (0 never, 1 always)
+    int32_t deep_depth;       // first depth of the instance whose units share passes (kDeepCells)
     int32_t bits_policy;      // depth 1 from bit planes: a unit is a segment of an edge's ranks
     // Results of a launch, written into pinned host memory by its last kernel.
     Ctl *h_ctl;               // copy of the control block
@@ -235,15 +246,33 @@ hipError_t launch_depth_prepare(const DepthArgs &a, hipStream_t s);   // snapsho
 // units: the instance for the depth's work units: 0 one test, 1 (edge, level)
 // groups (depth 1 with a.xy_policy), 2 one test of at most kNarrowDepth + 2
 // columns (the instance without the wider counting loops, whose registers
-// otherwise spill), 3 units of the bit-plane kernel (launch_depth1_bits); the
+// otherwise spill), 3 units of the bit-plane kernel (launch_depth1_bits), 4 one
+// test counted from bit planes, 5 one test whose passes its units share; the
 // host's choice for a depth must match depth_units().
 hipError_t launch_depth_tests(const DepthArgs &a, int grid, hipStream_t s,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr, int units = 0);
 constexpr int kNarrowDepth = 2;
+// Depths of 2 and more of a search with bit planes count from them where
+// reading bytes bounds the test: with many samples (1,000 x 200,000: depth 2
+// 928 -> 600 us, depth 3 399 -> 310 us).  With fewer a test spends more on its
+// table than on reading, and a table padded to powers of two leaves room for
+// fewer copies of it (220 x 100,000, depth 2: 260 -> 265 us; 64 datasets of
+// 50,000: 1.64 -> 1.80 ms).
+constexpr int64_t kBitSamples = 1 << 17;
+// Deep depths, from the one at which a table of variables of the mean
+// cardinality has kDeepCells cells (a workgroup's LDS holds about 6,500 with
+// their marginals): tests are few and many of their tables larger than the
+// LDS, so that a test has several units, which share its passes (220 x 100,000
+// of up to five categories: 168 tests of depth 5 503 -> 196 us, 252 of depth 6
+// 761 -> 379 us).  A test of one pass pays 3 - 8 us for that instance's
+// registers and cold code (depth 5 of 61 x 49,993), so it starts here.
+constexpr double kDeepCells = 4096.0;
 // Work units of depth d (the rule the depth preparation applies).
 inline int depth_units(const DepthArgs &a, int d) {
     if (a.edge_form || a.err_val) return 0;
     if (a.bits_policy && d == 1) return 3;
+    if (d >= a.deep_depth) return 5;
+    if (a.bits_policy && d > 1 && a.m_max >= kBitSamples) return 4;
     if (a.xy_policy == 1 && d == 1 && a.round_width == 0) return 1;
     if (d <= kNarrowDepth && a.tile.stat == 0 && a.tile.df_rule == 0) return 2;
     return 0;

@@ -835,6 +835,7 @@ struct Desc {
     int32_t valid;
     int32_t ncols;
     uint32_t xyk;            // (edge, level) units: ranks r .. r + xyk - 1 of the edge
+    int32_t var_off;         // first global variable of the problem
     uint16_t var[kMaxCols];  // variable ids (n <= 65535)
     uint8_t card[kMaxCols];
 };
@@ -919,6 +920,7 @@ BNS_INLINE void decode_edge_rank(const DepthArgs &A, int64_t e, unsigned long lo
     q.r = r;
     q.e = e;
     q.prob = rec.prob;
+    q.var_off = P.var_off;
     q.ncols = d + 2;
     q.var[0] = (uint16_t)rec.i;
     q.var[1] = (uint16_t)rec.j;
@@ -978,6 +980,53 @@ BNS_INLINE void stage_test(const Grp &g, const Desc &q, TestSh &t) {
     g.sync();
 }
 
+// The same for a search with bit planes: the test is staged to be counted
+// from them when its table, a cell per value of its bits, fits W words with
+// its marginals (one pass).  A table padded to powers of two gives the same
+// statistic: the cells of categories that are not there are 0 in rows, columns
+// or strata that are 0, which add nothing.
+BNS_INLINE void stage_test_bits(const Grp &g, const Desc &q, TestSh &t, const DepthArgs &A, uint32_t W) {
+    if (g.rank < 64) {
+        const int k = g.rank, nc = uni(q.ncols);
+        VarRec v{1, 0, 0, 0};
+        if (k < nc) v = A.bits.var[q.var_off + q.var[k]];
+        const BitProb &bp = A.bits.prob[uni(q.prob)];
+        const int b = (v.card > 1) + (v.card > 2) + (v.card > 4);
+        static_assert(kBitCards <= 8, "at most three bits per variable");
+        const uint64_t one = __ballot(b & 1), two = __ballot(b & 2), below = lanes_below_mask();
+        const int pre = __popcll(one & below) + 2 * __popcll(two & below);
+        const int nb = __popcll(one) + 2 * __popcll(two);
+        const uint32_t bx = __shfl(b, 0, 64), by = __shfl(b, 1, 64);
+        const uint64_t need = (1ull << nb) + ((uint64_t)((1u << bx) + (1u << by) + 1u) << (nb - (int)(bx + by)));
+        const bool fits = nb >= kMinPlaneBits && nb <= kMaxPlaneBits && need <= W;
+        if (fits) {
+            const uint8_t *planes = (const uint8_t *)bp.planes;
+            const uint64_t step = bp.plane_bytes;
+            const uint8_t *first = planes + step * (uint64_t)(v.card <= 3 ? v.plane : v.val);
+            for (int j = 0; j < b; ++j) t.col[pre + j] = first + step * (uint64_t)j;
+            if (k < nc) t.card[k] = 1u << b;
+            int64_t df = v.card - (k < 2 ? 1 : 0);  // (lanes past the columns: 1)
+#pragma unroll
+            for (int off = 1; off < 32; off <<= 1) df *= __shfl_xor((int)df, off, 64);
+            if (k == 0) t.df = df;
+        } else if (k < nc) {
+            t.col[k] = q.data + (int64_t)q.var[k] * q.ld;
+            t.card[k] = q.card[k];
+        }
+        if (k == 0) {
+            t.bits = fits ? nb : 0;
+            t.ncols = nc;
+            t.m = q.m;
+            uint32_t mlt = 1;
+            for (int c = 0; c < nc && !fits; ++c) {
+                t.mult[c] = mlt;
+                mlt *= q.card[c];
+            }
+        }
+    }
+    g.sync();
+}
+
 BNS_INLINE unsigned long long bcast_u64(unsigned long long v) {
     const unsigned lo = __shfl((unsigned)(v & 0xffffffffull), 0, 64);
     const unsigned hi = __shfl((unsigned)(v >> 32), 0, 64);
@@ -989,6 +1038,18 @@ BNS_INLINE uint64_t table_cells(const TestSh &t) {
     uint64_t T = 1;
     for (int k = 0; k < t.ncols && T <= 0xffffffffull; ++k) T *= t.card[k];
     return T;
+}
+
+// Passes of the test staged in t with W words and S lanes (as make_plan's; 1
+// also for a table that no number of passes holds).
+BNS_INLINE uint32_t test_passes(const TestSh &t, uint32_t W, int S) {
+    const uint64_t T = table_cells(t);
+    const uint32_t rx = uni(t.card[0]), ry = uni(t.card[1]), rxy = rx * ry;
+    if (T > kMaxCells || W <= (uint32_t)S) return 1u;
+    const uint32_t ns = (uint32_t)uni(T) / rxy, per = rxy + rx + ry + 1u;
+    if ((uint64_t)ns * per <= W) return 1u;
+    const uint32_t zc = (W - (uint32_t)S) / per;
+    return zc ? (ns + zc - 1u) / zc : 1u;
 }
 
 // ---------------------------------------------------------------------------
@@ -1387,6 +1448,9 @@ struct Batch {
 // a separate instance keeps that path's registers out of the per-test one (0).
 // 2: the per-test instance for depths up to kNarrowDepth (tests of at most
 // four columns), without the wider counting loops (fewer spilled registers).
+// 4: the per-test instance that counts from bit planes (those the planes fit);
+// 5: the per-test instance of deep depths, whose units share the passes of
+// tests with tables larger than the LDS.
 template <int LGB, bool VERIFY, bool GENERAL, int UNITS = 0>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_depth_tests(DepthArgs A) {
     extern __shared__ uint32_t lds[];
@@ -1402,6 +1466,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     // per-group tallies (kept in LDS: no vector registers across tests)
     __shared__ unsigned long long tal_exec[kWaves], tal_re[kWaves];
     __shared__ double tal_bytes[kWaves];
+    constexpr bool BITS = UNITS == 4, SHARE = UNITS == 5;
     Ctl *c = A.ctl;
     const unsigned long long t_enter = wall_clock64();
     // Everything the workgroup needs from the control block and the search
@@ -1451,7 +1516,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     const long long Lc = uni(hdr.Lc);
     const uint64_t cap = uni(hdr.cap);
     const int mode = uni(hdr.mode);
-    if (uni(hdr.xy) != (UNITS == 1 ? 1 : 0) || (UNITS == 2 && d > kNarrowDepth)) {
+    if (uni(hdr.xy) != (UNITS == 1 ? 1 : 0) || (UNITS == 2 && d > kNarrowDepth) || (BITS && !A.bits.prob)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) c->error = kDevUnitMismatch;
         return;
     }
@@ -1546,7 +1611,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
             if (chk)
                 ma_next = __hip_atomic_load(&A.min_accept[mine[j + 1].e], __ATOMIC_RELAXED,
                                             __HIP_MEMORY_SCOPE_AGENT);
-            stage_test(g, q, t);
+            if constexpr (BITS) stage_test_bits(g, q, t, A, W);
+            else stage_test(g, q, t);
             const int64_t qm = uni(q.m);
             // Split depths: unit (ticket, chunk) counts its chunk of samples
             // into the ticket's merge table; the group that merges the last
@@ -1555,11 +1621,28 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
             Src src{nullptr, nullptr, 0, qm};
             uint32_t *gt = nullptr;
             uint32_t nch = 1;
+            unsigned long long *parts = nullptr;  // partial statistics of a test whose passes are shared
             if (C > 1) {
                 const int chunk = uni(q.chunk);
                 const int64_t s0 = (int64_t)chunk * Lc;
                 nch = (uint32_t)((qm + Lc - 1) / Lc);
-                if (nch > 1 && table_cells(t) <= cap) {
+                const uint32_t np = SHARE ? test_passes(t, W, g.size) : 1u;
+                if (np > 2) {
+                    // a table of several passes: its units take passes, not
+                    // chunks of samples, which would all go through every
+                    // pass and merge a table larger than the LDS (with two
+                    // passes the shorter counts of chunks make up for that)
+                    nch = min((uint32_t)C, np);
+                    if (4ull * (uint64_t)nch > cap) nch = 1;
+                    if ((uint32_t)chunk >= nch) continue;
+                    if (nch > 1) {
+                        gt = A.split_tab + uni(q.tk) * cap;
+                        parts = (unsigned long long *)gt;
+                        src.c0 = (uint32_t)chunk;
+                        src.cstep = nch;
+                        src.part = 1;
+                    }
+                } else if (nch > 1 && table_cells(t) <= cap) {
                     if (s0 >= qm) continue;
                     gt = A.split_tab + uni(q.tk) * cap;
                     src.gdst = gt;
@@ -1570,9 +1653,47 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
                 }
             }
             for (;;) {
-                const TestOut o = run_test<VERIFY, GENERAL, UNITS == 2 ? kNarrowDepth + 2 : kMaxCols>(
+                const TestOut o = run_test<VERIFY, GENERAL, UNITS == 2 || BITS || SHARE ? kNarrowDepth + 2 : kMaxCols, SHARE, BITS>(
                     g, t, region, W, A.tile, uni(q.alpha), nullptr, src);
-                if (g.rank == 0) tal_bytes[ti] += (double)q.ncols * (double)(src.s1 - src.s0);
+                if (g.rank == 0 && !(src.part == 1 && src.c0 > 0) && src.part != 2)
+                    tal_bytes[ti] += (double)q.ncols * (double)(src.s1 - src.s0);
+                if (SHARE && src.part == 1) {
+                    // Partial sums in agent-scope atomics, by the protocol of
+                    // the merge tables below: rank 0's stores come before its
+                    // release of the counter; the group that counts the last
+                    // pass adds them in the order of the passes.
+                    const uint32_t at = 2u * (uint32_t)src.c0;
+                    uint32_t prev = 0;
+                    if (g.rank == 0) {
+                        __hip_atomic_store(parts + at, __builtin_bit_cast(unsigned long long, o.g2), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_store(parts + at + 1, __builtin_bit_cast(unsigned long long, o.p), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                        prev = __hip_atomic_fetch_add(&A.split_cnt[q.tk], 1u, __ATOMIC_ACQ_REL,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    prev = g.bcast(prev, t);
+                    if (prev + 1 != nch) break;
+                    if (g.rank == 0)
+                        __hip_atomic_store(&A.split_cnt[q.tk], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    double sg = 0.0, sd = 0.0;
+                    for (uint32_t k = 0; k < nch; ++k) {
+                        sg += __builtin_bit_cast(double, __hip_atomic_load(parts + 2 * k, __ATOMIC_RELAXED,
+                                                                           __HIP_MEMORY_SCOPE_AGENT));
+                        sd += __builtin_bit_cast(double, __hip_atomic_load(parts + 2 * k + 1, __ATOMIC_RELAXED,
+                                                                           __HIP_MEMORY_SCOPE_AGENT));
+                    }
+                    g.sync();
+                    // (zero again, as every merge table is between tests)
+                    for (uint32_t k = g.rank; k < 2 * nch; k += g.size)
+                        __hip_atomic_store(parts + k, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    src.c0 = 0;
+                    src.cstep = 1;
+                    src.part = 2;
+                    src.g2 = sg;
+                    src.dfa = sd;
+                    continue;
+                }
                 if (src.gdst) {
                     // Every access to a merge table and its chunk counter is
                     // an agent-scope atomic, so each word has one order of
@@ -2112,6 +2233,14 @@ static auto depth_tests_kernel(const DepthArgs &a, int units) -> decltype(&k_dep
         if (general) return &k_depth_tests<0, false, true, 1>;
         return a.grab_block_log2 ? &k_depth_tests<kGrabRunLog2, false, false, 1> : &k_depth_tests<0, false, false, 1>;
     }
+    if (units == 4) {
+        if (general) return &k_depth_tests<0, false, true, 4>;
+        return a.grab_block_log2 ? &k_depth_tests<kGrabRunLog2, false, false, 4> : &k_depth_tests<0, false, false, 4>;
+    }
+    if (units == 5) {
+        if (general) return &k_depth_tests<0, false, true, 5>;
+        return a.grab_block_log2 ? &k_depth_tests<kGrabRunLog2, false, false, 5> : &k_depth_tests<0, false, false, 5>;
+    }
     if (units == 2 && !general && !a.err_val)
         return a.grab_block_log2 ? &k_depth_tests<kGrabRunLog2, false, false, 2> : &k_depth_tests<0, false, false, 2>;
     // verification and other statistics: single-ticket dealing (the dealing
@@ -2123,7 +2252,7 @@ static auto depth_tests_kernel(const DepthArgs &a, int units) -> decltype(&k_dep
 
 hipError_t launch_depth_tests(const DepthArgs &a, int grid, hipStream_t s, hipEvent_t start,
                               hipEvent_t stop, int units) {
-    if (units == 3) return launch_depth1_bits(a, s, start, stop);
+    if (units == 3) return launch_depth1_bits(a, s, start, stop);  // (4: the test kernel from bit planes)
     auto kern = depth_tests_kernel(a, units);
     if (a.edge_form) kern = (a.tile.stat != 0 || a.tile.df_rule != 0) ? &k_depth_edges<true> : &k_depth_edges<false>;
     if (start && stop)
@@ -2148,6 +2277,12 @@ hipError_t allow_dynamic_lds(int bytes) {
                          (const void *)k_depth_tests<0, false, true, 1>,
                          (const void *)k_depth_tests<0, false, false, 2>,
                          (const void *)k_depth_tests<kGrabRunLog2, false, false, 2>,
+                         (const void *)k_depth_tests<0, false, false, 4>,
+                         (const void *)k_depth_tests<kGrabRunLog2, false, false, 4>,
+                         (const void *)k_depth_tests<0, false, true, 4>,
+                         (const void *)k_depth_tests<0, false, false, 5>,
+                         (const void *)k_depth_tests<kGrabRunLog2, false, false, 5>,
+                         (const void *)k_depth_tests<0, false, true, 5>,
                          (const void *)k_depth_edges<false>, (const void *)k_depth_edges<true>};
     hipError_t e = hipSuccess;
     for (const void *f : fns)

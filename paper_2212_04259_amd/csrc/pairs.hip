@@ -94,7 +94,8 @@ BNS_INLINE GramItem gram_item(const PairArgs &P, int64_t item) {
 // (89 us with the wave compares).  Bits of samples past m are 0.
 // ---------------------------------------------------------------------------
 template <int NB>
-BNS_INLINE void plane_words(const u32x4 (&x)[2], uint32_t valid, int r, uint32_t *out, int64_t stride) {
+BNS_INLINE void plane_words(const u32x4 (&x)[2], uint32_t valid, int r, uint32_t *out, uint32_t *val,
+                            int64_t stride) {
     uint32_t bit[NB];
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
@@ -112,6 +113,8 @@ BNS_INLINE void plane_words(const u32x4 (&x)[2], uint32_t valid, int r, uint32_t
         for (int k = 0; k < NB; ++k) wd &= ((cat >> k) & 1) ? bit[k] : ~bit[k];
         out[(int64_t)cat * stride] = wd;
     }
+    if (val)
+        for (int k = 0; k < NB && (1 << k) < r; ++k) val[(int64_t)k * stride] = bit[k] & valid;
 }
 
 // reset: the kernel is the first of a search (depths 0 and 1 from bit planes)
@@ -159,6 +162,8 @@ __global__ __launch_bounds__(kWG) void k_planes(PairArgs P, const uint8_t *cards
             }
         }
         uint32_t *out = P.planes + uni(gp.plane_off) + (int64_t)uni(P.var_oh[g]) * stride;
+        uint32_t *val = P.var && value_planes(r) > 0 ? P.planes + uni(gp.plane_off) + (int64_t)uni(P.var[g].val) * stride
+                                                     : nullptr;
 #pragma unroll
         for (int u = 0; u < kPlaneItem; ++u) {
             const int64_t wi = w0 + 64 * u;
@@ -169,10 +174,10 @@ __global__ __launch_bounds__(kWG) void k_planes(PairArgs P, const uint8_t *cards
                 valid = 0u;
                 for (int i = 0; i < (int)left; ++i) valid |= 1u << (8 * (i & 3) + (i >> 2));
             }
-            if (r <= 2) plane_words<1>(x[u], valid, r, out + wi, stride);
-            else if (r <= 4) plane_words<2>(x[u], valid, r, out + wi, stride);
-            else if (r <= 8) plane_words<3>(x[u], valid, r, out + wi, stride);
-            else plane_words<8>(x[u], valid, r, out + wi, stride);
+            if (r <= 2) plane_words<1>(x[u], valid, r, out + wi, nullptr, stride);
+            else if (r <= 4) plane_words<2>(x[u], valid, r, out + wi, val ? val + wi : nullptr, stride);
+            else if (r <= 8) plane_words<3>(x[u], valid, r, out + wi, val ? val + wi : nullptr, stride);
+            else plane_words<8>(x[u], valid, r, out + wi, val ? val + wi : nullptr, stride);
         }
     }
 }
