@@ -965,16 +965,12 @@ BNS_INLINE Plan make_plan(const TestSh &t, uint32_t W, int max_rep_log2, int S, 
     if ((uint64_t)P.T + marg <= W) {
         P.zc_per = P.nstrata;
         P.nchunks = 1;
-        // Replicate while the replicated table fits next to the reduced one
-        // and the zero/reduce work stays small against the increments.
-        const int64_t m = msamp;
-        while (P.logR < max_rep_log2) {
-            const uint64_t R2 = 2ull << P.logR;
-            if ((uint64_t)P.T * R2 + P.T + marg > W) break;
-            if ((uint64_t)P.T * R2 > addr_words) break;
-            if ((int64_t)(P.T * R2) * 4 > m + 16 * S) break;
-            ++P.logR;
-        }
+        // The most copies (a power of two) that fit next to the reduced table,
+        // while the zero/reduce work stays small against the increments.
+        const uint64_t per_cell = (uint64_t)(msamp + 16 * S) >> 2;
+        const uint32_t words = (uint32_t)min(per_cell, (uint64_t)min(W - P.T - marg, addr_words));
+        const uint32_t copies = words / P.T;
+        if (copies > 1u) P.logR = min(31 - __clz((int)copies), max_rep_log2);
     } else {
         // Passes over z ranges; S spill words follow the counted cells.
         uint32_t zc = (W > (uint32_t)S) ? (W - (uint32_t)S) / per_stratum : 0;
@@ -987,6 +983,14 @@ BNS_INLINE Plan make_plan(const TestSh &t, uint32_t W, int max_rep_log2, int S, 
         P.nchunks = (P.nstrata + zc - 1) / zc;
     }
     return P;
+}
+
+// Clears n LDS words at a 16-byte boundary (a group's share of the LDS), 16
+// bytes per lane and step, up to three words past n too (the marginals follow,
+// written later); first: the value of word 0.
+BNS_INLINE void clear_words(uint32_t *p, uint32_t n, uint32_t first, int rank, int S) {
+    u32x4 *q = (u32x4 *)p;
+    for (uint32_t i = rank; i < (n + 3u) >> 2; i += S) q[i] = u32x4{i ? 0u : first, 0u, 0u, 0u};
 }
 
 // Reads a counter that other workgroups updated with device-scope atomics.
@@ -1061,7 +1065,7 @@ BNS_INLINE double table_pass(const Grp &g, TestSh &t, const Plan &P, uint32_t *l
             if constexpr (kBits) nb = uni(t.bits);
             // (samples of the planes' last word past s1)
             const uint32_t past = nb > 0 ? (uint32_t)(-src.s1) & 31u : 0u;
-            for (uint32_t i = g.rank; i < head; i += g.size) rep_tab[i] = i ? 0u : 0u - past;
+            clear_words(rep_tab, head, 0u - past, g.rank, g.size);
             g.sync();
             if (nb > 0)
                 count_bits(t, nb, rep_tab, logR, src.s0, src.s1, g.rank, g.size);

@@ -50,6 +50,10 @@ __device__ inline void unrank_serial(const Binom &B, int64_t p, int d, uint64_t 
     int64_t x0 = 0;
     for (int k = 0; k < d; ++k) {
         const int j = d - k - 1;
+        if (j == 0) {  // S(x) = x - x0
+            c[k] = (int32_t)(x0 + (int64_t)rr);
+            return;
+        }
         const uint64_t base = B.at(p - x0, j + 1);
         int64_t lo = x0, hi = p - j - 1;
         while (lo < hi) {
@@ -858,6 +862,10 @@ BNS_INLINE void unrank_lane(const uint64_t *tab, int stride, int rows, int64_t p
     int64_t x0 = 0;
     for (int k = 0; k < d; ++k) {
         const int j = d - k - 1;
+        if (j == 0) {  // S(x) = x - x0
+            out[k] = (uint16_t)(x0 + (int64_t)rr);
+            return;
+        }
         const uint64_t base = bnm(tab, stride, rows, p - x0, j + 1);
         // largest x in [x0, p - j - 1] with S(x) <= rr, by bisection
         int64_t lo = x0, hi = p - j - 1;
@@ -964,17 +972,23 @@ BNS_INLINE void decode_edge_rank(const DepthArgs &A, int64_t e, unsigned long lo
 
 // Stages a decoded test into the group's TestSh (all lanes of the group).
 BNS_INLINE void stage_test(const Grp &g, const Desc &q, TestSh &t) {
-    for (int k = g.rank; k < q.ncols; k += g.size) {
-        t.col[k] = q.data + (int64_t)q.var[k] * q.ld;
-        t.card[k] = q.card[k];
-    }
-    if (g.rank == 0) {
-        t.ncols = q.ncols;
-        t.m = q.m;
-        uint32_t mlt = 1;
-        for (int k = 0; k < q.ncols; ++k) {
-            t.mult[k] = mlt;
-            mlt *= q.card[k];
+    static_assert(kMaxCols <= 64, "a lane per column");
+    if (g.rank < 64) {
+        const int k = g.rank, nc = uni(q.ncols);
+        const uint32_t r = k < nc ? q.card[k] : 1u;
+        uint32_t mlt = 1, mine = 1;  // (the strides' product from lane to lane, not through LDS)
+        for (int j = 0; j < nc; ++j) {
+            mine = k == j ? mlt : mine;
+            mlt *= (uint32_t)__builtin_amdgcn_readlane((int)r, j);
+        }
+        if (k < nc) {
+            t.col[k] = q.data + (int64_t)q.var[k] * q.ld;
+            t.card[k] = r;
+            t.mult[k] = mine;
+        }
+        if (k == 0) {
+            t.ncols = nc;
+            t.m = q.m;
         }
     }
     g.sync();
@@ -1453,7 +1467,7 @@ struct Batch {
 // tests with tables larger than the LDS.
 template <int LGB, bool VERIFY, bool GENERAL, int UNITS = 0>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_depth_tests(DepthArgs A) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     __shared__ TestSh tsh[kWaves];
     __shared__ Desc slots[kWaves * kSlotsPerWave];
     __shared__ unsigned long long lvl_base[kMaxLevels + 1];
@@ -1822,7 +1836,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
 // ---------------------------------------------------------------------------
 template <bool GENERAL>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_depth_edges(DepthArgs A) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     __shared__ TestSh tsh[kWaves];
     __shared__ Desc slots[kWaves];
     __shared__ uint64_t btab_lds[kBinomLds];
@@ -2344,7 +2358,7 @@ __global__ __launch_bounds__(kWG) void k_ci_batch(const uint8_t *data, int64_t l
                                                   double alpha, Tile tile, CiOutDev *out,
                                                   CiOutSoa soa, uint32_t *tables,
                                                   const int64_t *table_off, CiDone done) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     __shared__ TestSh tsh[kWaves];
     const int w = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
@@ -2451,7 +2465,7 @@ __global__ __launch_bounds__(kWG) void k_plain_count(const uint8_t *data, int64_
                                                      const uint8_t *cards, const PlainTest pt,
                                                      int64_t spb, uint32_t *partials, int64_t T,
                                                      int lds_words) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     __shared__ TestSh t;
     fill_plain(t, data, ld, m, cards, pt);
     const int64_t s0 = (int64_t)blockIdx.x * spb;
