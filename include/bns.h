@@ -264,16 +264,15 @@ bns_status bns_ci_batch(const bns_dataset *ds, const bns_ci_test *tests, int64_t
  * the library holds on each device it runs on until the process ends (calls
  * of up to 1 MiB in a pinned area made with the process's first dataset on
  * the device, likewise held), instead of library-allocated buffers; no
- * hipMalloc, hipFree or pinned host
- * allocation happens in the call.  Same arguments, checks, kernels and results
- * as bns_ci_batch (all pointers are host pointers; outputs may be NULL), minus
+ * hipMalloc, hipFree or pinned host allocation happens in the call.  Same
+ * arguments, checks, kernels and results as bns_ci_batch (all pointers are host pointers; outputs may be NULL), minus
  * the table output.  A call needs 16 n_tests + 4 z_pool_len + 28 n_tests bytes
  * of scratch (each section rounded up to 256 bytes); a larger one fails with
  * BNS_E_NOMEM before any device work.  Calls are synchronous (the stream of
  * opt->stream, NULL = the null stream, has run the call's work and all work
- * before it when the call returns) and the library serialises calls per device, so they never overlap on a device
- * within a process; overlapping calls would race on the shared scratch area,
- * which keeps the last call's contents.  The dataset must have been created
+ * before it when the call returns) and the library serialises calls per
+ * device, so they never overlap on a device within a process; overlapping
+ * calls would race on the shared scratch area, which keeps the last call's contents.  The dataset must have been created
  * beforehand (that allocates). */
 #define BNS_NOALLOC_SCRATCH_BYTES (16 << 20)
 bns_status bns_ci_batch_noalloc(const bns_dataset *ds, const bns_ci_test *tests, int64_t n_tests,

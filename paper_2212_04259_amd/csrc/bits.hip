@@ -662,7 +662,7 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
     const int64_t tile_words = (int64_t)kGramT * kGramT;
     auto entry = [&](int a, int b) {
         int off;
-        const int64_t t = gram_tile(gp, kGramT, a, b, &off);
+        const int64_t t = gram_tile(gp, a, b, &off);
         return PA.part + (gp.item_base + t * nch) * tile_words + off;
     };
     if (tid == 0) removed_sh = 0u;

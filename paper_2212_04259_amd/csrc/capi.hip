@@ -784,11 +784,17 @@ static const int64_t kBitTableWords = 256ll << 20;
 // each; beyond, the depth runs in the test kernel).
 static const int64_t kTriItemsMax = 16384;
 
+// Samples from which the contraction is worth a pass that makes bit planes of
+// the columns first (all pairs of 150 x 5,000: 132 us from bytes, 117 from
+// planes; 60 x 2,000: 97 and 133; 1,000 x 2,000: 910 and 933).
+static const int64_t kPlaneSamples = 4096;
+
 // planes: bit planes wanted; they are used when they take no more memory than
-// the columns (a mean cardinality of at most 9) or than 64 MiB.  values: planes
-// of values after those of each problem (see value_planes).
+// the columns (a mean cardinality of at most 9) or than 64 MiB, and (bits: always, the
+// search's depth 1 needs them) from kPlaneSamples samples on.  values: planes of
+// values after those of each problem (see value_planes).
 static bns_status plan_pairs(const DevCtx &dc, const bns_dataset *const *ds, int32_t P, bool planes, PairPlan &pp,
-                             bool values = false) {
+                             bool bits = false, bool values = false) {
     pp = PairPlan();
     const int64_t T = kGramT;
     int64_t m_max = 1, plane_bytes = 0;
@@ -799,7 +805,8 @@ static bns_status plan_pairs(const DevCtx &dc, const bns_dataset *const *ds, int
         for (uint8_t c : ds[k]->cards) plane_bytes += (c - 1) * blocks * (kPlaneBlock / 8);
         col_bytes += (double)ds[k]->n * (double)ds[k]->m;
     }
-    pp.planes = planes && (double)plane_bytes <= std::max(col_bytes, 64.0 * 1048576.0);
+    pp.planes = planes && (bits || m_max >= kPlaneSamples) &&
+                (double)plane_bytes <= std::max(col_bytes, 64.0 * 1048576.0);
     // 64 x 64 tiles.  Bytes: a workgroup's LDS (two steps of 2 x 64 one-hot
     // columns) leaves room for more workgroups per CU than 128 x 128 tiles
     // do, which the expansion and LDS traffic need more than the larger
@@ -1432,7 +1439,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
         bits = level == 0;
         pp = PairPlan();
         if (bits || want_pairs) {
-            st = plan_pairs(dc, ds, P, level < 2, pp, bits && values_want);
+            st = plan_pairs(dc, ds, P, level < 2, pp, bits, bits && values_want);
             if (bits && (st != BNS_OK || !pp.planes)) continue;
             if (st != BNS_OK && o.depth0 == BNS_DEPTH0_PAIRS) return st;
         }

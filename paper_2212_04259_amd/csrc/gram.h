@@ -45,7 +45,8 @@ BNS_INLINE u32x4 onehot16(u32x4 w, uint32_t plo, uint32_t phi, uint32_t cat, boo
 }
 
 // Word of entry (a, b), a <= b, of a problem's tiles: tile and offset in it.
-BNS_INLINE int64_t gram_tile(const GramProb &gp, int T, int a, int b, int *off) {
+BNS_INLINE int64_t gram_tile(const GramProb &gp, int a, int b, int *off) {
+    constexpr int T = kGramT;  // (a power of two: an entry costs no divisions)
     const int ta = a / T, tb = b / T;
     *off = (a - ta * T) * T + (b - tb * T);
     return (int64_t)ta * gp.nb - (int64_t)ta * (ta - 1) / 2 + (tb - ta);
@@ -53,10 +54,9 @@ BNS_INLINE int64_t gram_tile(const GramProb &gp, int T, int a, int b, int *off) 
 
 // Entry (a, b), a <= b, of a problem's Gram matrix.
 BNS_INLINE uint32_t gram_entry(const PairArgs &P, const GramProb &gp, int a, int b) {
-    const int T = P.T;
     int off;
-    const int64_t ti = gram_tile(gp, T, a, b, &off);
-    return (uint32_t)P.gram[(gp.tile_base + ti) * (int64_t)T * T + off];
+    const int64_t ti = gram_tile(gp, a, b, &off);
+    return (uint32_t)P.gram[(gp.tile_base + ti) * (int64_t)(kGramT * kGramT) + off];
 }
 
 }  // namespace bns

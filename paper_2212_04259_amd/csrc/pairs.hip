@@ -450,78 +450,75 @@ BNS_INLINE void pair_terms(int ri, int rj, int64_t m, int stat_kind, bool adj, d
 // oi and oj (oi < oj).  The diagonal entries are the category counts.  With
 // planes only the cells of neither variable's last category are entries; the
 // last column is what the other columns leave of N_x+, the last row what the
-// other rows leave of N_+y.  Up to kRegCats categories (the usual networks)
-// the table is completed in registers.
-constexpr int kRegCats = 5;
+// other rows leave of N_+y.  Up to kPairCats categories (the usual networks) the
+// table is completed in the lane's column of `cell` (kPairCats^2 words,
+// kPairWG apart): the loads of four rows are in flight together, and one copy
+// of the term's code serves every cell.  (25 cells unrolled in registers were
+// 20 KB of code, which a call of a few hundred pairs spent longer fetching
+// than on its tests: all pairs of 20 x 100,000 of up to six categories 184 us
+// a call with them, 141 with this; of 300 x 50,000 239 and 214.)
+constexpr int kPairCats = 8;
+constexpr int kPairWG = 64;
 
 BNS_INLINE void pair_stat(const PairArgs &P, const GramProb &gp, int oi, int oj, int ri, int rj, int64_t m,
-                          int stat_kind, bool adj, double &stat, int64_t &df) {
+                          int stat_kind, bool adj, double &stat, int64_t &df, uint32_t *cell) {
+    // categories that have entries
+    const int pi = P.planes ? ri - 1 : ri, pj = P.planes ? rj - 1 : rj;
+    if (ri <= kPairCats && rj <= kPairCats) {
+        auto at = [&](int x, int y) -> uint32_t & { return cell[(x * kPairCats + y) * kPairWG]; };
+        uint32_t ni[kPairCats], nj[kPairCats], li = (uint32_t)m, lj = (uint32_t)m;
+#pragma unroll
+        for (int x = 0; x < kPairCats; ++x) ni[x] = x < pi ? gram_entry(P, gp, oi + x, oi + x) : 0u;
+#pragma unroll
+        for (int y = 0; y < kPairCats; ++y) nj[y] = y < pj ? gram_entry(P, gp, oj + y, oj + y) : 0u;
+        for (int x0 = 0; x0 < pi; x0 += 4) {
+            uint32_t v[4][kPairCats];
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int y = 0; y < kPairCats; ++y)
+                    v[x][y] = x0 + x < pi && y < pj ? gram_entry(P, gp, oi + x0 + x, oj + y) : 0u;
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int y = 0; y < kPairCats; ++y)
+                    if (x0 + x < pi && y < pj) at(x0 + x, y) = v[x][y];
+        }
+#pragma unroll
+        for (int x = 0; x < kPairCats; ++x) li -= ni[x];
+#pragma unroll
+        for (int y = 0; y < kPairCats; ++y) lj -= nj[y];
+        // counts of a category (registers are not indexed: eight selects)
+        auto pick = [](const uint32_t (&n)[kPairCats], int k, int last, uint32_t rest) {
+            uint32_t r = rest;
+#pragma unroll
+            for (int q = 0; q < kPairCats; ++q)
+                if (q == k && k < last) r = n[q];
+            return r;
+        };
+        uint32_t left_row = 0;
+        pair_terms(ri, rj, m, stat_kind, adj, stat, df,
+                   [&](int x, int y) {
+                       if (y == 0) left_row = pick(ni, x, pi, li);
+                       uint32_t N;
+                       if (y == pj) {
+                           N = left_row;
+                       } else if (x < pi) {
+                           N = at(x, y);
+                       } else {
+                           N = pick(nj, y, pj, lj);
+                           for (int a = 0; a < pi; ++a) N -= at(a, y);
+                       }
+                       left_row -= N;
+                       return N;
+                   },
+                   [&](int x) { return pick(ni, x, pi, li); }, [&](int y) { return pick(nj, y, pj, lj); });
+        return;
+    }
     if (!P.planes) {
         pair_terms(ri, rj, m, stat_kind, adj, stat, df, [&](int x, int y) { return gram_entry(P, gp, oi + x, oj + y); },
                    [&](int x) { return gram_entry(P, gp, oi + x, oi + x); },
                    [&](int y) { return gram_entry(P, gp, oj + y, oj + y); });
-        return;
-    }
-    const int pi = ri - 1, pj = rj - 1;
-    if (ri <= kRegCats && rj <= kRegCats) {
-        // every entry loaded once, all loads in flight together
-        uint32_t N[kRegCats][kRegCats], ni[kRegCats], nj[kRegCats];
-#pragma unroll
-        for (int x = 0; x < kRegCats; ++x)
-#pragma unroll
-            for (int y = 0; y < kRegCats; ++y)
-                N[x][y] = (x < pi && y < pj) ? gram_entry(P, gp, oi + x, oj + y) : 0u;
-#pragma unroll
-        for (int x = 0; x < kRegCats; ++x) ni[x] = x < pi ? gram_entry(P, gp, oi + x, oi + x) : 0u;
-#pragma unroll
-        for (int y = 0; y < kRegCats; ++y) nj[y] = y < pj ? gram_entry(P, gp, oj + y, oj + y) : 0u;
-        // counts of the last categories, then the last column and row
-        uint32_t li = (uint32_t)m, lj = (uint32_t)m;
-#pragma unroll
-        for (int x = 0; x < kRegCats; ++x) li -= ni[x];
-#pragma unroll
-        for (int y = 0; y < kRegCats; ++y) lj -= nj[y];
-#pragma unroll
-        for (int x = 0; x < kRegCats; ++x)
-            if (x == pi) ni[x] = li;
-#pragma unroll
-        for (int y = 0; y < kRegCats; ++y)
-            if (y == pj) nj[y] = lj;
-#pragma unroll
-        for (int x = 0; x < kRegCats; ++x) {
-            uint32_t rest = ni[x];
-#pragma unroll
-            for (int y = 0; y < kRegCats; ++y) rest -= N[x][y];
-#pragma unroll
-            for (int y = 0; y < kRegCats; ++y)
-                if (y == pj && x < pi) N[x][y] = rest;
-        }
-#pragma unroll
-        for (int y = 0; y < kRegCats; ++y) {
-            uint32_t rest = nj[y];
-#pragma unroll
-            for (int x = 0; x < kRegCats; ++x) rest -= x < pi ? N[x][y] : 0u;
-#pragma unroll
-            for (int x = 0; x < kRegCats; ++x)
-                if (x == pi && y <= pj) N[x][y] = rest;
-        }
-        int na = 0, nb = 0;
-        stat = 0.0;
-#pragma unroll
-        for (int y = 0; y < kRegCats; ++y) nb += y <= pj && nj[y] > 0u ? 1 : 0;
-#pragma unroll
-        for (int x = 0; x < kRegCats; ++x) {
-            if (x > pi) continue;
-            na += ni[x] > 0u ? 1 : 0;
-#pragma unroll
-            for (int y = 0; y < kRegCats; ++y) {
-                if (y > pj) continue;
-                if (stat_kind) stat += x2_term<double>(N[x][y], ni[x], nj[y], (uint32_t)m);
-                else stat += g2_half_term<double>(N[x][y], ni[x], nj[y], (uint32_t)m);
-            }
-        }
-        if (!stat_kind) stat *= 2.0;
-        df = adj ? (int64_t)(na - 1) * (int64_t)(nb - 1) : (int64_t)pi * (int64_t)pj;
         return;
     }
     uint32_t li = (uint32_t)m, lj = (uint32_t)m;
@@ -549,7 +546,8 @@ BNS_INLINE void pair_stat(const PairArgs &P, const GramProb &gp, int oi, int oj,
 }
 
 // The depth-0 tests of a skeleton search: one lane per edge of the depth.
-__global__ __launch_bounds__(kWG) void k_depth0_pairs(DepthArgs A) {
+__global__ __launch_bounds__(kPairWG) void k_depth0_pairs(DepthArgs A) {
+    __shared__ uint32_t cells[kPairCats * kPairCats * kPairWG];
     Ctl *c = A.ctl;
     __shared__ int quit;
     if (threadIdx.x == 0) quit = c->done;
@@ -560,8 +558,8 @@ __global__ __launch_bounds__(kWG) void k_depth0_pairs(DepthArgs A) {
     const int lane = threadIdx.x & 63;
     unsigned long long ex = 0;
     double ob = 0.0;
-    for (unsigned long long e = (unsigned long long)blockIdx.x * kWG + threadIdx.x; e < E;
-         e += (unsigned long long)gridDim.x * kWG) {
+    for (unsigned long long e = (unsigned long long)blockIdx.x * kPairWG + threadIdx.x; e < E;
+         e += (unsigned long long)gridDim.x * kPairWG) {
         const EdgeRec rec = A.edges[e];
         const ProbDev pd = A.probs[rec.prob];
         const GramProb gp = P.gp[rec.prob];
@@ -569,7 +567,7 @@ __global__ __launch_bounds__(kWG) void k_depth0_pairs(DepthArgs A) {
         double stat;
         int64_t df;
         pair_stat(P, gp, P.var_oh[gi], P.var_oh[gj], A.cards[gi], A.cards[gj], pd.m, A.tile.stat,
-                  A.tile.df_rule != 0, stat, df);
+                  A.tile.df_rule != 0, stat, df, cells + threadIdx.x);
         if (chi2_tail_lane(df, stat) > pd.alpha) A.min_accept[e] = 0ull;  // the depth's only test accepted
         ++ex;
         ob += 2.0 * (double)pd.m;
@@ -586,12 +584,13 @@ __global__ __launch_bounds__(kWG) void k_depth0_pairs(DepthArgs A) {
 
 // Every pair i < j of one dataset (all-pairs entry point): pair index
 // i n - i (i + 1) / 2 + j - i - 1.
-__global__ __launch_bounds__(kWG) void k_ci_pairs(PairArgs P, const uint8_t *cards, int32_t n, double alpha,
+__global__ __launch_bounds__(kPairWG) void k_ci_pairs(PairArgs P, const uint8_t *cards, int32_t n, double alpha,
                                                   int stat_kind, int df_rule, double *stat_out, int64_t *df_out,
                                                   double *p_out, int32_t *flags_out) {
     const GramProb gp = P.gp[0];
+    __shared__ uint32_t cells[kPairCats * kPairCats * kPairWG];
     const int64_t npairs = (int64_t)n * (n - 1) / 2;
-    for (int64_t q = (int64_t)blockIdx.x * kWG + threadIdx.x; q < npairs; q += (int64_t)gridDim.x * kWG) {
+    for (int64_t q = (int64_t)blockIdx.x * kPairWG + threadIdx.x; q < npairs; q += (int64_t)gridDim.x * kPairWG) {
         // row i: the largest i with i n - i (i + 1) / 2 <= q
         int lo = 0, hi = n - 2;
         while (lo < hi) {
@@ -603,7 +602,8 @@ __global__ __launch_bounds__(kWG) void k_ci_pairs(PairArgs P, const uint8_t *car
         const int j = (int)(q - ((int64_t)i * n - (int64_t)i * (i + 1) / 2)) + i + 1;
         double stat;
         int64_t df;
-        pair_stat(P, gp, P.var_oh[i], P.var_oh[j], cards[i], cards[j], gp.m, stat_kind, df_rule != 0, stat, df);
+        pair_stat(P, gp, P.var_oh[i], P.var_oh[j], cards[i], cards[j], gp.m, stat_kind, df_rule != 0, stat, df,
+                  cells + threadIdx.x);
         const double p = chi2_tail_lane(df, stat);
         if (stat_out) stat_out[q] = stat;
         if (df_out) df_out[q] = df;
@@ -648,7 +648,7 @@ hipError_t launch_gram_tiles(const DepthArgs &a, hipStream_t s) {
 
 hipError_t launch_depth0_pairs(const DepthArgs &a, hipStream_t s) {
     launch_gram(a.pairs, a.cards, a.ctl, s);
-    hipLaunchKernelGGL(k_depth0_pairs, dim3(a.edge_grid), dim3(kWG), 0, s, a);
+    hipLaunchKernelGGL(k_depth0_pairs, dim3(a.edge_grid * (kWG / kPairWG)), dim3(kPairWG), 0, s, a);
     return hipGetLastError();
 }
 
@@ -657,8 +657,8 @@ hipError_t launch_ci_pairs(const PairArgs &p, const uint8_t *cards, int32_t n, d
                            hipStream_t s) {
     launch_gram(p, cards, nullptr, s);
     const int64_t npairs = (int64_t)n * (n - 1) / 2;
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(2048, (npairs + kWG - 1) / kWG));
-    hipLaunchKernelGGL(k_ci_pairs, dim3(grid), dim3(kWG), 0, s, p, cards, n, alpha, stat, df_rule, stat_out,
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(8192, (npairs + kPairWG - 1) / kPairWG));
+    hipLaunchKernelGGL(k_ci_pairs, dim3(grid), dim3(kPairWG), 0, s, p, cards, n, alpha, stat, df_rule, stat_out,
                        df_out, p_out, flags_out);
     return hipGetLastError();
 }
