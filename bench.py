@@ -453,9 +453,13 @@ def main():
     l2_hit = measured_l2_hit_rates(CONFIGS[a.config]["name"])
     # LDS increments of the counting step: one per sample of each executed
     # test (operand bytes / (d + 2) columns); the contraction paths count on
-    # MFMA and have none.  Peak: this device's own rate (bns_lds_increment_rate).
+    # MFMA and have none, nor has depth 1 from bit planes (popcounts), which
+    # follows a depth-0 contraction where all cardinalities are at most 5.  Peak: this device's own rate (bns_lds_increment_rate).
     lds_peak = bns.bns_lds_increment_rate(0)[0]
-    incs_d = [tot[d]["operand_bytes"] / (d + 2) if tot[d]["test_group"] != 3 else 0.0 for d in range(launches)]
+    planes1 = (launches > 0 and tot[0]["test_group"] == 3 and all(int(d.cards.max()) <= 5 for d in dss)
+               and not any(knobs.get(k) for k in ("depth1", "group_tests", "test_group", "round_tests", "form")))
+    incs_d = [0.0 if tot[d]["test_group"] == 3 or (d == 1 and planes1) else tot[d]["operand_bytes"] / (d + 2)
+              for d in range(launches)]
     per_depth = []
     for d in range(min(launches, ndep)):
         sd = span_d[d]
@@ -464,7 +468,8 @@ def main():
             "tests_executed": tot[d]["tests_executed"],
             "alu_frac": (req_bytes_d[d] / sd) / ALU_LANE_OPS_PER_S if sd > 0 else None,
             "operand_gbs_required": req_bytes_d[d] / sd / 1e9 if sd > 0 else None,
-            "lanes_per_test": {1: "wave", 2: "workgroup", 3: "Gram contraction"}.get(tot[d]["test_group"]),
+            "lanes_per_test": "bit planes" if d == 1 and planes1 else
+                              {1: "wave", 2: "workgroup", 3: "Gram contraction"}.get(tot[d]["test_group"]),
             "chunks": tot[d]["chunks"], "chunk_samples": tot[d]["chunk_samples"],
             "lds_frac": (incs_d[d] / sd) / lds_peak if (lds_peak and sd > 0 and incs_d[d] > 0) else None,
         })
