@@ -598,22 +598,6 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 }
 
-// A pair's decision in FP64 by a whole wave: lane c < ri rj holds cell c of
-// its table (out of line: rare).  n: the table [x][y], then N_x+ and N_+y.
-static __device__ __noinline__ bool pair_near(const uint32_t *n, int ri, int rj, uint32_t m, int df, double alpha,
-                                              int stat) {
-    const int lane = threadIdx.x & 63;
-    const int x = lane / rj, y = lane - x * rj;
-    double s = 0.0;
-    if (lane < ri * rj) {
-        const uint32_t N = n[x * kBitCards + y], nx = n[kBitCards * kBitCards + x];
-        const uint32_t ny = n[kBitCards * (kBitCards + 1) + y];
-        s = stat ? x2_term<double>(N, nx, ny, m) : g2_half_term<double>(N, nx, ny, m);
-    }
-    s = wave_sum(s);
-    return chi2_tail_wave(df, stat ? s : 2.0 * s).p > alpha;
-}
-
 // ---------------------------------------------------------------------------
 // Depth 0 of a search that runs depth 1 from bit planes: one workgroup per
 // block of 16 x 16 pairs, one lane per pair.  The lane sums its cells over
@@ -635,8 +619,8 @@ constexpr int kBitPlanes = kBitCards - 1;
 __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
     __shared__ uint32_t cnt[2][kPairSide][kBitCards];  // category counts of the block's rows and columns
     __shared__ uint8_t keep_sh[kPairSide][kPairSide + 4];
-    __shared__ uint32_t near_sh[kWaves][kBitCards * (kBitCards + 2)];
-    __shared__ unsigned int removed_sh;
+    __shared__ uint32_t cell_sh[kWG * kBitCards * kBitCards];  // re-evaluated pairs (an odd stride: lanes on different banks)
+    __shared__ unsigned int removed_sh, recheck_sh;
     const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
     const PairArgs &PA = A.pairs;
     int lo = 0, hi = A.n_probs - 1;
@@ -665,7 +649,7 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
         const int64_t t = gram_tile(gp, a, b, &off);
         return PA.part + (gp.item_base + t * nch) * tile_words + off;
     };
-    if (tid == 0) removed_sh = 0u;
+    if (tid == 0) removed_sh = recheck_sh = 0u;
     // category counts: two lanes' worth of variables, one plane per lane
     if (tid < 2 * kPairSide * kBitPlanes) {
         const int side = tid / (kPairSide * kBitPlanes), q = tid - side * kPairSide * kBitPlanes;
@@ -705,7 +689,6 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
     const int i = kPairSide * ib + ti, j = kPairSide * jb + tj;
     bool kept = false, near = false;
     int df = 0, ri = 1, rj = 1;
-    uint32_t *mine = near_sh[tid >> 6];
     uint32_t N[kBitCards][kBitCards];
     if (i < j && j < P.n) {
         const VarRec vi = vars[i], vj = vars[j];
@@ -790,23 +773,23 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
         kept = df > 0 && stat > cr.y;
         near = df > 0 && !(stat < cr.x) && !kept;
     }
-    for (uint64_t todo = __ballot(near); todo; todo &= todo - 1ull) {
-        // the wave decides its near pairs one after the other
-        const int L = __ffsll((long long)todo) - 1;
-        if ((tid & 63) == L) {
+    if (near) {
+        // in FP64, each lane its own pair (one loop over the cells: unrolled
+        // from registers it would be 20 KB of code)
+        uint32_t *mine = cell_sh + tid * kBitCards * kBitCards;
 #pragma unroll
-            for (int x = 0; x < kBitCards; ++x) {
+        for (int x = 0; x < kBitCards; ++x)
 #pragma unroll
-                for (int y = 0; y < kBitCards; ++y) mine[x * kBitCards + y] = N[x][y];
-                mine[kBitCards * kBitCards + x] = cnt[0][ti][x < ri ? x : 0];
-                mine[kBitCards * (kBitCards + 1) + x] = cnt[1][tj][x < rj ? x : 0];
+            for (int y = 0; y < kBitCards; ++y) mine[x * kBitCards + y] = N[x][y];
+        double s = 0.0;
+#pragma unroll 1
+        for (int x = 0; x < ri; ++x)
+#pragma unroll 1
+            for (int y = 0; y < rj; ++y) {
+                const uint32_t v = mine[x * kBitCards + y], nx = cnt[0][ti][x], ny = cnt[1][tj][y];
+                s += A.tile.stat ? x2_term<double>(v, nx, ny, m) : g2_half_term<double>(v, nx, ny, m);
             }
-        }
-        Grp::wave().sync();
-        const bool indep = pair_near(mine, __shfl(ri, L, 64), __shfl(rj, L, 64), m, __shfl(df, L, 64), P.alpha,
-                                     A.tile.stat);
-        if ((tid & 63) == L) kept = !indep;
-        Grp::wave().sync();
+        kept = !(chi2_tail_lane(df, A.tile.stat ? s : 2.0 * s) > P.alpha);
     }
     keep_sh[ti][tj] = kept ? 1 : 0;
     __syncthreads();
@@ -847,15 +830,19 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
         }
     }
     for (int off = 32; off > 0; off >>= 1) gone += __shfl_xor(gone, off, 64);
+    const unsigned int again = (unsigned int)__popcll(__ballot(near));
     if ((tid & 63) == 0 && gone) atomicAdd(&removed_sh, gone);
+    if ((tid & 63) == 0 && again) atomicAdd(&recheck_sh, again);
     __syncthreads();
     if (tid == 0) {
         Ctl *c = A.ctl;
         const unsigned long long np = (unsigned long long)P.n * (unsigned long long)(P.n - 1) / 2ull;
         if (removed_sh) atomicAdd(&c->stats[0].removed, (unsigned long long)removed_sh);
+        if (recheck_sh) atomicAdd(&c->stats[0].rechecks, (unsigned long long)recheck_sh);
         if (A.per_prob) {
             PStatDev &ps = A.pstat[(int64_t)lo * kMaxDepths];
             if (removed_sh) atomicAdd(&ps.removed, (unsigned long long)removed_sh);
+            if (recheck_sh) atomicAdd(&ps.rechecks, (unsigned long long)recheck_sh);
             if ((int)blockIdx.x == B.block_base) ps.edges = ps.tickets = ps.required = ps.executed = np;
         }
         if ((int)blockIdx.x == B.block_base) atomicAdd(&c->stats[0].operand_bytes, 2.0 * (double)np * (double)P.m);

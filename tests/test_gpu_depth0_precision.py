@@ -1,0 +1,47 @@
+"""Arithmetic of depth 0 from bit planes: the FP64 re-evaluations it reports
+are those of the per-depth test kernel.
+
+The counts are whole numbers; a wide band keeps every pair's p-value far (many
+times the FP32 error) from the band's ends.
+"""
+
+import numpy as np
+import pytest
+
+from bnsynth import make_dataset
+
+pytestmark = pytest.mark.gpu
+
+TESTS = 1  # options.depth0: the per-depth test kernel
+
+
+@pytest.fixture(scope="module")
+def bns():
+    import paper_2212_04259_amd as b
+    b.load()
+    return b
+
+
+def _data(k):
+    return make_dataset(16 + 7 * k, 20 + 7 * k, 3, 2, 5, 0.5, 700 + 900 * k, seed=8100 + k)
+
+
+def _rechecks(bns, sets, alphas, **opt):
+    hs = [bns.bns_dataset_create(d.data, d.cards) for d in sets]
+    o = bns.bns_options_default(recheck_band=0.3, **opt)
+    if len(hs) == 1:
+        outs = [bns.bns_pc_skeleton_dataset(hs[0], alphas[0], 1, o)]
+    else:
+        outs = bns.bns_pc_skeleton_batch(hs, alphas, [1] * len(hs), o)
+    return [s.stats[0]["rechecks"] for s in outs]
+
+
+@pytest.mark.parametrize("statistic,df_rule", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("datasets", [1, 3])
+def test_rechecks_are_reported(bns, statistic, df_rule, datasets):
+    sets = [_data(k) for k in range(datasets)]
+    alphas = [0.05, 0.4, 0.9][:datasets]
+    print(f"depth 0 rechecks stat={statistic} df={df_rule} datasets={datasets}", flush=True)
+    want = _rechecks(bns, sets, alphas, depth0=TESTS, statistic=statistic, df_rule=df_rule)
+    assert min(want) > 10
+    assert _rechecks(bns, sets, alphas, statistic=statistic, df_rule=df_rule) == want
