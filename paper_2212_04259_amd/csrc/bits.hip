@@ -602,9 +602,11 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
 // Depth 0 of a search that runs depth 1 from bit planes: one workgroup per
 // block of 16 x 16 pairs, one lane per pair.  The lane sums its cells over
 // the chunks of the Gram tiles, completes the table, leaves it and its
-// transpose in the pairwise tables, and decides the pair by its FP32
-// statistic against the critical values (in FP64 within their reach); the
-// block writes the adjacency, the removal depths and, for small searches, its
+// transpose in the pairwise tables, and decides the pair by its statistic
+// against the critical values: in FP64 where the caller asks for it or the
+// contraction is asked for or chosen by the amount of work (BitArgs.fp64), else
+// in FP32, and again in FP64 within the critical values' reach.  The block
+// writes the adjacency, the removal depths and, for small searches, its
 // 16-bit pieces of the adjacency bit rows.  Every pair is tested once, so the
 // depth needs no edge list (records, level order and removals of half a
 // million edges).  What bounds it: a few dependent loads per lane, and the
@@ -688,6 +690,8 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
     __syncthreads();
     const int i = kPairSide * ib + ti, j = kPairSide * jb + tj;
     bool kept = false, near = false;
+    const bool all64 = A.bits.fp64 != 0;
+    double2 cr = make_double2(0.0, 0.0);
     int df = 0, ri = 1, rj = 1;
     uint32_t N[kBitCards][kBitCards];
     if (i < j && j < P.n) {
@@ -764,14 +768,14 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
                 B.gram[(ci + x) * R + cj + y] = (int32_t)N[x][y];
                 B.gram[(cj + y) * R + ci + x] = (int32_t)N[x][y];
                 const uint32_t ny = cnt[1][tj][y];
-                st += x2 ? x2_term<float>(N[x][y], nx, ny, m) : bit_g2_term(N[x][y], nx, ny, m);
+                if (!all64) st += x2 ? x2_term<float>(N[x][y], nx, ny, m) : bit_g2_term(N[x][y], nx, ny, m);
             }
         }
         const double stat = x2 ? (double)st : 2.0 * (double)st;
         df = A.tile.df_rule ? (na - 1) * (nb - 1) : pi * pj;
-        const double2 cr = A.bits.crit[(int64_t)B.crit_row * kCritDf + df];
-        kept = df > 0 && stat > cr.y;
-        near = df > 0 && !(stat < cr.x) && !kept;
+        cr = A.bits.crit[(int64_t)B.crit_row * kCritDf + df];
+        kept = df > 0 && !all64 && stat > cr.y;
+        near = df > 0 && (all64 || (!(stat < cr.x) && !kept));
     }
     if (near) {
         // in FP64, each lane its own pair (one loop over the cells: unrolled
@@ -789,7 +793,9 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
                 const uint32_t v = mine[x * kBitCards + y], nx = cnt[0][ti][x], ny = cnt[1][tj][y];
                 s += A.tile.stat ? x2_term<double>(v, nx, ny, m) : g2_half_term<double>(v, nx, ny, m);
             }
-        kept = !(chi2_tail_lane(df, A.tile.stat ? s : 2.0 * s) > P.alpha);
+        const double stat = A.tile.stat ? s : 2.0 * s;
+        kept = stat > cr.y;
+        if (!kept && !(stat < cr.x)) kept = !(chi2_tail_lane(df, stat) > P.alpha);
     }
     keep_sh[ti][tj] = kept ? 1 : 0;
     __syncthreads();
@@ -830,7 +836,7 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
         }
     }
     for (int off = 32; off > 0; off >>= 1) gone += __shfl_xor(gone, off, 64);
-    const unsigned int again = (unsigned int)__popcll(__ballot(near));
+    const unsigned int again = all64 ? 0u : (unsigned int)__popcll(__ballot(near));
     if ((tid & 63) == 0 && gone) atomicAdd(&removed_sh, gone);
     if ((tid & 63) == 0 && again) atomicAdd(&recheck_sh, again);
     __syncthreads();

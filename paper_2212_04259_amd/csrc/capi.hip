@@ -1630,6 +1630,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
         a.bits.grid = std::max(1, dc.num_cu * bits_max_wg_per_cu());
         a.bits.run_log2 = a.grab_block_log2;
         a.bits.blocks = blocks16;
+        a.bits.fp64 = tile.fp64 || want_pairs;
         a.bits_policy = 1;
         a.xy_policy = 0;
     }

@@ -142,6 +142,8 @@ struct BitArgs {
     int32_t grid;          // workgroups of the kernel
     int32_t run_log2;      // units dealt to a grab counter in runs of 2^this
     int32_t blocks;        // workgroups of the depth-0 kernel (blocks of 16 x 16 pairs)
+    int32_t fp64;          // depth 0: every pair's statistic in FP64
+    int32_t pad;
 };
 
 // Arguments of the per-depth pipeline of a skeleton search (all device pointers).

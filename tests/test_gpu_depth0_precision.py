@@ -1,5 +1,6 @@
 """Arithmetic of depth 0 from bit planes: the FP64 re-evaluations it reports
-are those of the per-depth test kernel.
+are those of the per-depth test kernel, and where the statistic is FP64 from
+the start (by the options, or from 5e8 pair-samples on) there are none.
 
 The counts are whole numbers; a wide band keeps every pair's p-value far (many
 times the FP32 error) from the band's ends.
@@ -12,7 +13,7 @@ from bnsynth import make_dataset
 
 pytestmark = pytest.mark.gpu
 
-TESTS = 1  # options.depth0: the per-depth test kernel
+TESTS, PAIRS = 1, 2  # options.depth0: the per-depth test kernel, the contraction
 
 
 @pytest.fixture(scope="module")
@@ -45,3 +46,21 @@ def test_rechecks_are_reported(bns, statistic, df_rule, datasets):
     want = _rechecks(bns, sets, alphas, depth0=TESTS, statistic=statistic, df_rule=df_rule)
     assert min(want) > 10
     assert _rechecks(bns, sets, alphas, statistic=statistic, df_rule=df_rule) == want
+
+
+@pytest.mark.parametrize("opt", [dict(precision=1), dict(depth0=PAIRS), dict(precision=1, depth0=PAIRS), dict(precision=1, statistic=1, df_rule=1)])
+def test_fp64_statistic(bns, opt):
+    print(f"depth 0 in FP64 {opt}", flush=True)
+    assert _rechecks(bns, [_data(2)], [0.05], **opt) == [0]
+
+
+@pytest.mark.parametrize("m,fp64", [(19_000, False), (21_000, True)])
+def test_fp64_by_work(bns, m, fp64):
+    # 225 variables: 25,200 pairs, 5e8 pair-samples at 19,842 samples
+    n = 225
+    rng = np.random.default_rng(m)
+    data, cards = rng.integers(0, 3, (n, m), dtype=np.uint8), np.full(n, 3, dtype=np.uint8)
+    print(f"depth 0 of {n} x {m}", flush=True)
+    ds = bns.bns_dataset_create(data, cards)
+    sk = bns.bns_pc_skeleton_dataset(ds, 0.05, 1, bns.bns_options_default(recheck_band=0.3))
+    assert (sk.stats[0]["rechecks"] == 0) == fp64
