@@ -238,7 +238,7 @@ struct BitItem1 {
 // first acceptance.  Returns the first accepting rank (or ~0) and counts the
 // tests run and re-checked.
 template <bool GENERAL>
-BNS_INLINE uint32_t bit_unit(const DepthArgs &A, BitSh &s, const double2 *crit, const ProbDev &P, const BitProb &B,
+BNS_INLINE uint32_t bit_unit(const DepthArgs &A, BitSh &s, const CritVal *crit, const ProbDev &P, const BitProb &B,
                              const BitItem1 &rec, uint32_t &exec, uint32_t &rechecks) {
     const int lane = threadIdx.x & 63;
     const Grp g = Grp::wave();
@@ -429,7 +429,7 @@ BNS_INLINE uint32_t bit_unit(const DepthArgs &A, BitSh &s, const double2 *crit, 
                 s.df[lane] = df;
             }
             s.st[lane] = st;
-            const double2 cr = crit[df];  // (df <= (kBitCards - 1)^2 kBitCards)
+            const CritVal cr = crit[df];  // (df <= (kBitCards - 1)^2 kBitCards)
             acc_t = df <= 0 || st < cr.x;
             near = df > 0 && !(st < cr.x) && !(st > cr.y);
         }
@@ -478,7 +478,7 @@ BNS_INLINE unsigned long long bit_units(unsigned long long units, int p, int lgb
 template <bool GENERAL>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_depth1_bits(DepthArgs A) {
     __shared__ BitSh sh[kWaves];
-    __shared__ double2 crit_sh[kCritDf];
+    __shared__ CritVal crit_sh[kCritDf];
     __shared__ ProbDev prob_sh;   // searches of one problem
     __shared__ BitProb bprob_sh;
     __shared__ BitItem1 items_sh[kWaves];
@@ -569,7 +569,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
         if (uni(u.r) >= uni(u.r1)) continue;
         const ProbDev &P = one_prob ? prob_sh : A.probs[uni(u.prob)];
         const BitProb &B = one_prob ? bprob_sh : A.bits.prob[uni(u.prob)];
-        const double2 *crit = one_crit ? crit_sh : A.bits.crit + (int64_t)uni(B.crit_row) * kCritDf;
+        const CritVal *crit = one_crit ? crit_sh : A.bits.crit + (int64_t)uni(B.crit_row) * kCritDf;
         uint32_t ex = 0, re = 0;
         const uint32_t first = bit_unit<GENERAL>(A, s, crit, P, B, u, ex, re);
         if (lane == 0) {
@@ -691,7 +691,7 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
     const int i = kPairSide * ib + ti, j = kPairSide * jb + tj;
     bool kept = false, near = false;
     const bool all64 = A.bits.fp64 != 0;
-    double2 cr = make_double2(0.0, 0.0);
+    CritVal cr{0.0, 0.0};
     int df = 0, ri = 1, rj = 1;
     uint32_t N[kBitCards][kBitCards];
     if (i < j && j < P.n) {

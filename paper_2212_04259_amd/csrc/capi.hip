@@ -11,7 +11,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <fstream>
-#include <limits>
 #include <memory>
 #include <mutex>
 #include <sstream>
@@ -168,13 +167,6 @@ struct GraphEntry {
     }
 };
 
-// Statistics that enclose the decisions of one alpha: for df = 1 .. kCritDf - 1
-// a statistic below x has p > alpha + reach, one above y has p < alpha - reach.
-struct CritRow {
-    double alpha, reach;
-    std::vector<double2> v;
-};
-
 // Pinned staging of a CI batch of at most kCiStageBytes: the kernel itself
 // brings the results to host memory and raises a completion flag, which the
 // host polls: no copies out, no stream synchronisation.  Allocated with the
@@ -202,7 +194,6 @@ struct DevCtx {
     DevBuf pair_part;    // partial Gram tiles of depth 0 through the pair contraction
     DevBuf planes;       // bit planes of the columns
     DevBuf tables;       // every pairwise table, for depth 1 from bit planes
-    std::vector<CritRow> crit;  // critical values by alpha and band
     DevBuf tri_node, tri_rowoff, tri_eidx, tri_part;  // depth 1 through the masked contractions
     DevBuf pairs_setup, pairs_out;  // bns_ci_pairs: tile plan and results
     DevBuf err_val, err_tag, err_cnt;  // verification log
@@ -940,66 +931,6 @@ struct PlanesKeep {
     }
 };
 
-// Upper tail of the chi-square distribution with df degrees of freedom at 2 x
-// and the Gamma(df / 2, 1) density there (closed forms for integer df).
-static double chi2_upper(int df, double x, double *dens) {
-    const double pi = 3.141592653589793;
-    const bool odd = (df & 1) != 0;
-    const int n = df >> 1;
-    double term = odd ? 2.0 * std::sqrt(x / pi) : 1.0, sum = 0.0, last = 0.0;
-    for (int k = 0; k < n; ++k) {
-        sum += term;
-        last = term;
-        term *= x / ((double)(k + 1) + (odd ? 0.5 : 0.0));
-    }
-    const double ex = std::exp(-x);
-    *dens = n > 0 ? ex * last : ex / std::sqrt(pi * x);
-    return (odd ? std::erfc(std::sqrt(x)) : 0.0) + ex * sum;
-}
-
-// 2 x with upper tail q in (0, 1), to about 1e-12: Newton's method from the
-// Wilson-Hilferty approximation, kept inside a shrinking bracket.
-static double chi2_quantile(int df, double q) {
-    // normal quantile (Abramowitz and Stegun 26.2.23)
-    const double u = std::sqrt(-2.0 * std::log(q < 0.5 ? q : 1.0 - q));
-    double zn = u - (2.515517 + 0.802853 * u + 0.010328 * u * u) /
-                        (1.0 + 1.432788 * u + 0.189269 * u * u + 0.001308 * u * u * u);
-    if (q >= 0.5) zn = -zn;
-    const double h = 2.0 / (9.0 * df), c = 1.0 - h + zn * std::sqrt(h);
-    double x = std::max(0.5 * df * c * c * c, 1e-8 * df), lo = 0.0, hi = 700.0;
-    for (int it = 0; it < 100; ++it) {
-        double d;
-        const double f = chi2_upper(df, x, &d) - q;
-        if (f > 0) lo = x;
-        else hi = x;
-        double nx = x + f / d;
-        if (!(nx > lo && nx < hi)) nx = 0.5 * (lo + hi);
-        const bool done = std::fabs(nx - x) <= 1e-12 * x;
-        x = nx;
-        if (done) break;
-    }
-    return 2.0 * x;
-}
-
-// The row of (alpha, reach): decisions outside [x, y] are certain without a
-// tail.  reach covers the re-check band and, with 1e-3, four times the
-// propagated FP32 error bound (at most 1e-4 for df < kCritDf).
-static const std::vector<double2> &crit_row(DevCtx &dc, double alpha, double band) {
-    const double reach = std::max(band, 1e-3);
-    for (const CritRow &c : dc.crit)
-        if (c.alpha == alpha && c.reach == reach) return c.v;
-    if (dc.crit.size() >= 64) dc.crit.erase(dc.crit.begin());
-    CritRow r{alpha, reach, std::vector<double2>((size_t)kCritDf, make_double2(0.0, 0.0))};
-    const double inf = std::numeric_limits<double>::infinity();
-    for (int df = 1; df < kCritDf; ++df) {
-        // (a part in 10^6 to spare)
-        r.v[(size_t)df].x = alpha + reach < 1.0 ? chi2_quantile(df, alpha + reach) * (1.0 - 1e-6) : 0.0;
-        r.v[(size_t)df].y = alpha - reach > 1e-12 ? chi2_quantile(df, alpha - reach) * (1.0 + 1e-6) : inf;
-    }
-    dc.crit.push_back(std::move(r));
-    return dc.crit.back().v;
-}
-
 // ---------------------------------------------------------------------------
 // bns_ci_pairs: every pairwise marginal test of a dataset through the pair
 // contraction.
@@ -1449,7 +1380,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
         o_vars = (o_varoh + sizeof(int32_t) * pp.var_oh.size() + 15) & ~(size_t)15;
         o_bits = al8(o_vars + (bits ? sizeof(VarRec) * (size_t)G : 0));
         o_crit = (o_bits + (bits ? sizeof(BitProb) * (size_t)P : 0) + 15) & ~(size_t)15;
-        setup_bytes = al8(o_crit + (bits ? sizeof(double2) * kCritDf * crit_alpha.size() : 0));
+        setup_bytes = al8(o_crit + (bits ? sizeof(CritVal) * kCritDf * crit_alpha.size() : 0));
         const double table_bytes = bits ? 4.0 * (double)table_words : 0.0;
         // every workspace buffer of the search (removal records: the first
         // launch's share; later growth is checked when it happens)
@@ -1502,9 +1433,11 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
                 blocks16 += nb16 * (nb16 + 1) / 2;
                 tab += (int64_t)R * R;
             }
+            bool card[kBitCards + 1] = {};
+            for (uint8_t cv : gcards) card[cv] = true;
+            const CritMask need = crit_need(card, kBitCards, tile.df_rule != 0);
             for (size_t q = 0; q < crit_alpha.size(); ++q)
-                std::memcpy(h + o_crit + q * sizeof(double2) * kCritDf,
-                            crit_row(dc, crit_alpha[q], tile.fp64 ? 0.0 : tile.band).data(), sizeof(double2) * kCritDf);
+                crit_values(crit_alpha[q], tile.fp64 ? 0.0 : tile.band, need, (CritVal *)(h + o_crit) + q * kCritDf);
         }
     }
     if (!(dc.setup_last_dev == dc.setup.p && dc.setup_last.size() == setup_bytes &&
@@ -1625,7 +1558,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
         a.bits.prob = (const BitProb *)(sb + o_bits);
         a.bits.var = (const VarRec *)(sb + o_vars);
         a.pairs.var = values_want ? a.bits.var : nullptr;
-        a.bits.crit = (const double2 *)(sb + o_crit);
+        a.bits.crit = (const CritVal *)(sb + o_crit);
         a.bits.n_crit = (int32_t)crit_alpha.size();
         a.bits.grid = std::max(1, dc.num_cu * bits_max_wg_per_cu());
         a.bits.run_log2 = a.grab_block_log2;

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "bns_internal.h"
+#include "crit.h"
 
 namespace bns {
 
@@ -107,7 +108,7 @@ constexpr int kBitCards = 5;   // largest cardinality: at most 4 planes per vari
 constexpr int kBitUnit = 8;    // tests per pass at most
 constexpr int kBitSegs = 8;    // segments of an edge's ranks at most
 constexpr int kBitSegRanks = 16;  // ranks per segment aimed for
-constexpr int kCritDf = 128;   // critical values by df: df <= (kBitCards - 1)^2 kBitCards = 80
+static_assert((kBitCards - 1) * (kBitCards - 1) * kBitCards < kCritDf, "critical values by df");
 
 struct VarRec {
     int32_t card;
@@ -137,7 +138,7 @@ struct BitProb {
 struct BitArgs {
     const BitProb *prob;   // per problem (null: depth 1 uses the test kernel)
     const VarRec *var;     // per global variable
-    const double2 *crit;   // [row][df]: a statistic below .x accepts, above .y does not (between: by its p)
+    const CritVal *crit;   // [row][df]: a statistic below .x accepts, above .y does not (between: by its p)
     int32_t n_crit;        // rows: distinct alphas
     int32_t grid;          // workgroups of the kernel
     int32_t run_log2;      // units dealt to a grab counter in runs of 2^this
