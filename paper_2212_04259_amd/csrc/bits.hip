@@ -197,33 +197,31 @@ BNS_INLINE float bit_g2_term(uint32_t N, uint32_t nxz, uint32_t nyz, uint32_t nz
     return N == 0 ? E : (float)N * (fabsf(t) <= TermCfg<float>::tau ? near : far);
 }
 
-// A test within reach of alpha: its decision from the tail in FP64 and, for
-// an FP32 statistic in the band or the error bound, from the statistic in
-// FP64 too.  Out of line: rare, and its code would push the counting loops
-// out of the instruction cache.
+// A test that its statistic's critical values leave open: an FP32 statistic is
+// formed again in FP64 (in the band or the error bound of alpha: with alpha
+// below the band every dependent test), and a tail is evaluated only where the
+// FP64 statistic is at the quantile of alpha itself.  Out of line: its code
+// would push the counting loops out of the instruction cache.
 static __device__ __noinline__ bool bit_near(const uint32_t *tab, uint32_t rx, uint32_t ry, uint32_t rz, double st,
-                                             int64_t df, double alpha, double band, int stat, bool fp64,
-                                             bool *recheck) {
-    *recheck = false;
-    const uint32_t T = rx * ry * rz;
-    const Tail tl = chi2_tail_wave(df, st);
-    if (fp64) return tl.p > alpha;
-    const double gap = fabs(tl.p - alpha);
-    const double rel = (32.0 + (double)T / 64.0 + 1.0) * 5.96e-8 + 1e-6;
-    if (!(gap < band || gap < 4.0 * (tl.dens * 0.5 * st * rel))) return tl.p > alpha;
-    *recheck = true;
-    const float inv_rx = 1.0f / (float)rx, inv_ry = 1.0f / (float)ry;
-    double part = 0.0;
-    for (uint32_t c = threadIdx.x & 63u; c < T; c += 64u) {
-        const BitCell q = bit_cell(c, rx, ry, inv_rx, inv_ry);
-        const uint32_t *mz = tab + T + q.z * (rx + ry + 1u);
-        const uint32_t nzz = mz[rx + ry];
-        if (nzz)
-            part += stat ? x2_term<double>(tab[c], mz[q.x], mz[rx + q.y], nzz)
-                         : g2_half_term<double>(tab[c], mz[q.x], mz[rx + q.y], nzz);
+                                             int64_t df, double alpha, double x64, double y64, int stat, bool fp64) {
+    if (!fp64) {
+        const uint32_t T = rx * ry * rz;
+        const float inv_rx = 1.0f / (float)rx, inv_ry = 1.0f / (float)ry;
+        double part = 0.0;
+        for (uint32_t c = threadIdx.x & 63u; c < T; c += 64u) {
+            const BitCell q = bit_cell(c, rx, ry, inv_rx, inv_ry);
+            const uint32_t *mz = tab + T + q.z * (rx + ry + 1u);
+            const uint32_t nzz = mz[rx + ry];
+            if (nzz)
+                part += stat ? x2_term<double>(tab[c], mz[q.x], mz[rx + q.y], nzz)
+                             : g2_half_term<double>(tab[c], mz[q.x], mz[rx + q.y], nzz);
+        }
+        part = wave_sum(part);
+        st = stat ? part : 2.0 * part;
     }
-    part = wave_sum(part);
-    return chi2_tail_wave(df, stat ? part : 2.0 * part).p > alpha;
+    if (st < x64) return true;
+    if (st > y64) return false;
+    return chi2_tail_wave(df, st).p > alpha;
 }
 
 // A decoded work unit: ranks r .. r1 - 1 of edge e (depth 1: at most
@@ -429,7 +427,7 @@ BNS_INLINE uint32_t bit_unit(const DepthArgs &A, BitSh &s, const CritVal *crit, 
                 s.df[lane] = df;
             }
             s.st[lane] = st;
-            const CritVal cr = crit[df];  // (df <= (kBitCards - 1)^2 kBitCards)
+            const CritVal &cr = crit[df];  // (df <= (kBitCards - 1)^2 kBitCards)
             acc_t = df <= 0 || st < cr.x;
             near = df > 0 && !(st < cr.x) && !(st > cr.y);
         }
@@ -438,10 +436,10 @@ BNS_INLINE uint32_t bit_unit(const DepthArgs &A, BitSh &s, const CritVal *crit, 
         while (todo) {
             const int ti = __ffsll((long long)todo) - 1;
             todo &= todo - 1ull;
-            bool re = false;
-            if (bit_near(s.tab + s.toff[ti], rx, ry, s.rz[ti], s.st[ti], s.df[ti], P.alpha, A.tile.band, stat, fp64, &re))
+            const CritVal &cr = crit[s.df[ti]];
+            if (bit_near(s.tab + s.toff[ti], rx, ry, s.rz[ti], s.st[ti], s.df[ti], P.alpha, cr.x64, cr.y64, stat, fp64))
                 am |= 1ull << ti;
-            rechecks += re ? 1u : 0u;
+            rechecks += fp64 ? 0u : 1u;
         }
         exec += (uint32_t)kb;
         g.sync();  // the tables are rewritten by the next pass
@@ -621,8 +619,9 @@ constexpr int kBitPlanes = kBitCards - 1;
 __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
     __shared__ uint32_t cnt[2][kPairSide][kBitCards];  // category counts of the block's rows and columns
     __shared__ uint8_t keep_sh[kPairSide][kPairSide + 4];
-    __shared__ uint32_t cell_sh[kWG * kBitCards * kBitCards];  // re-evaluated pairs (an odd stride: lanes on different banks)
-    __shared__ unsigned int removed_sh, recheck_sh;
+    __shared__ uint32_t cell_sh[kWG * kBitCards * kBitCards];  // tables of the pairs decided in FP64 (an odd stride)
+    __shared__ uint32_t near_sh[kWG];                          // those pairs: lane, r_i, r_j, df
+    __shared__ unsigned int near_n, removed_sh;
     const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
     const PairArgs &PA = A.pairs;
     int lo = 0, hi = A.n_probs - 1;
@@ -651,7 +650,7 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
         const int64_t t = gram_tile(gp, a, b, &off);
         return PA.part + (gp.item_base + t * nch) * tile_words + off;
     };
-    if (tid == 0) removed_sh = recheck_sh = 0u;
+    if (tid == 0) removed_sh = near_n = 0u;
     // category counts: two lanes' worth of variables, one plane per lane
     if (tid < 2 * kPairSide * kBitPlanes) {
         const int side = tid / (kPairSide * kBitPlanes), q = tid - side * kPairSide * kBitPlanes;
@@ -691,7 +690,6 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
     const int i = kPairSide * ib + ti, j = kPairSide * jb + tj;
     bool kept = false, near = false;
     const bool all64 = A.bits.fp64 != 0;
-    CritVal cr{0.0, 0.0};
     int df = 0, ri = 1, rj = 1;
     uint32_t N[kBitCards][kBitCards];
     if (i < j && j < P.n) {
@@ -773,32 +771,49 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
         }
         const double stat = x2 ? (double)st : 2.0 * (double)st;
         df = A.tile.df_rule ? (na - 1) * (nb - 1) : pi * pj;
-        cr = A.bits.crit[(int64_t)B.crit_row * kCritDf + df];
+        const CritVal &cr = A.bits.crit[(int64_t)B.crit_row * kCritDf + df];
         kept = df > 0 && !all64 && stat > cr.y;
         near = df > 0 && (all64 || (!(stat < cr.x) && !kept));
     }
     if (near) {
-        // in FP64, each lane its own pair (one loop over the cells: unrolled
-        // from registers it would be 20 KB of code)
-        uint32_t *mine = cell_sh + tid * kBitCards * kBitCards;
 #pragma unroll
         for (int x = 0; x < kBitCards; ++x)
 #pragma unroll
-            for (int y = 0; y < kBitCards; ++y) mine[x * kBitCards + y] = N[x][y];
-        double s = 0.0;
-#pragma unroll 1
-        for (int x = 0; x < ri; ++x)
-#pragma unroll 1
-            for (int y = 0; y < rj; ++y) {
-                const uint32_t v = mine[x * kBitCards + y], nx = cnt[0][ti][x], ny = cnt[1][tj][y];
-                s += A.tile.stat ? x2_term<double>(v, nx, ny, m) : g2_half_term<double>(v, nx, ny, m);
-            }
-        const double stat = A.tile.stat ? s : 2.0 * s;
-        kept = stat > cr.y;
-        if (!kept && !(stat < cr.x)) kept = !(chi2_tail_lane(df, stat) > P.alpha);
+            for (int y = 0; y < kBitCards; ++y) cell_sh[(tid * kBitCards + x) * kBitCards + y] = N[x][y];
+        near_sh[atomicAdd(&near_n, 1u)] = (uint32_t)(tid | ri << 8 | rj << 12 | df << 16);
     }
     keep_sh[ti][tj] = kept ? 1 : 0;
     __syncthreads();
+    // These pairs' statistics in FP64, four lanes each (a chain of 16 cells of
+    // one lane takes 13 us; and one loop: unrolled from registers its code
+    // would be 20 KB).
+    const uint32_t nn = near_n;
+    for (uint32_t q0 = 0; q0 < 4u * nn; q0 += kWG) {
+        const uint32_t it = q0 + (uint32_t)tid;
+        const bool on = it < 4u * nn;
+        const uint32_t rec = near_sh[on ? it >> 2 : 0u];
+        const uint32_t pt = rec & 255u, a = (rec >> 8) & 15u, b = (rec >> 12) & 15u, d = rec >> 16;
+        const uint32_t pi = pt >> 4, pj = pt & 15u;
+        const float inv_b = 1.0f / (float)b;
+        double s = 0.0;
+#pragma unroll 1
+        for (uint32_t c = it & 3u; c < a * b; c += 4u) {
+            const uint32_t x = fast_div(c, b, inv_b), y = c - x * b;
+            const uint32_t v = cell_sh[(pt * kBitCards + x) * kBitCards + y], nx = cnt[0][pi][x], ny = cnt[1][pj][y];
+            s += A.tile.stat ? x2_term<double>(v, nx, ny, m) : g2_half_term<double>(v, nx, ny, m);
+        }
+        s += __shfl_xor(s, 1, 64);
+        s += __shfl_xor(s, 2, 64);
+        if (on && (it & 3u) == 0u) {
+            const double stat = A.tile.stat ? s : 2.0 * s;
+            const CritVal &cr = A.bits.crit[(int64_t)B.crit_row * kCritDf + d];
+            bool k = stat > cr.y64;
+            if (!k && !(stat < cr.x64)) k = !(chi2_tail_lane(d, stat) > P.alpha);
+            keep_sh[pi][pj] = k ? 1 : 0;
+        }
+    }
+    __syncthreads();
+    kept = keep_sh[ti][tj] != 0;
     // both orders of every pair of the block; (row, column) of the block's own
     // and of its transpose
     unsigned int gone = i < j && j < P.n && !kept ? 1u : 0u;
@@ -836,19 +851,17 @@ __global__ __launch_bounds__(kWG) void k_depth0_bits(DepthArgs A, int small) {
         }
     }
     for (int off = 32; off > 0; off >>= 1) gone += __shfl_xor(gone, off, 64);
-    const unsigned int again = all64 ? 0u : (unsigned int)__popcll(__ballot(near));
     if ((tid & 63) == 0 && gone) atomicAdd(&removed_sh, gone);
-    if ((tid & 63) == 0 && again) atomicAdd(&recheck_sh, again);
     __syncthreads();
     if (tid == 0) {
         Ctl *c = A.ctl;
         const unsigned long long np = (unsigned long long)P.n * (unsigned long long)(P.n - 1) / 2ull;
         if (removed_sh) atomicAdd(&c->stats[0].removed, (unsigned long long)removed_sh);
-        if (recheck_sh) atomicAdd(&c->stats[0].rechecks, (unsigned long long)recheck_sh);
+        if (nn && !all64) atomicAdd(&c->stats[0].rechecks, (unsigned long long)nn);
         if (A.per_prob) {
             PStatDev &ps = A.pstat[(int64_t)lo * kMaxDepths];
             if (removed_sh) atomicAdd(&ps.removed, (unsigned long long)removed_sh);
-            if (recheck_sh) atomicAdd(&ps.rechecks, (unsigned long long)recheck_sh);
+            if (nn && !all64) atomicAdd(&ps.rechecks, (unsigned long long)nn);
             if ((int)blockIdx.x == B.block_base) ps.edges = ps.tickets = ps.required = ps.executed = np;
         }
         if ((int)blockIdx.x == B.block_base) atomicAdd(&c->stats[0].operand_bytes, 2.0 * (double)np * (double)P.m);

@@ -1437,7 +1437,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
             for (uint8_t cv : gcards) card[cv] = true;
             const CritMask need = crit_need(card, kBitCards, tile.df_rule != 0);
             for (size_t q = 0; q < crit_alpha.size(); ++q)
-                crit_values(crit_alpha[q], tile.fp64 ? 0.0 : tile.band, need, (CritVal *)(h + o_crit) + q * kCritDf);
+                crit_values(crit_alpha[q], tile.band, tile.fp64 != 0, need, (CritVal *)(h + o_crit) + q * kCritDf);
         }
     }
     if (!(dc.setup_last_dev == dc.setup.p && dc.setup_last.size() == setup_bytes &&

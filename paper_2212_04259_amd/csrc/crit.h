@@ -1,7 +1,7 @@
 // Critical values of the chi-square distribution (host code, no HIP): the
 // statistics that enclose the decisions of one alpha, so that the depths that
 // run from bit planes evaluate no tail outside them.  Computed for each call,
-// for the degrees of freedom that the call can reach: about 0.06 us a value, so
+// for the degrees of freedom that the call can reach: about 0.1 us each, so
 // an alpha that was not seen before costs what a repeated one does.
 #pragma once
 
@@ -11,7 +11,7 @@
 
 namespace bns {
 
-constexpr int kCritDf = 128;  // df below this; bit planes reach (kBitCards - 1)^2 kBitCards = 80
+constexpr int kCritDf = 96;  // df below this; bit planes reach (kBitCards - 1)^2 kBitCards = 80
 
 // 1 / (k + h) for the terms of the closed forms.
 struct CritInv {
@@ -49,50 +49,77 @@ inline double normal_upper(double q) {
     return q < 0.5 ? z : -z;
 }
 
-// x with chi2_upper(df, x) = q, q in [1e-90, 1 - 1e-9], to a part in 10^6; zn =
-// normal_upper(q).  Halley's method from the Wilson-Hilferty approximation, kept inside a shrinking
-// bracket: with the density g and its slope g r, r = (df / 2 - 1) / x - 1, a
-// step of h leaves about h (h r)^2 / 12, so usually one evaluation does.
-inline double chi2_half_quantile(int df, double q, double zn) {
-    if (df == 2) return -std::log(q);
-    const double wh = 2.0 / (9.0 * df), c = 1.0 - wh + zn * std::sqrt(wh), a1 = 0.5 * df - 1.0;
-    double x = std::fmax(0.5 * df * c * c * c, 1e-3 * df), lo = 0.0, hi = 700.0;
-    if (!(x < hi)) x = 0.5 * hi;
+// A quantile x (half a statistic) and the density there, to a part in 10^5 and
+// in 10 for tails in [1e-90, 1 - 1e-9].
+struct HalfQuantile {
+    double x, g;
+};
+
+// x with chi2_upper(df, x) = q by Halley's method from (x, its tail - q, its
+// density), kept inside a shrinking bracket.  With the density's slope g r, r =
+// (df / 2 - 1) / x - 1, a step of h leaves at most about h (h r)^2 / 6.
+inline HalfQuantile chi2_solve(int df, double q, double x, double f, double g) {
+    const double a1 = 0.5 * df - 1.0;
+    double lo = 0.0, hi = 700.0;
     for (int it = 0; it < 200; ++it) {
-        double g;
-        const double f = chi2_upper(df, x, &g) - q;
         if (f > 0) lo = x;
         else hi = x;
         const double h0 = f / g, r = a1 / x - 1.0, h = h0 / (1.0 + 0.5 * h0 * r);
-        double nx = x + h;
-        const bool in = nx > lo && nx < hi;
-        if (!in) nx = 0.5 * (lo + hi);
-        const bool done = (in && std::fabs(h) <= 5e-3 * x && std::fabs(h0 * r) <= 0.02) || hi - lo <= 1e-12 * hi;
-        x = nx;
-        if (done) break;
+        const bool in = x + h > lo && x + h < hi;
+        if ((in && std::fabs(h) <= 0.02 * x && std::fabs(h0 * r) <= 0.05) || hi - lo <= 1e-12 * hi)
+            return HalfQuantile{in ? x + h : x, g * (1.0 + h * r)};
+        x = in ? x + h : 0.5 * (lo + hi);
+        f = chi2_upper(df, x, &g) - q;
     }
-    return x;
+    return HalfQuantile{x, g};
 }
 
+// The same from the Wilson-Hilferty approximation; zn = normal_upper(q).
+// Usually one evaluation.
+inline HalfQuantile chi2_half_quantile(int df, double q, double zn) {
+    if (df == 2) return HalfQuantile{-std::log(q), q};
+    const double wh = 2.0 / (9.0 * df), c = 1.0 - wh + zn * std::sqrt(wh);
+    const double x = std::fmin(std::fmax(0.5 * df * c * c * c, 1e-3 * df), 350.0);
+    double g;
+    const double f = chi2_upper(df, x, &g) - q;
+    return chi2_solve(df, q, x, f, g);
+}
+
+// Statistics that enclose the decisions of one alpha and df.  An FP32
+// statistic below x has p > alpha + band, one above y has p < alpha - band, by
+// more than four times its error bound (a relative error below 4e-6 for the
+// tables of the bit-plane paths); an FP64 statistic below x64 has p > alpha,
+// one above y64 has p < alpha.
 struct CritVal {
-    double x, y;
+    double x, y, x64, y64;
 };
+constexpr double kCritSpare32 = 1e-4, kCritSpare64 = 4e-5;
 using CritMask = std::array<bool, kCritDf>;  // degrees of freedom in use
 
-// out[df] for the degrees of freedom of need: a statistic below x has p >
-// alpha + reach, one above y has p < alpha - reach (others: nothing certain).
-// reach covers the re-check band and, with 1e-3, four times the propagated
-// FP32 error bound (at most 1e-4 for df < kCritDf).
-inline void crit_values(double alpha, double band, const CritMask &need, CritVal *out) {
-    const double reach = std::fmax(band, 1e-3), inf = std::numeric_limits<double>::infinity();
-    const double up = alpha + reach, dn = alpha - reach;
-    const double zu = up < 1.0 - 1e-9 ? normal_upper(up) : 0.0, zd = dn > 1e-12 ? normal_upper(dn) : 0.0;
+// out[df] for the degrees of freedom of need (others: nothing certain).  fp64:
+// no FP32 statistic is compared (x and y are x64 and y64).
+inline void crit_values(double alpha, double band, bool fp64, const CritMask &need, CritVal *out) {
+    const double inf = std::numeric_limits<double>::infinity();
+    const bool able = alpha >= 1e-90 && alpha <= 1.0 - 1e-9;
+    const double zn = able ? normal_upper(alpha) : 0.0;
+    const double up = alpha + band;
+    // (alpha = band: a p below half an ulp of alpha is not within the band)
+    const double dn = alpha == band ? alpha * 1e-16 : alpha - band;
     for (int df = 0; df < kCritDf; ++df) {
-        out[df] = CritVal{0.0, inf};
-        if (df == 0 || !need[(size_t)df]) continue;
-        // (a part in 10^5 to spare)
-        if (up < 1.0 - 1e-9) out[df].x = 2.0 * chi2_half_quantile(df, up, zu) * (1.0 - 1e-5);
-        if (dn > 1e-12) out[df].y = 2.0 * chi2_half_quantile(df, dn, zd) * (1.0 + 1e-5);
+        CritVal v{0.0, inf, 0.0, inf};
+        if (able && need[(size_t)df]) {
+            const HalfQuantile h = chi2_half_quantile(df, alpha, zn);
+            v.x64 = 2.0 * h.x * (1.0 - kCritSpare64);
+            v.y64 = 2.0 * h.x * (1.0 + kCritSpare64);
+            if (fp64) {
+                v.x = v.x64;
+                v.y = v.y64;
+            } else {
+                if (up <= 1.0 - 1e-9) v.x = 2.0 * chi2_solve(df, up, h.x, -band, h.g).x * (1.0 - kCritSpare32);
+                if (dn >= 1e-90) v.y = 2.0 * chi2_solve(df, dn, h.x, alpha - dn, h.g).x * (1.0 + kCritSpare32);
+            }
+        }
+        out[df] = v;
     }
 }
 

@@ -138,7 +138,7 @@ struct BitProb {
 struct BitArgs {
     const BitProb *prob;   // per problem (null: depth 1 uses the test kernel)
     const VarRec *var;     // per global variable
-    const CritVal *crit;   // [row][df]: a statistic below .x accepts, above .y does not (between: by its p)
+    const CritVal *crit;   // [row][df]
     int32_t n_crit;        // rows: distinct alphas
     int32_t grid;          // workgroups of the kernel
     int32_t run_log2;      // units dealt to a grab counter in runs of 2^this

@@ -64,3 +64,32 @@ def test_fp64_by_work(bns, m, fp64):
     ds = bns.bns_dataset_create(data, cards)
     sk = bns.bns_pc_skeleton_dataset(ds, 0.05, 1, bns.bns_options_default(recheck_band=0.3))
     assert (sk.stats[0]["rechecks"] == 0) == fp64
+
+
+@pytest.mark.parametrize("band,alpha", [(0.0, 0.05), (1e-6, 1e-4), (1e-3, 1e-3)])
+def test_rechecks_at_the_ends_of_the_band(bns, band, alpha):
+    # a narrow band, and an alpha no larger than it: with alpha = band a pair
+    # whose p is 0 to the last bit of alpha is not within the band
+    ds = make_dataset(60, 80, 3, 2, 4, 0.5, 6_000, seed=8200)
+    h = bns.bns_dataset_create(ds.data, ds.cards)
+    print(f"depth 0 rechecks band={band} alpha={alpha}", flush=True)
+    got, want = [bns.bns_pc_skeleton_dataset(h, alpha, 1, bns.bns_options_default(recheck_band=band, **opt)).stats[0]["rechecks"]
+                 for opt in (dict(), dict(depth0=TESTS))]
+    # (a pair whose p is at an end of the band to the FP32 error may fall on either side)
+    assert abs(got - want) <= 1
+
+
+def _span(bns, h, alpha, depth):
+    o = bns.bns_options_default(depth0=0)
+    return float(np.median([bns.bns_pc_skeleton_dataset(h, alpha, 1, o).stats[depth]["span_seconds"] for _ in range(25)]))
+
+
+def test_small_alpha_costs_no_more_than_its_fp64(bns):
+    # alpha below the band: every dependent decision is made again in FP64
+    ds = make_dataset(20, 25, 3, 2, 4, 0.5, 5_000, seed=8301)
+    h = bns.bns_dataset_create(ds.data, ds.cards)
+    print("depths 0 and 1 at a small alpha", flush=True)
+    for depth, most in ((0, 1.5), (1, 1.5)):
+        usual, small = _span(bns, h, 0.05, depth), _span(bns, h, 1e-4, depth)
+        print(f"depth {depth}: {usual * 1e6:.1f} us at 0.05, {small * 1e6:.1f} us at 1e-4", flush=True)
+        assert small < most * usual
