@@ -673,8 +673,15 @@ BNS_INLINE void count_range(const TestSh &t, uint32_t *tab, uint32_t cbase, uint
 // The order of the samples within a word does not matter; samples past the
 // end have no bit set and count into cell 0, which starts that much below 0.
 // ---------------------------------------------------------------------------
+constexpr int kByteCols = 6;       // columns up to which the byte form has loops of its own
 constexpr int kMinPlaneBits = 4;   // (fewer: nearly every variable constant)
-constexpr int kMaxPlaneBits = 12;  // one pass: 4,096 cells, of which a workgroup's LDS holds one copy and the marginals
+// A table of 2^bits cells larger than this, or than kMaxPlanePad times the
+// test's own, loses more copies of it (and bank conflicts, and cells to clear
+// and sum) than the shorter reads give: depth 3 of 60 x 150,000 with up to five
+// categories 53 us from bytes, 54 with these limits, 102 with 12 bits and any
+// padding; of 300 x 200,000 153, 142, 209; depth 2 there 546, 381, 388.
+constexpr int kMaxPlaneBits = 9, kMaxPlaneBitsWide = 12;
+constexpr float kMaxPlanePad = 3.2f;
 
 template <int J>
 BNS_INLINE void bit_exchange(uint32_t &a, uint32_t &b) {
@@ -755,18 +762,24 @@ BNS_INLINE void count_planes(const TestSh &t, uint32_t *tab, int logR, uint32_t 
     }
 }
 
+template <bool kWide>
 BNS_INLINE void count_bits(const TestSh &t, int nb, uint32_t *tab, int logR, int64_t s0, int64_t s1, int rank, int S) {
     const uint32_t w0 = (uint32_t)(s0 >> 5), w1 = (uint32_t)((s1 + 31) >> 5);
+    if constexpr (kWide) {
+        switch (nb) {
+            case 10: return count_planes<10>(t, tab, logR, w0, w1, rank, S);
+            case 11: return count_planes<11>(t, tab, logR, w0, w1, rank, S);
+            case 12: return count_planes<12>(t, tab, logR, w0, w1, rank, S);
+            default: break;
+        }
+    }
     switch (nb) {
-        case 4: count_planes<4>(t, tab, logR, w0, w1, rank, S); break;
-        case 5: count_planes<5>(t, tab, logR, w0, w1, rank, S); break;
-        case 6: count_planes<6>(t, tab, logR, w0, w1, rank, S); break;
-        case 7: count_planes<7>(t, tab, logR, w0, w1, rank, S); break;
-        case 8: count_planes<8>(t, tab, logR, w0, w1, rank, S); break;
-        case 9: count_planes<9>(t, tab, logR, w0, w1, rank, S); break;
-        case 10: count_planes<10>(t, tab, logR, w0, w1, rank, S); break;
-        case 11: count_planes<11>(t, tab, logR, w0, w1, rank, S); break;
-        default: count_planes<12>(t, tab, logR, w0, w1, rank, S); break;
+        case 4: return count_planes<4>(t, tab, logR, w0, w1, rank, S);
+        case 5: return count_planes<5>(t, tab, logR, w0, w1, rank, S);
+        case 6: return count_planes<6>(t, tab, logR, w0, w1, rank, S);
+        case 7: return count_planes<7>(t, tab, logR, w0, w1, rank, S);
+        case 8: return count_planes<8>(t, tab, logR, w0, w1, rank, S);
+        default: return count_planes<9>(t, tab, logR, w0, w1, rank, S);
     }
 }
 
@@ -1068,7 +1081,7 @@ BNS_INLINE double table_pass(const Grp &g, TestSh &t, const Plan &P, uint32_t *l
             clear_words(rep_tab, head, 0u - past, g.rank, g.size);
             g.sync();
             if (nb > 0)
-                count_bits(t, nb, rep_tab, logR, src.s0, src.s1, g.rank, g.size);
+                count_bits<(kNcMax > kByteCols)>(t, nb, rep_tab, logR, src.s0, src.s1, g.rank, g.size);
             else if (chunked)
                 count_range<true, kNcMax>(t, rep_tab, P.rxy * z0, Tc, Tc, 0, src.s0, src.s1, g.rank, g.size);
             else

@@ -250,8 +250,10 @@ hipError_t launch_depth_prepare(const DepthArgs &a, hipStream_t s);   // snapsho
 // groups (depth 1 with a.xy_policy), 2 one test of at most kNarrowDepth + 2
 // columns (the instance without the wider counting loops, whose registers
 // otherwise spill), 3 units of the bit-plane kernel (launch_depth1_bits), 4 one
-// test counted from bit planes, 5 one test whose passes its units share; the
-// host's choice for a depth must match depth_units().
+// test counted from bit planes (depth 2), 5 one test whose passes its units
+// share, 6 as 4 at deeper depths (with the wider counting loops, for the tests
+// that stay with the bytes: without them five columns took 102 us instead of
+// 54 at depth 3 of 60 x 150,000); the host's choice for a depth must match depth_units().
 hipError_t launch_depth_tests(const DepthArgs &a, int grid, hipStream_t s,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr, int units = 0);
 constexpr int kNarrowDepth = 2;
@@ -260,7 +262,10 @@ constexpr int kNarrowDepth = 2;
 // 928 -> 600 us, depth 3 399 -> 310 us).  With fewer a test spends more on its
 // table than on reading, and a table padded to powers of two leaves room for
 // fewer copies of it (220 x 100,000, depth 2: 260 -> 265 us; 64 datasets of
-// 50,000: 1.64 -> 1.80 ms).
+// 50,000: 1.64 -> 1.80 ms).  By the longest dataset of a batch: with one long
+// one the short ones are no worse off from planes (depth 2 of one of 140,000
+// and 60 of 100,000 samples 2.2 ms, 4.1 with the short ones from bytes; with
+// 30 of 20,000 446 us, 507).
 constexpr int64_t kBitSamples = 1 << 17;
 // Deep depths, from the one at which a table of variables of the mean
 // cardinality has kDeepCells cells (a workgroup's LDS holds about 6,500 with
@@ -275,7 +280,7 @@ inline int depth_units(const DepthArgs &a, int d) {
     if (a.edge_form || a.err_val) return 0;
     if (a.bits_policy && d == 1) return 3;
     if (d >= a.deep_depth) return 5;
-    if (a.bits_policy && d > 1 && a.m_max >= kBitSamples) return 4;
+    if (a.bits_policy && d > 1 && a.m_max >= kBitSamples) return d <= kNarrowDepth ? 4 : 6;
     if (a.xy_policy == 1 && d == 1 && a.round_width == 0) return 1;
     if (d <= kNarrowDepth && a.tile.stat == 0 && a.tile.df_rule == 0) return 2;
     return 0;

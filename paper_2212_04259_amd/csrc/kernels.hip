@@ -996,7 +996,8 @@ BNS_INLINE void stage_test(const Grp &g, const Desc &q, TestSh &t) {
 
 // The same for a search with bit planes: the test is staged to be counted
 // from them when its table, a cell per value of its bits, fits W words with
-// its marginals (one pass).  A table padded to powers of two gives the same
+// its marginals (one pass) and is not much larger than its own (of more
+// columns than the byte form has loops for: whatever its size).  A table padded to powers of two gives the same
 // statistic: the cells of categories that are not there are 0 in rows, columns
 // or strata that are 0, which add nothing.
 BNS_INLINE void stage_test_bits(const Grp &g, const Desc &q, TestSh &t, const DepthArgs &A, uint32_t W) {
@@ -1012,7 +1013,11 @@ BNS_INLINE void stage_test_bits(const Grp &g, const Desc &q, TestSh &t, const De
         const int nb = __popcll(one) + 2 * __popcll(two);
         const uint32_t bx = __shfl(b, 0, 64), by = __shfl(b, 1, 64);
         const uint64_t need = (1ull << nb) + ((uint64_t)((1u << bx) + (1u << by) + 1u) << (nb - (int)(bx + by)));
-        const bool fits = nb >= kMinPlaneBits && nb <= kMaxPlaneBits && need <= W;
+        float pad = (float)(1u << b) / (float)v.card;
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) pad *= __shfl_xor(pad, off, 64);
+        const bool worth = nc > kByteCols ? nb <= kMaxPlaneBitsWide : nb <= kMaxPlaneBits && pad <= kMaxPlanePad;
+        const bool fits = nb >= kMinPlaneBits && worth && need <= W;
         if (fits) {
             const uint8_t *planes = (const uint8_t *)bp.planes;
             const uint64_t step = bp.plane_bytes;
@@ -1462,7 +1467,8 @@ struct Batch {
 // a separate instance keeps that path's registers out of the per-test one (0).
 // 2: the per-test instance for depths up to kNarrowDepth (tests of at most
 // four columns), without the wider counting loops (fewer spilled registers).
-// 4: the per-test instance that counts from bit planes (those the planes fit);
+// 4: the per-test instance of depth 2 that counts from bit planes (those the
+// planes fit), 6: that of deeper depths, with the wider counting loops;
 // 5: the per-test instance of deep depths, whose units share the passes of
 // tests with tables larger than the LDS.
 template <int LGB, bool VERIFY, bool GENERAL, int UNITS = 0>
@@ -1480,7 +1486,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     // per-group tallies (kept in LDS: no vector registers across tests)
     __shared__ unsigned long long tal_exec[kWaves], tal_re[kWaves];
     __shared__ double tal_bytes[kWaves];
-    constexpr bool BITS = UNITS == 4, SHARE = UNITS == 5;
+    constexpr bool BITS = UNITS == 4 || UNITS == 6, SHARE = UNITS == 5;
     Ctl *c = A.ctl;
     const unsigned long long t_enter = wall_clock64();
     // Everything the workgroup needs from the control block and the search
@@ -1530,7 +1536,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     const long long Lc = uni(hdr.Lc);
     const uint64_t cap = uni(hdr.cap);
     const int mode = uni(hdr.mode);
-    if (uni(hdr.xy) != (UNITS == 1 ? 1 : 0) || (UNITS == 2 && d > kNarrowDepth) || (BITS && !A.bits.prob)) {
+    if (uni(hdr.xy) != (UNITS == 1 ? 1 : 0) || ((UNITS == 2 || UNITS == 4) && d > kNarrowDepth) || (BITS && !A.bits.prob)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) c->error = kDevUnitMismatch;
         return;
     }
@@ -1667,7 +1673,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
                 }
             }
             for (;;) {
-                const TestOut o = run_test<VERIFY, GENERAL, UNITS == 2 || BITS || SHARE ? kNarrowDepth + 2 : kMaxCols, SHARE, BITS>(
+                const TestOut o = run_test<VERIFY, GENERAL, UNITS == 2 || UNITS == 4 || SHARE ? kNarrowDepth + 2 : kMaxCols, SHARE, BITS>(
                     g, t, region, W, A.tile, uni(q.alpha), nullptr, src);
                 if (g.rank == 0 && !(src.part == 1 && src.c0 > 0) && src.part != 2)
                     tal_bytes[ti] += (double)q.ncols * (double)(src.s1 - src.s0);
@@ -2251,6 +2257,10 @@ static auto depth_tests_kernel(const DepthArgs &a, int units) -> decltype(&k_dep
         if (general) return &k_depth_tests<0, false, true, 4>;
         return a.grab_block_log2 ? &k_depth_tests<kGrabRunLog2, false, false, 4> : &k_depth_tests<0, false, false, 4>;
     }
+    if (units == 6) {
+        if (general) return &k_depth_tests<0, false, true, 6>;
+        return a.grab_block_log2 ? &k_depth_tests<kGrabRunLog2, false, false, 6> : &k_depth_tests<0, false, false, 6>;
+    }
     if (units == 5) {
         if (general) return &k_depth_tests<0, false, true, 5>;
         return a.grab_block_log2 ? &k_depth_tests<kGrabRunLog2, false, false, 5> : &k_depth_tests<0, false, false, 5>;
@@ -2294,6 +2304,9 @@ hipError_t allow_dynamic_lds(int bytes) {
                          (const void *)k_depth_tests<0, false, false, 4>,
                          (const void *)k_depth_tests<kGrabRunLog2, false, false, 4>,
                          (const void *)k_depth_tests<0, false, true, 4>,
+                         (const void *)k_depth_tests<0, false, false, 6>,
+                         (const void *)k_depth_tests<kGrabRunLog2, false, false, 6>,
+                         (const void *)k_depth_tests<0, false, true, 6>,
                          (const void *)k_depth_tests<0, false, false, 5>,
                          (const void *)k_depth_tests<kGrabRunLog2, false, false, 5>,
                          (const void *)k_depth_tests<0, false, true, 5>,
