@@ -272,8 +272,11 @@ constexpr int64_t kBitSamples = 1 << 17;
 // their marginals): tests are few and many of their tables larger than the
 // LDS, so that a test has several units, which share its passes (220 x 100,000
 // of up to five categories: 168 tests of depth 5 503 -> 196 us, 252 of depth 6
-// 761 -> 379 us).  A test of one pass pays 3 - 8 us for that instance's
-// registers and cold code (depth 5 of 61 x 49,993), so it starts here.
+// 761 -> 379 us).  A test of one pass pays 3 - 11 us for that instance's
+// registers and cold code (depth 5 of 61 x 49,993; of 60 x 130,000), so it
+// starts here.  It keeps the byte loops of five and six columns: variables of
+// up to eight categories reach it at depths 3 and 4 (157 tests of depth 4 of 60
+// x 50,000 226 us without them, 151 with them, 173 without shared passes).
 constexpr double kDeepCells = 4096.0;
 // Work units of depth d (the rule the depth preparation applies).
 inline int depth_units(const DepthArgs &a, int d) {

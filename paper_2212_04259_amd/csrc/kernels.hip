@@ -1673,7 +1673,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
                 }
             }
             for (;;) {
-                const TestOut o = run_test<VERIFY, GENERAL, UNITS == 2 || UNITS == 4 || SHARE ? kNarrowDepth + 2 : kMaxCols, SHARE, BITS>(
+                const TestOut o = run_test<VERIFY, GENERAL, UNITS == 2 || UNITS == 4 ? kNarrowDepth + 2 : kMaxCols, SHARE, BITS>(
                     g, t, region, W, A.tile, uni(q.alpha), nullptr, src);
                 if (g.rank == 0 && !(src.part == 1 && src.c0 > 0) && src.part != 2)
                     tal_bytes[ti] += (double)q.ncols * (double)(src.s1 - src.s0);

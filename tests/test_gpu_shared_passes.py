@@ -1,0 +1,42 @@
+"""Deep depths, whose instance shares a test's passes among its units: no slower
+than the instance without (the same search with constant two-category columns
+added, which take part in depth 0 only and lower the mean cardinality that
+decides), and with the same tests.
+"""
+
+import numpy as np
+import pytest
+
+from bnsynth import make_dataset
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bns():
+    import paper_2212_04259_amd as b
+    b.load()
+    return b
+
+
+def _stats(bns, data, cards, depth):
+    h = bns.bns_dataset_create(data, cards)
+    runs = [bns.bns_pc_skeleton_dataset(h, 0.05, depth).stats[depth] for _ in range(15)]
+    return float(np.median([s["span_seconds"] for s in runs])), runs[0]["tests_required"]
+
+
+def _both(bns, edges, hi, m, seed, depth):
+    n = 60
+    ds = make_dataset(n, edges, 3, 2, hi, 0.5, m, seed=seed)
+    print(f"depth {depth} of {n} x {m}, up to {hi} categories", flush=True)
+    shared, tests = _stats(bns, ds.data, ds.cards, depth)
+    pad = np.zeros((3 * n, m), np.uint8), np.full(3 * n, 2, np.uint8)
+    alone, tests2 = _stats(bns, np.concatenate([ds.data, pad[0]]), np.concatenate([ds.cards, pad[1]]), depth)
+    assert tests == tests2 > 0
+    print(f"{tests} tests: {shared * 1e6:.1f} us, without shared passes {alone * 1e6:.1f} us", flush=True)
+    return shared, alone
+
+
+def test_six_columns(bns):
+    shared, alone = _both(bns, 78, 8, 50_000, 4, 4)
+    assert shared < 1.1 * alone
