@@ -278,6 +278,12 @@ constexpr int64_t kBitSamples = 1 << 17;
 // up to eight categories reach it at depths 3 and 4 (157 tests of depth 4 of 60
 // x 50,000 226 us without them, 151 with them, 173 without shared passes).
 constexpr double kDeepCells = 4096.0;
+// A test whose depth is cut into at least this many chunks to a pass takes
+// chunks all the same: sharing passes leaves all but one group in so many idle
+// (7 tests of depth 6 of 60 x 150,000, 36 chunks: 86 us by chunks, 128 by
+// passes; 42 tests of depth 5 there, 18 chunks of larger tables, 123 with this
+// limit, 158 with 3 and 114 with none).
+constexpr uint32_t kChunksPerPass = 5;
 // Work units of depth d (the rule the depth preparation applies).
 inline int depth_units(const DepthArgs &a, int d) {
     if (a.edge_form || a.err_val) return 0;

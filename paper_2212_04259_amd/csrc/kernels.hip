@@ -1647,11 +1647,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
                 const int64_t s0 = (int64_t)chunk * Lc;
                 nch = (uint32_t)((qm + Lc - 1) / Lc);
                 const uint32_t np = SHARE ? test_passes(t, W, g.size) : 1u;
-                if (np > 2) {
+                if (np > 2 && (uint64_t)C < kChunksPerPass * np) {
                     // a table of several passes: its units take passes, not
                     // chunks of samples, which would all go through every
                     // pass and merge a table larger than the LDS (with two
-                    // passes the shorter counts of chunks make up for that)
+                    // passes, or many chunks to a pass, their shorter counts
+                    // make up for that)
                     nch = min((uint32_t)C, np);
                     if (4ull * (uint64_t)nch > cap) nch = 1;
                     if ((uint32_t)chunk >= nch) continue;

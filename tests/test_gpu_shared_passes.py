@@ -40,3 +40,10 @@ def _both(bns, edges, hi, m, seed, depth):
 def test_six_columns(bns):
     shared, alone = _both(bns, 78, 8, 50_000, 4, 4)
     assert shared < 1.1 * alone
+
+
+@pytest.mark.parametrize("edges,hi,seed,depth", [(78, 5, 9, 5), (90, 4, 13, 6), (90, 6, 14, 6), (90, 6, 15, 5)])
+def test_few_tests(bns, edges, hi, seed, depth):
+    # 7 to 24 tests, 26 chunks of samples each
+    shared, alone = _both(bns, edges, hi, 130_000, seed, depth)
+    assert shared < 1.15 * alone
