@@ -1210,6 +1210,11 @@ BNS_INLINE TestOut run_test(const Grp &g, TestSh &t, uint32_t *lds, uint32_t W, 
     // fitted in one pass, otherwise by a second counting pass.
     const uint32_t *tab = nullptr;
     bool fp64 = tile.fp64 != 0;
+    // (a test whose passes are shared is counted again by one group alone, so
+    // where alpha is within the band of 0, and nearly every dependent decision
+    // is made again, its groups sum in FP64 at once)
+    const bool at_once = kSearch && src.part != 0 && !fp64 && alpha <= tile.band;
+    fp64 = fp64 || at_once;
     const int stat = kGeneral ? tile.stat : 0;
     const bool adj = kGeneral && tile.df_rule != 0;
     double g2 = 0.0, p = 1.0, p_first = 1.0;
@@ -1240,8 +1245,9 @@ BNS_INLINE TestOut run_test(const Grp &g, TestSh &t, uint32_t *lds, uint32_t W, 
             o.g2_first = g2;
             p_first = p;
         }
-        if (fp64 || df <= 0) break;
         const double gap = fabs(p - alpha);
+        if (at_once && df > 0 && gap < tile.band) o.flags |= 2;
+        if (fp64 || df <= 0) break;
         // propagate the FP32 error bound of the statistic through the tail's slope
         const double dp = tl.dens * 0.5 * g2 * fp32_g2_rel_bound(P, g.size);
         if (!(gap < tile.band || gap < 4.0 * dp)) break;
