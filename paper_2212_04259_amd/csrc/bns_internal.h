@@ -14,6 +14,7 @@ constexpr int kWaves = kWG / 64;
 // depth 0), so no admissible test has more than 22 conditioning variables.
 constexpr int kMaxZ = 22;
 constexpr int kMaxCols = kMaxZ + 2;
+constexpr int kByteCols = 6;  // columns up to which counting from bytes has a loop of its own
 constexpr int kBinomK = kMaxZ + 1;  // binomial table columns: k = 0..kMaxZ
 constexpr int kMaxLevels = 64;      // ticket levels: level L holds test ranks [2^L - 1, 2^(L+1) - 1)
 constexpr uint32_t kMaxCells = 1u << 24;  // largest contingency table (cells)

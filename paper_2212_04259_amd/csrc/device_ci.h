@@ -673,7 +673,6 @@ BNS_INLINE void count_range(const TestSh &t, uint32_t *tab, uint32_t cbase, uint
 // The order of the samples within a word does not matter; samples past the
 // end have no bit set and count into cell 0, which starts that much below 0.
 // ---------------------------------------------------------------------------
-constexpr int kByteCols = 6;       // columns up to which the byte form has loops of its own
 constexpr int kMinPlaneBits = 4;   // (fewer: nearly every variable constant)
 // A table of 2^bits cells larger than this, or than kMaxPlanePad times the
 // test's own, loses more copies of it (and bank conflicts, and cells to clear

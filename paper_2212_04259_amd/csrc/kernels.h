@@ -251,7 +251,7 @@ hipError_t launch_depth_prepare(const DepthArgs &a, hipStream_t s);   // snapsho
 // columns (the instance without the wider counting loops, whose registers
 // otherwise spill), 3 units of the bit-plane kernel (launch_depth1_bits), 4 one
 // test counted from bit planes (depth 2), 5 one test whose passes its units
-// share, 6 as 4 at deeper depths (with the wider counting loops, for the tests
+// share (7: of at most kByteCols columns), 6 as 4 at deeper depths (with the wider counting loops, for the tests
 // that stay with the bytes: without them five columns took 102 us instead of
 // 54 at depth 3 of 60 x 150,000); the host's choice for a depth must match depth_units().
 hipError_t launch_depth_tests(const DepthArgs &a, int grid, hipStream_t s,
@@ -274,9 +274,10 @@ constexpr int64_t kBitSamples = 1 << 17;
 // of up to five categories: 168 tests of depth 5 503 -> 196 us, 252 of depth 6
 // 761 -> 379 us).  A test of one pass pays 3 - 11 us for that instance's
 // registers and cold code (depth 5 of 61 x 49,993; of 60 x 130,000), so it
-// starts here.  It keeps the byte loops of five and six columns: variables of
-// up to eight categories reach it at depths 3 and 4 (157 tests of depth 4 of 60
-// x 50,000 226 us without them, 151 with them, 173 without shared passes).
+// starts here.  Variables of up to eight categories reach it at depths 3 and 4,
+// in an instance with the byte loops of five and six columns (157 tests of
+// depth 4 of 60 x 50,000 226 us without them, 151 with them, 173 without shared
+// passes); deeper ones leave them out (220 x 100,000: depth 5 394 and 379 us).
 constexpr double kDeepCells = 4096.0;
 // A test whose depth is cut into at least this many chunks to a pass takes
 // chunks all the same: sharing passes leaves all but one group in so many idle
@@ -288,7 +289,7 @@ constexpr uint32_t kChunksPerPass = 5;
 inline int depth_units(const DepthArgs &a, int d) {
     if (a.edge_form || a.err_val) return 0;
     if (a.bits_policy && d == 1) return 3;
-    if (d >= a.deep_depth) return 5;
+    if (d >= a.deep_depth) return d + 2 <= kByteCols ? 7 : 5;
     if (a.bits_policy && d > 1 && a.m_max >= kBitSamples) return d <= kNarrowDepth ? 4 : 6;
     if (a.xy_policy == 1 && d == 1 && a.round_width == 0) return 1;
     if (d <= kNarrowDepth && a.tile.stat == 0 && a.tile.df_rule == 0) return 2;

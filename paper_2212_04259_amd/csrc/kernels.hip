@@ -1470,7 +1470,8 @@ struct Batch {
 // 4: the per-test instance of depth 2 that counts from bit planes (those the
 // planes fit), 6: that of deeper depths, with the wider counting loops;
 // 5: the per-test instance of deep depths, whose units share the passes of
-// tests with tables larger than the LDS.
+// tests with tables larger than the LDS; 7: the same for tests of at most
+// kByteCols columns, with their counting loops.
 template <int LGB, bool VERIFY, bool GENERAL, int UNITS = 0>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_depth_tests(DepthArgs A) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
@@ -1486,7 +1487,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     // per-group tallies (kept in LDS: no vector registers across tests)
     __shared__ unsigned long long tal_exec[kWaves], tal_re[kWaves];
     __shared__ double tal_bytes[kWaves];
-    constexpr bool BITS = UNITS == 4 || UNITS == 6, SHARE = UNITS == 5;
+    constexpr bool BITS = UNITS == 4 || UNITS == 6, SHARE = UNITS == 5 || UNITS == 7;
     Ctl *c = A.ctl;
     const unsigned long long t_enter = wall_clock64();
     // Everything the workgroup needs from the control block and the search
@@ -1536,7 +1537,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     const long long Lc = uni(hdr.Lc);
     const uint64_t cap = uni(hdr.cap);
     const int mode = uni(hdr.mode);
-    if (uni(hdr.xy) != (UNITS == 1 ? 1 : 0) || ((UNITS == 2 || UNITS == 4) && d > kNarrowDepth) || (BITS && !A.bits.prob)) {
+    if (uni(hdr.xy) != (UNITS == 1 ? 1 : 0) || ((UNITS == 2 || UNITS == 4) && d > kNarrowDepth) || (UNITS == 5 && d + 2 <= kByteCols) || (BITS && !A.bits.prob)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) c->error = kDevUnitMismatch;
         return;
     }
@@ -1674,7 +1675,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
                 }
             }
             for (;;) {
-                const TestOut o = run_test<VERIFY, GENERAL, UNITS == 2 || UNITS == 4 ? kNarrowDepth + 2 : kMaxCols, SHARE, BITS>(
+                const TestOut o = run_test<VERIFY, GENERAL, UNITS == 2 || UNITS == 4 || UNITS == 5 ? kNarrowDepth + 2 : kMaxCols, SHARE, BITS>(
                     g, t, region, W, A.tile, uni(q.alpha), nullptr, src);
                 if (g.rank == 0 && !(src.part == 1 && src.c0 > 0) && src.part != 2)
                     tal_bytes[ti] += (double)q.ncols * (double)(src.s1 - src.s0);
@@ -2258,6 +2259,10 @@ static auto depth_tests_kernel(const DepthArgs &a, int units) -> decltype(&k_dep
         if (general) return &k_depth_tests<0, false, true, 4>;
         return a.grab_block_log2 ? &k_depth_tests<kGrabRunLog2, false, false, 4> : &k_depth_tests<0, false, false, 4>;
     }
+    if (units == 7) {
+        if (general) return &k_depth_tests<0, false, true, 7>;
+        return a.grab_block_log2 ? &k_depth_tests<kGrabRunLog2, false, false, 7> : &k_depth_tests<0, false, false, 7>;
+    }
     if (units == 6) {
         if (general) return &k_depth_tests<0, false, true, 6>;
         return a.grab_block_log2 ? &k_depth_tests<kGrabRunLog2, false, false, 6> : &k_depth_tests<0, false, false, 6>;
@@ -2305,6 +2310,9 @@ hipError_t allow_dynamic_lds(int bytes) {
                          (const void *)k_depth_tests<0, false, false, 4>,
                          (const void *)k_depth_tests<kGrabRunLog2, false, false, 4>,
                          (const void *)k_depth_tests<0, false, true, 4>,
+                         (const void *)k_depth_tests<0, false, false, 7>,
+                         (const void *)k_depth_tests<kGrabRunLog2, false, false, 7>,
+                         (const void *)k_depth_tests<0, false, true, 7>,
                          (const void *)k_depth_tests<0, false, false, 6>,
                          (const void *)k_depth_tests<kGrabRunLog2, false, false, 6>,
                          (const void *)k_depth_tests<0, false, true, 6>,
