@@ -16,6 +16,7 @@
 #include <stdint.h>
 
 #include "bns_internal.h"
+#include "strata.h"
 
 #define BNS_INLINE __device__ __forceinline__
 
@@ -885,9 +886,9 @@ BNS_INLINE double adj_df_partial(const Grp &g, const uint32_t *rows, const uint3
 }
 
 // Statistic (FP32) and adjusted df of the strata of one pass of a table of
-// RX x ry cells each, a stratum per lane: its marginals stay in registers.  A
-// pass has hundreds of strata, whose marginal tables took 10 - 23 k cycles and
-// their cells 6 k more.
+// RX x ry cells each, a stratum per lane (strata_by_lane): its marginals stay in
+// registers.  The marginal tables of hundreds of strata took 10 - 23 k cycles
+// and their cells 6 k more.
 template <int RX>
 BNS_INLINE void strata_partial(const Grp &g, const uint32_t *tab, uint32_t ry, uint32_t Zc, int stat, float &acc,
                                double *df_adj) {
@@ -1111,7 +1112,7 @@ BNS_INLINE double table_pass(const Grp &g, TestSh &t, const Plan &P, uint32_t *l
         if (gtab)
             for (uint32_t i = g.rank; i < Tc; i += g.size) gtab[P.rxy * z0 + i] = red[i];
         if constexpr (kSearch) {
-            if (!fp64 && chunked && P.rx >= 2u && P.rx <= 5u) {
+            if (!fp64 && chunked && strata_by_lane(P.rx, P.zc_per, (uint32_t)g.size)) {
                 double *const dp = df_adj ? &dfp : nullptr;
                 switch (P.rx) {
                     case 2: strata_partial<2>(g, red, P.ry, Zc, stat, part32, dp); break;
@@ -1146,16 +1147,6 @@ BNS_INLINE double stat_fp64_resident(const Grp &g, TestSh &t, const Plan &P, con
     const uint32_t *strata = cols + P.ry * Zc;
     const double part = stat_partial<double>(g, tab, rows, cols, strata, P.rx, P.ry, Zc, stat);
     return (stat ? 1.0 : 2.0) * g.sum(part, t);
-}
-
-// Relative error bound of the FP32 G^2 sum: every summand is non-negative and
-// carries at most a few tens of ulp of error (conversions, reciprocals, the
-// series or the log2), and each lane adds up to ceil(cells/lanes) of them
-// before a tree, so the relative error stays below (32 + cells/lanes) * 2^-24
-// per pass.
-BNS_INLINE double fp32_g2_rel_bound(const Plan &P, int S) {
-    const double per_lane = (double)(P.rxy * P.zc_per) / (double)S + 1.0;
-    return (32.0 + per_lane) * 5.96e-8 * (double)P.nchunks + 1e-6;
 }
 
 // Tail of the group (chi2_tail_wave needs a whole wave; a workgroup lets its
@@ -1248,7 +1239,9 @@ BNS_INLINE TestOut run_test(const Grp &g, TestSh &t, uint32_t *lds, uint32_t W, 
         if (at_once && df > 0 && gap < tile.band) o.flags |= 2;
         if (fp64 || df <= 0) break;
         // propagate the FP32 error bound of the statistic through the tail's slope
-        const double dp = tl.dens * 0.5 * g2 * fp32_g2_rel_bound(P, g.size);
+        const bool by_lane = kSearch && P.nchunks > 1 && strata_by_lane(P.rx, P.zc_per, (uint32_t)g.size);
+        const double rel = fp32_sum_bound(lane_terms(P.rxy, P.zc_per, (uint32_t)g.size, by_lane), P.nchunks);
+        const double dp = tl.dens * 0.5 * g2 * rel;
         if (!(gap < tile.band || gap < 4.0 * dp)) break;
         o.flags |= 2;
         if (P.nchunks > 1) {
