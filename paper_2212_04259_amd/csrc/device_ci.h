@@ -1201,9 +1201,9 @@ BNS_INLINE TestOut run_test(const Grp &g, TestSh &t, uint32_t *lds, uint32_t W, 
     const uint32_t *tab = nullptr;
     bool fp64 = tile.fp64 != 0;
     // (a test whose passes are shared is counted again by one group alone, so
-    // where alpha is within the band of 0, and nearly every dependent decision
-    // is made again, its groups sum in FP64 at once)
-    const bool at_once = kSearch && src.part != 0 && !fp64 && alpha <= tile.band;
+    // where alpha is within the band of 0 or 1, and nearly every dependent or
+    // independent decision is made again, its groups sum in FP64 at once)
+    const bool at_once = kSearch && src.part != 0 && !fp64 && fmin(alpha, 1.0 - alpha) <= tile.band;
     fp64 = fp64 || at_once;
     const int stat = kGeneral ? tile.stat : 0;
     const bool adj = kGeneral && tile.df_rule != 0;

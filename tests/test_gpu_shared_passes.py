@@ -94,3 +94,10 @@ def test_few_strata(bns, cards, depth):
     shared, alone = _compare_spans(bns, data, c, depth, 0.9995, f"cards {cards}", 60, split_min_samples=1024, statistic=1,
                                    df_rule=1)
     assert shared < alone
+
+
+def test_large_alpha(bns):
+    # alpha within the re-check band of 1
+    data, c = _columns([3, 60, 3, 3, 3, 3, 3], 100_001, seed=1)
+    shared, alone = _compare_spans(bns, data, c, 5, 0.9995, "alpha 0.9995", 60, split_min_samples=1024)
+    assert shared < alone
