@@ -228,7 +228,6 @@ struct DevCtx {
     }
     std::vector<std::unique_ptr<GraphEntry>> graphs;  // captured depth launches
     int search_lds = 0;  // default dynamic LDS of the skeleton test kernel (bytes)
-    bool last_bits = false;  // the last search ran depths 0 and 1 from bit planes
     int last_sequences = 0;  // depth sequences the last finished search needed
     void *hres = nullptr;    // pinned staging for result downloads
     size_t hres_bytes = 0;
@@ -1552,7 +1551,6 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     if (pp.on) {
         a.pairs = pair_args(dc, pp, dc.setup.as<char>(), o_gp, o_ohvar, o_ohcat, o_varoh);
     }
-    dc.last_bits = bits;
     if (bits) {
         char *sb = dc.setup.as<char>();
         a.bits.prob = (const BitProb *)(sb + o_bits);
@@ -1812,6 +1810,7 @@ static bns_status run_batched(DevCtx &dc, const bns_dataset *const *ds, int32_t 
     std::vector<std::unique_ptr<bns_skeleton>> sks((size_t)P);
     for (int32_t k = 0; k < P; ++k) {
         sks[k].reset(new bns_skeleton());
+        sks[k]->planes = bits;
         bns_skeleton *sk = sks[k].get();
         const int n = ds[k]->n;
         const int64_t base = probs[k].adj_off, nn = (int64_t)n * n;
@@ -2163,12 +2162,14 @@ extern "C" bns_status bns_autotune(const bns_dataset *const *ds, int32_t n_probl
             }
     }
     std::vector<bns_skeleton *> outs((size_t)n_problems, nullptr);
+    bool ran_planes = false;  // the last timed search ran depths 0 and 1 from bit planes
     auto timed = [&](const bns_options &c, double *sec) -> bns_status {
         std::vector<double> t;
         for (int r = 0; r < reps + 1; ++r) {  // first run warms caches and graphs
             const auto t0 = std::chrono::steady_clock::now();
             bns_status s2 = bns_pc_skeleton_batch(ds, n_problems, alpha, max_depth, &c, outs.data());
             const auto t1 = std::chrono::steady_clock::now();
+            if (s2 == BNS_OK) ran_planes = outs[0]->planes;
             for (auto *h : outs) bns_skeleton_free(h);
             if (s2 != BNS_OK) return s2;
             if (r > 0) t.push_back(std::chrono::duration<double>(t1 - t0).count());
@@ -2181,14 +2182,7 @@ extern "C" bns_status bns_autotune(const bns_dataset *const *ds, int32_t n_probl
     double cur_t = 0.0;
     st = timed(cur, &cur_t);
     if (st != BNS_OK) return st;
-    bool planes = false;  // depths 0 and 1 ran from bit planes
-    {
-        DevCtx *dc = nullptr;
-        st = get_ctx(ds[0]->device, &dc);
-        if (st != BNS_OK) return st;
-        std::lock_guard<std::mutex> lk(dc->mu);
-        planes = dc->last_bits;
-    }
+    const bool planes = ran_planes;  // under the options as given
     // Per depth: one wave or one workgroup per test, whichever ran that
     // depth's test kernel in less time (device-clock spans).  The skeleton,
     // and so each depth's edges and tests, is the same either way.

@@ -25,6 +25,7 @@ struct bns_skeleton {
     std::vector<int32_t> depth;   // n x n, removal depth or -1
     std::vector<int64_t> sepoff;  // n x n, offset of the pair's sepset in pool or -1
     bool full = false;
+    bool planes = false;  // a search that ran depths 0 and 1 from bit planes
     // compact: pool records by pair, made when a sepset is first asked for
     // (open addressing, record + 1, 0 = empty)
     mutable std::vector<uint32_t> slot;
