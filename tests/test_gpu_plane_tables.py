@@ -50,6 +50,36 @@ def test_tables(bns, orc, cards, m):
         compare_with_oracle(bns.bns_pc_skeleton(data, cards, 0.01, 4, o), ref, f"{cards.tolist()} m={m} {opt}")
 
 
+@pytest.mark.parametrize("statistic,df_rule,precision", [(1, 0, 0), (0, 1, 0), (1, 1, 0), (0, 0, 1), (1, 1, 1)])
+@pytest.mark.parametrize("split", [0, -1])
+def test_other_statistics(bns, orc, statistic, df_rule, precision, split):
+    # a table padded to powers of two adds nothing to the statistic or the
+    # adjusted df; a category and a stratum that no sample has, and a variable
+    # of one category
+    data, cards = _chain([3, 5, 4, 2, 5, 3, 1, 4], PLANES_FROM + 33, seed=11 + statistic)
+    data[0][data[0] == 2] = 0
+    data[4][(data[4] == 3) & (data[3] == 1)] = 1
+    print(f"plane tables stat={statistic} df={df_rule} fp64={precision} split={split}", flush=True)
+    ref = orc.pc_skeleton(data, cards, 0.01, 4, statistic=statistic, df_rule=df_rule)
+    o = bns.bns_options_default(depth0=2, statistic=statistic, df_rule=df_rule, precision=precision, split_min_samples=split)
+    got = bns.bns_pc_skeleton(data, cards, 0.01, 4, o)
+    compare_with_oracle(got, ref, f"stat={statistic} df={df_rule} fp64={precision}")
+    assert len(got.stats) > 3
+
+
+@pytest.mark.parametrize("statistic,df_rule", [(0, 0), (1, 1)])
+def test_long_and_short_datasets(bns, orc, statistic, df_rule):
+    # the longest one decides for the batch
+    sizes = [PLANES_FROM + 33, 1_000, 31, 20_001, 129]
+    sets = [_chain([3, 5, 4, 2, 4, 3, 2, 5], m, seed=40 + k) for k, m in enumerate(sizes)]
+    print("plane tables, long and short datasets", flush=True)
+    hs = [bns.bns_dataset_create(d, c) for d, c in sets]
+    o = bns.bns_options_default(depth0=2, statistic=statistic, df_rule=df_rule)
+    outs = bns.bns_pc_skeleton_batch(hs, [0.01] * len(hs), [-1] * len(hs), o)
+    for (d, c), m, got in zip(sets, sizes, outs):
+        compare_with_oracle(got, orc.pc_skeleton(d, c, 0.01, -1, statistic=statistic, df_rule=df_rule), f"m={m}")
+
+
 @pytest.mark.parametrize("seed", [3, 4])
 def test_no_slower_than_from_bytes(bns, seed):
     # five columns of up to five categories: just below and just above the rule
