@@ -18,16 +18,16 @@ __host__ __device__ inline bool strata_by_lane(uint32_t rx, uint32_t zc_per, uin
 }
 
 // Terms one lane adds in a pass at most.
-__host__ __device__ inline uint32_t lane_terms(uint32_t rxy, uint32_t zc_per, uint32_t lanes, bool by_lane) {
-    return by_lane ? rxy * ((zc_per + lanes - 1u) / lanes) : (rxy * zc_per + lanes - 1u) / lanes;
+__host__ __device__ inline double lane_terms(uint32_t rxy, uint32_t zc_per, uint32_t lanes, bool by_lane) {
+    return by_lane ? (double)(rxy * ((zc_per + lanes - 1u) / lanes)) : (double)(rxy * zc_per) / (double)lanes + 1.0;
 }
 
 // Relative error bound of the FP32 G^2 sum: every summand is non-negative and
 // carries at most a few tens of ulp of error (conversions, reciprocals, the
 // series or the log2), and each lane adds up to lane_terms of them before a
 // tree, so the relative error stays below (32 + terms) * 2^-24 per pass.
-__host__ __device__ inline double fp32_sum_bound(uint32_t terms, uint32_t passes) {
-    return (32.0 + (double)terms) * 5.96e-8 * (double)passes + 1e-6;
+__host__ __device__ inline double fp32_sum_bound(double terms, uint32_t passes) {
+    return (32.0 + terms) * 5.96e-8 * (double)passes + 1e-6;
 }
 
 }  // namespace bns

@@ -13,8 +13,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = """
 #include "strata.h"
 extern "C" int by_lane(unsigned rx, unsigned zc, unsigned lanes) { return bns::strata_by_lane(rx, zc, lanes); }
-extern "C" unsigned terms(unsigned rxy, unsigned zc, unsigned lanes, int by) { return bns::lane_terms(rxy, zc, lanes, by != 0); }
-extern "C" double bound(unsigned terms, unsigned passes) { return bns::fp32_sum_bound(terms, passes); }
+extern "C" double terms(unsigned rxy, unsigned zc, unsigned lanes, int by) { return bns::lane_terms(rxy, zc, lanes, by != 0); }
+extern "C" double bound(double terms, unsigned passes) { return bns::fp32_sum_bound(terms, passes); }
 """
 
 
@@ -31,7 +31,8 @@ def lib(tmp_path_factory):
                    check=True, capture_output=True)
     L = ctypes.CDLL(str(so))
     L.bound.restype = ctypes.c_double
-    L.terms.restype = ctypes.c_uint
+    L.bound.argtypes = [ctypes.c_double, ctypes.c_uint]
+    L.terms.restype = ctypes.c_double
     return L
 
 
@@ -50,5 +51,7 @@ def test_terms_and_lanes(lib, lanes, words, rx, ry):
             per_lane = [len(range(r, rxy * zc, lanes)) for r in range(lanes)]
         most = lib.terms(rxy, zc, lanes, by)
         assert max(per_lane) <= most
+        if not by:  # as for every sum by cells (batches of tests, one-pass tables)
+            assert most == rxy * zc / lanes + 1
         # a sum of k terms in FP32, each with 32 ulp of its own, then a tree of the lanes
         assert lib.bound(most, 3) >= 3 * (32 + max(per_lane)) * 2.0 ** -24
