@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -1212,7 +1213,11 @@ static hipError_t wait_published(hipStream_t s, const volatile unsigned long lon
                                  unsigned long long want) {
     const auto t0 = std::chrono::steady_clock::now();
     for (unsigned it = 1;; ++it) {
-        if (*flag == want) return hipSuccess;
+        if (*flag == want) {
+            // (the results are read after the flag)
+            std::atomic_thread_fence(std::memory_order_acquire);
+            return hipSuccess;
+        }
         if ((it & 63u) != 0u) continue;
         hipError_t e = hipStreamQuery(s);
         if (e == hipErrorNotReady && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(2000))
