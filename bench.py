@@ -457,7 +457,8 @@ def main():
     # follows a depth-0 contraction where all cardinalities are at most 5.  Peak: this device's own rate (bns_lds_increment_rate).
     lds_peak = bns.bns_lds_increment_rate(0)[0]
     planes1 = (launches > 0 and tot[0]["test_group"] == 3 and all(int(d.cards.max()) <= 5 for d in dss)
-               and not any(knobs.get(k) for k in ("depth1", "group_tests", "test_group", "round_tests", "form")))
+               and not any(knobs.get(k) for k in ("depth1", "group_tests", "test_group", "round_tests", "form"))
+               and not (knobs.get("wave_depths", 0) | knobs.get("block_depths", 0)) & 3)
     incs_d = [0.0 if tot[d]["test_group"] == 3 or (d == 1 and planes1) else tot[d]["operand_bytes"] / (d + 2)
               for d in range(launches)]
     per_depth = []

@@ -122,8 +122,9 @@ typedef struct bns_options {
                               Decisions, skeleton and sepsets are those of the normal
                               search.  0 = off (default) */
     int32_t workspace_mb;  /* largest device workspace a call may hold, in MiB (datasets
-                              excluded); a call that needs more fails with BNS_E_NOMEM
-                              before any device work.  0 = no limit (default) */
+                              excluded): bit planes and pairwise tables that do not fit are
+                              left out, and a call that needs more without them fails with
+                              BNS_E_NOMEM before any device work.  0 = no limit (default) */
     int32_t statistic;     /* BNS_STAT_*: the test statistic (default BNS_STAT_G2) */
     int32_t df_rule;       /* BNS_DF_*: the degrees of freedom (default BNS_DF_DECLARED) */
     int32_t depth0;        /* batched form, depth 0 (one marginal test per pair):
@@ -159,22 +160,37 @@ enum {
                             stratum (empty categories and strata dropped); df 0 gives p = 1 */
 };
 
-/* Depth-0 path of the batched form. */
+/* Depth-0 path of the batched form.
+ *
+ * Bit planes: when every variable has at most 5 categories, the search has
+ * depth 1, and the caller leaves the paths and shapes of depths 0 and 1 open
+ * (depth0 AUTO or PAIRS, depth1, group_tests, test_group and round_tests 0, no
+ * bit of depths 0 and 1 in wave_depths and block_depths, no verification, fewer
+ * than 2^26 samples, planes below 4 GiB a dataset, pairwise tables up to 1 GiB
+ * and within workspace_mb), depth 0 makes every pairwise table from the columns'
+ * bit planes and depth 1 counts from both. */
 enum {
-    BNS_DEPTH0_AUTO = 0,    /* PAIRS when the depth's pair-samples (pairs times samples, summed
-                               over the problems) reach 5e8 and the partial tiles fit, else TESTS */
+    BNS_DEPTH0_AUTO = 0,    /* from bit planes where they apply, else PAIRS when the depth's
+                               pair-samples (pairs times samples, summed over the problems)
+                               reach 5e8 and the partial tiles fit, else TESTS.  The
+                               arithmetic is that of PAIRS from 5e8 pair-samples on, below
+                               that options.precision */
     BNS_DEPTH0_TESTS = 1,   /* the depth's tests run in the per-depth test kernel */
     BNS_DEPTH0_PAIRS = 2    /* all pairwise tables at once as one contraction of one-hot
-                               columns (Section IV-B: depth 0 tests every pair); the
-                               statistic is evaluated in FP64.  Verification mode
-                               (report_errors) keeps depth 0 in the test kernel */
+                               columns, or of their bit planes (Section IV-B: depth 0 tests
+                               every pair); the statistic is evaluated in FP64.
+                               Verification mode (report_errors) keeps depth 0 in the test
+                               kernel */
 };
 
 /* Depth-1 path of the batched form. */
 enum {
-    BNS_DEPTH1_AUTO = 0,    /* TESTS (the contraction evaluates every depth-1 test, where the
-                               sequential order stops an edge at its first accepting test:
-                               measured slower on all five benchmark workloads) */
+    BNS_DEPTH1_AUTO = 0,    /* from bit planes where they apply (see the depth-0 paths: ands
+                               and popcounts of plane words, several tests of an edge per
+                               pass), else TESTS (the contraction evaluates every depth-1
+                               test, where the sequential order stops an edge at its first
+                               accepting test: measured slower on all five benchmark
+                               workloads) */
     BNS_DEPTH1_TESTS = 1,   /* the depth's tests run in the per-depth test kernel */
     BNS_DEPTH1_GRAM = 2     /* every depth-1 table as a block of masked Gram matrices: for
                                each node u and category c of u, the one-hot columns of u's
@@ -189,7 +205,8 @@ enum {
 /* Work units of depth 1 in the test kernel (the counterpart of Section IV-B's
  * group of tests of one edge). */
 enum {
-    BNS_GROUP_AUTO = 0,   /* EDGE when the search's columns (variables x samples bytes of
+    BNS_GROUP_AUTO = 0,   /* (leaves depth 1 from bit planes open; in the test kernel:)
+                             EDGE when the search's columns (variables x samples bytes of
                              all its datasets) exceed 64 MiB, a quarter of MI355X's last-level
                              cache (its tests would re-read X and Y from DRAM), else TEST */
     BNS_GROUP_TEST = 1,   /* one test per work unit */
@@ -301,7 +318,9 @@ typedef struct bns_depth_stats {
     int32_t depth;
     int32_t test_group;      /* batched form: lanes per test at this depth, 1 = one wave,
                                 2 = one workgroup, 3 = depth 0 ran as the pair contraction
-                                (bns_ci_pairs' tables); 0 in the plain form */
+                                (bns_ci_pairs' tables); 1 too where depth 1 ran from bit
+                                planes (a wave per edge or segment of its tests); 0 in the
+                                plain form */
     int64_t edges;           /* edges alive when the depth started */
     int64_t tests_required;  /* tests in the canonical sequential order: per edge, up to
                                 and including its first accepting test */

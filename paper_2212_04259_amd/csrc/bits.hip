@@ -18,8 +18,9 @@
 // share the planes of X and Y, whose conjunctions are formed once per word.
 // The epilogue completes the pass's tables in LDS, one cell per lane,
 // sums the statistic over half-waves, and compares it with the two critical
-// values that enclose the range where the p-value could matter (decided by
-// the FP64 tail as in the test kernel); no tail is evaluated outside it.
+// values beyond which its FP64 decision is certain; between them it is formed
+// again in FP64 and compared with the quantile of alpha itself (a tail is
+// evaluated only there).
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -467,8 +468,8 @@ BNS_INLINE unsigned long long bit_units(unsigned long long units, int p, int lgb
 // consecutive units dealt to p; a wave's first unit is static, the rest are
 // grabbed, from the counter with the most left once its own is used up.
 // What bounds it: the words of X, Y and Z on their way from the L2s (20 to 29
-// bytes per clock and compute unit; the vector ALU is ~45% busy on 1,000
-// variables x 200,000 samples), so a pass takes as many tests of one edge as
+// bytes per clock and compute unit, with two waves per SIMD to wait for them;
+// the vector ALU is ~45% busy on 1,000 variables x 200,000 samples), so a pass takes as many tests of one edge as
 // its counts fit registers, and 16-byte loads.  Against one LDS increment per
 // sample (k_depth_tests): that search's depth 1 15.1 -> 3.0 ms, 220 x 100,000
 // 1.42 -> 0.46 ms, the 64-dataset batch 7.4 -> 2.2 ms, 60 x 50,000 161 -> 98
@@ -608,10 +609,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
 // 16-bit pieces of the adjacency bit rows.  Every pair is tested once, so the
 // depth needs no edge list (records, level order and removals of half a
 // million edges).  What bounds it: a few dependent loads per lane, and the
-// FP32 terms at many pairs.  With the chunk sum and the FP64 pair kernel in
-// its place, depth 0 and its preparation took 220 us more at 1,000 variables,
-// 190 us at 220 (one workgroup's edge list) and 30 us at 20; this kernel takes
-// 74, 22 and 12 us there.
+// FP64 terms at many pairs.  With the chunk sum and the FP64 pair kernel in
+// its place, depth 0 and its preparation took 210 us more at 1,000 variables,
+// 185 us at 220 (one workgroup's edge list) and 30 us at 20; this kernel takes
+// 92, 28 (FP64) and 13 us (FP32) there.
 // ---------------------------------------------------------------------------
 constexpr int kPairSide = 16;
 constexpr int kBitPlanes = kBitCards - 1;
